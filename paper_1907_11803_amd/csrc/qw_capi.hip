@@ -428,6 +428,94 @@ qw_status ooc_query(qw_index *ix, int64_t Q, int K, hipStream_t s, int32_t *out_
     return ooc_answer(ix, Q, a, ix->ws.qrows, out_ids, out_dist, s, io);
 }
 
+// Room for one round of queries; false when the device has none, or when the
+// stream is being captured and the room is not there yet (the per-query
+// kernel, which needs no lists, answers then).
+bool ensure_brute(qw_index *ix, const BrutePlan &p, hipStream_t s)
+{
+    Workspace &w = ix->ws;
+    const size_t q = (size_t)p.chunk;
+    const size_t bmin = sizeof(int32_t) * q * (size_t)p.streams;
+    const size_t bkeys = sizeof(unsigned long long) * q * (size_t)p.cap;
+    // per query: bound, count, flag, fallback entry, list offset; then the
+    // fallback queue's length and work counter
+    const size_t bstate = q * (4 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256;
+    if (w.bf_min.bytes >= bmin && w.bf_keys.bytes >= bkeys && w.bf_state.bytes >= bstate) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (w.bf_min.ensure(bmin) == QW_OK && w.bf_keys.ensure(bkeys) == QW_OK &&
+        w.bf_state.ensure(bstate) == QW_OK)
+        return true;
+    w.bf_min.release();
+    w.bf_keys.release();
+    w.bf_state.release();
+    return false;
+}
+
+// Brute force on the matrix cores, p.chunk queries a round; `fb` is the
+// per-query kernel's setup, for queries whose key list overflowed.
+qw_status brute_mfma(qw_index *ix, const BrutePlan &p, VerifyArgs fb, int64_t Q, hipStream_t s,
+                     int32_t *out_ids, int32_t *out_dist)
+{
+    Workspace &w = ix->ws;
+    auto *coff = w.bf_state.as<unsigned long long>();
+    auto *bound = reinterpret_cast<int32_t *>(coff + p.chunk);
+    auto *count = reinterpret_cast<uint32_t *>(bound) + p.chunk;
+    uint32_t *flag = count + p.chunk;
+    auto *fb_list = reinterpret_cast<int32_t *>(flag + p.chunk);
+    uint32_t *fb_count = reinterpret_cast<uint32_t *>(fb_list) + p.chunk;  // length, work counter
+    const int K = fb.K;
+    for (int64_t q0 = 0; q0 < Q; q0 += p.chunk) {
+        BruteArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.data = ix->data.p;
+        a.queries = static_cast<const uint8_t *>(w.qrows) + q0 * ix->dp;
+        a.n = ix->n;
+        a.dp = ix->dp;
+        a.Q = (int32_t)std::min<int64_t>(p.chunk, Q - q0);
+        a.K = K;
+        a.minima = w.bf_min.as<int32_t>();
+        a.bound = bound;
+        a.count = count;
+        a.flag = flag;
+        a.coff = coff;
+        a.keys = w.bf_keys.as<unsigned long long>();
+        QW_TRY(launch_fill_u32(fb_count, 0u, 2, s));
+        QW_TRY(launch_brute(p, a, s));
+        SelectArgs m;
+        std::memset(&m, 0, sizeof(m));
+        m.keys = a.keys;
+        m.coff = coff;
+        m.ucount = count;
+        m.flag = flag;
+        m.K = K;
+        m.LC = pow2_at_least(std::max(512, 4 * K));
+        m.dtype = ix->dtype;
+        m.dp = ix->dp;
+        m.d = ix->d;
+        m.fb_count = fb_count;
+        m.fb_list = fb_list;
+        m.out_ids = out_ids + q0 * K;
+        m.out_dist = out_dist + q0 * K;
+        QW_TRY(launch_select(m, a.Q, s));
+        fb.queries = a.queries;
+        fb.nitems = 0;
+        fb.in_list = fb_list;
+        fb.in_count = fb_count;
+        fb.counter = fb_count + 1;
+        fb.cap_log2 = 1;
+        fb.limit = 1;
+        fb.buf = (uint32_t)pow2_at_least(std::max(64, 2 * (K + verify_per_iter(ix->dp, ix->dtype))));
+        fb.out_ids = m.out_ids;
+        fb.out_dist = m.out_dist;
+        QW_TRY(launch_verify(fb, (int)std::min<int64_t>(a.Q, 4 * ix->cus), s));
+    }
+    return QW_OK;
+}
+
 qw_status check_index(const qw_index *ix)
 {
     if (!ix) return QW_EINVAL;
@@ -1231,6 +1319,9 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     VerifyArgs a = base_args(ix, K, VM_ALL);
     a.nl = 0;  // no bucket lists: every point
     a.pmagic = 0;
+    BrutePlan bp;
+    if (brute_plan(ix->n, ix->dtype, ix->dp, Q, K, &bp) && ensure_brute(ix, bp, s))
+        return brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist));
     a.nitems = Q;
     a.cap_log2 = 1;
     a.limit = 1;

@@ -134,6 +134,8 @@ struct Workspace {
         vals2, hist, order, binoff, counters, ovf, gscratch, mlpout, scan;
     // flat pipeline
     DevBuf ucount, coff, flag, pkeys, fb;
+    // brute force: stream minima, per-query state, key lists
+    DevBuf bf_min, bf_state, bf_keys;
     // the query rows the kernels of the current call read: the caller's own
     // (no padding needed) or qpad
     const void *qrows = nullptr;
@@ -536,6 +538,26 @@ struct SelectArgs {
     void *out_dist;
     const void *data, *queries;
 };
+
+// Brute force on the matrix cores (qw_brute.hip): one round of Q queries.
+struct BrutePlan {
+    int ks, r, cap, qw, nqt, slabs_s, slabs_c, streams;
+    int64_t chunk;               // queries per round
+};
+struct BruteArgs {
+    const void *data, *queries;  // padded rows of dp bytes
+    int64_t n, rows, stride;     // points; rows of this pass: row i is point i * stride
+    int32_t dp, Q, K;
+    int32_t nqt, qw, slabs, streams, top_bit;
+    uint32_t cap;                // keys per query
+    int32_t *minima;             // [Q][streams]
+    int32_t *bound;              // [Q]: at least the K-th distance
+    uint32_t *count, *flag;      // [Q]: keys found; 1: left to the per-query kernel
+    unsigned long long *coff, *keys;  // [Q]: the query's first key; [Q][cap] (distance << 32) | id
+};
+// false: not applicable (the per-query kernel answers).
+bool brute_plan(int64_t n, int32_t dtype, int32_t dp, int64_t Q, int32_t K, BrutePlan *p);
+qw_status launch_brute(const BrutePlan &p, BruteArgs a, hipStream_t s);
 
 // Staged candidate kernel (qw_opts.stage_split): one workgroup per run of
 // `chunk` consecutive items of the order (classes largest first), LDS caches

@@ -479,6 +479,52 @@ def test_bruteforce_matches_oracle(dtype):
     check_topk(ids, dist, ids_o, dist_o, dtype == "u8")
 
 
+@pytest.mark.parametrize("n,d,Q,K", [
+    (4096, 16, 1, 1), (4097, 17, 3, 10), (5000, 64, 16, 64), (9001, 65, 17, 65),   # one, two steps
+    (20011, 128, 65, 10), (4224, 200, 129, 37), (6001, 256, 257, 100),             # four steps
+    (8191, 257, 33, 16), (5003, 512, 40, 7), (4500, 700, 70, 20), (4100, 1024, 9, 128),
+    (70001, 96, 5, 300), (140003, 32, 2, 1024),                                    # sampled, long lists
+    (4096, 128, 700, 1), (4095, 128, 5, 5), (5000, 1025, 4, 5),                    # rounds of queries; not applicable
+])
+def test_bruteforce_matrix_cores(n, d, Q, K):
+    rng = np.random.default_rng(n + d)
+    centres = rng.integers(0, 256, (40, d))
+    data = np.clip(centres[rng.integers(0, 40, n)] + rng.integers(-9, 10, (n, d)), 0, 255).astype(np.uint8)
+    queries = np.clip(centres[rng.integers(0, 40, Q)] + rng.integers(-9, 10, (Q, d)), 0, 255).astype(np.uint8)
+    p = synth.hash_params(3, 1, 1, d, 1000.0)
+    ix = build(data, p.a, p.b(), 1000.0)
+    ids_o, dist_o = oracle.bruteforce(data, queries, K)
+    for _ in range(2):
+        ids, dist = ix.bruteforce(dev(queries), K)
+        check_topk(ids, dist, ids_o, dist_o, True)
+
+
+@pytest.mark.parametrize("kind", ["equal", "extreme", "sorted"])
+def test_bruteforce_matrix_cores_key_lists(kind):
+    # equal rows overflow every key list (the per-query kernel answers); rows
+    # of 0 and 255 reach the largest distances; blocks of near rows shorter
+    # than the sample's stride in one place of the collection
+    rng = np.random.default_rng(5)
+    n, d, Q, K = 30000, 128, 70, 10
+    data = rng.integers(0, 256, (n, d), dtype=np.uint8)
+    queries = rng.integers(0, 256, (Q, d), dtype=np.uint8)
+    if kind == "equal":
+        data[:] = data[0]
+        queries[::2] = data[0]
+    elif kind == "extreme":
+        data = np.where(rng.random((n, 1)) < 0.5, 0, 255).astype(np.uint8) * np.ones((1, d), np.uint8)
+        queries = np.where(rng.random((Q, d)) < 0.5, 0, 255).astype(np.uint8)
+    else:
+        queries[:] = 128
+        data[5001:5005] = 127
+        data[9000:9007] = 130
+    p = synth.hash_params(3, 1, 1, d, 1000.0)
+    ix = build(data, p.a, p.b(), 1000.0)
+    ids_o, dist_o = oracle.bruteforce(data, queries, K)
+    ids, dist = ix.bruteforce(dev(queries), K)
+    check_topk(ids, dist, ids_o, dist_o, True)
+
+
 def test_huge_w_equals_bruteforce():
     """Every point in one bucket per layer: LSH top-K equals exact kNN."""
     rng = np.random.default_rng(61)
