@@ -150,7 +150,10 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
     for (int pass = 0; pass < 2; ++pass, dry = false) {
         if (!dry) {
             size_t free_b = 0, total_b = 0;
-            if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && extra > free_b) return QW_ENOMEM;
+            if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && extra > free_b &&
+                !(pool_give_back(ix->device) && hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
+                  extra <= free_b))
+                return QW_ENOMEM;
             (void)hipGetLastError();
         }
         const size_t elem = ix->dtype == QW_U8 ? 1 : 4;
@@ -999,7 +1002,18 @@ void qw_free_index(qw_index *ix)
     drop_graphs(ix);
     if (ix->ev_init)
         for (auto &e : ix->ev) (void)hipEventDestroy(e);
-    delete ix;  // the destructor releases the side stream and its events
+    // the device is idle: the larger buffers may serve the next index (the
+    // synchronisation above covers the current device only)
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev == ix->device) {
+        Workspace &w = ix->ws;
+        for (DevBuf *b : {&ix->data, &ix->ids, &w.qpad, &w.h, &w.bstart, &w.bsize, &w.ovf, &w.gscratch,
+                          &w.order, &w.pkeys, &w.bf_min, &w.bf_keys})
+            b->retire(dev);
+        for (DevBuf &t : ix->tabs) t.retire(dev);
+    }
+    (void)hipGetLastError();
+    delete ix;  // the destructor releases the rest, the side stream and its events
 }
 
 qw_status qw_get_index_info(const qw_index *ix, qw_index_info *info)
@@ -1017,9 +1031,10 @@ qw_status qw_get_index_info(const qw_index *ix, qw_index_info *info)
     info->max_bucket = ix->max_bucket;
     const DevBuf *bufs[] = {&ix->a32, &ix->b32, &ix->a_hi, &ix->a_lo, &ix->gb_plain,
                             &ix->gb_fast, &ix->data, &ix->hmin, &ix->hmax, &ix->shift,
-                            &ix->ids, &ix->tab, &ix->tab_off, &ix->tab_mask, &ix->mlp_dev,
+                            &ix->ids, &ix->tab_ptr, &ix->tab_ents, &ix->mlp_dev,
                             &ix->mlp_lane};
     for (const DevBuf *b : bufs) info->device_bytes += (int64_t)b->bytes;
+    for (const DevBuf &t : ix->tabs) info->device_bytes += (int64_t)t.bytes;
     info->has_count_model = ix->mlp.empty() ? 0 : 1;
     info->count_margin = ix->mlp_margin;
     info->probing = ix->probe_mode;

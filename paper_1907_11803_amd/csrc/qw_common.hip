@@ -2,6 +2,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <algorithm>
+#include <mutex>
+#include <vector>
 
 #include "qw_internal.h"
 
@@ -17,6 +19,99 @@ void note_hip_error(hipError_t e, const char *what, const char *file, int line)
         std::fprintf(stderr, "qwlsh: %s\n", g_last_error);
 }
 
+// ---------------------------------------------------------------- block pool
+// Freed device blocks kept for the next buffers of their size.  The driver
+// clears freed memory at 20 to 60 GB/s and an allocation waits for it once
+// the memory never used before has run out (measured: about 280 GB of
+// allocations in, a 1 GiB hipMalloc + hipFree pair goes from 0.3 to 20-60 ms),
+// so a program that builds index after index pays for every byte it frees.
+// Per device at most kPoolBytes in kPoolBlocks blocks, oldest out first; a
+// block that kPoolAge later requests did not want goes back to the driver, and
+// all do when an allocation would not fit beside them.  Only memory that no
+// enqueued work uses is put here, so any thread or stream may take it.
+namespace {
+
+constexpr size_t kPoolBytes = size_t(1) << 30, kPoolMin = size_t(1) << 20;
+constexpr size_t kPoolBlocks = 32;
+constexpr uint64_t kPoolAge = 1024;
+
+struct PoolBlock {
+    void *p;
+    size_t bytes;
+    uint64_t at;  // request count when it came
+};
+struct Pool {
+    std::mutex mu;
+    std::vector<PoolBlock> blocks;  // oldest first
+    size_t total = 0;
+    uint64_t now = 0;
+    void drop(size_t i)
+    {
+        (void)hipFree(blocks[i].p);
+        total -= blocks[i].bytes;
+        blocks.erase(blocks.begin() + (ptrdiff_t)i);
+    }
+};
+constexpr int kPoolDevices = 64;
+
+Pool *pool_of(int dev)
+{
+    static Pool *pools = new Pool[kPoolDevices];  // never destroyed: the runtime may be gone by then
+    return dev >= 0 && dev < kPoolDevices ? &pools[dev] : nullptr;
+}
+
+// A block of `want` bytes, or up to a quarter more.
+void *pool_take(int dev, size_t want, size_t *bytes)
+{
+    Pool *pl = pool_of(dev);
+    if (!pl || want < kPoolMin) return nullptr;
+    std::lock_guard<std::mutex> lock(pl->mu);
+    ++pl->now;
+    while (!pl->blocks.empty() && pl->now - pl->blocks[0].at > kPoolAge) pl->drop(0);
+    size_t best = pl->blocks.size();
+    for (size_t i = 0; i < pl->blocks.size(); ++i)
+        if (pl->blocks[i].bytes >= want && pl->blocks[i].bytes <= want + want / 4 &&
+            (best == pl->blocks.size() || pl->blocks[i].bytes < pl->blocks[best].bytes))
+            best = i;
+    if (best == pl->blocks.size()) return nullptr;
+    void *p = pl->blocks[best].p;
+    *bytes = pl->blocks[best].bytes;
+    pl->total -= *bytes;
+    pl->blocks.erase(pl->blocks.begin() + (ptrdiff_t)best);
+    return p;
+}
+
+bool pool_put(int dev, void *p, size_t bytes)
+{
+    Pool *pl = pool_of(dev);
+    if (!pl || bytes < kPoolMin || bytes > kPoolBytes) return false;
+    std::lock_guard<std::mutex> lock(pl->mu);
+    while (!pl->blocks.empty() && (pl->total + bytes > kPoolBytes || pl->blocks.size() >= kPoolBlocks))
+        pl->drop(0);
+    try {
+        pl->blocks.push_back(PoolBlock{p, bytes, ++pl->now});
+    } catch (...) {
+        return false;
+    }
+    pl->total += bytes;
+    return true;
+}
+
+// Gives every block back; true when there was one.
+bool pool_drain(int dev)
+{
+    Pool *pl = pool_of(dev);
+    if (!pl) return false;
+    std::lock_guard<std::mutex> lock(pl->mu);
+    const bool any = !pl->blocks.empty();
+    while (!pl->blocks.empty()) pl->drop(pl->blocks.size() - 1);
+    return any;
+}
+
+}  // namespace
+
+bool pool_give_back(int dev) { return pool_drain(dev); }
+
 qw_status DevBuf::ensure(size_t want)
 {
     if (want <= bytes && p) return QW_OK;
@@ -25,16 +120,21 @@ qw_status DevBuf::ensure(size_t want)
     if (want == 0) want = 16;
     if (want > (SIZE_MAX >> 1)) return QW_ENOMEM;
     want = (want + 255) & ~size_t(255);
-    // beyond the device's free memory: refused here, whatever the allocator
-    // would do with it
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && want > free_b) return QW_ENOMEM;
-    (void)hipGetLastError();
-    if (hipMalloc(&p, want) != hipSuccess) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) (void)hipGetLastError();
+    p = pool_take(dev, want, &bytes);
+    if (p) return QW_OK;
+    for (int tries = 0;; ++tries) {
+        // beyond the device's free memory: refused here, whatever the
+        // allocator would do with it
+        size_t free_b = 0, total_b = 0;
+        const bool over = hipMemGetInfo(&free_b, &total_b) == hipSuccess && want > free_b;
+        (void)hipGetLastError();
+        if (!over && hipMalloc(&p, want) == hipSuccess) break;
         (void)hipGetLastError();
         p = nullptr;
         bytes = 0;
-        return QW_ENOMEM;
+        if (tries > 0 || !pool_drain(dev)) return QW_ENOMEM;
     }
     bytes = want;
     return QW_OK;
@@ -46,6 +146,12 @@ void DevBuf::release()
     p = nullptr;
     bytes = 0;
     owned = true;
+}
+
+void DevBuf::retire(int dev)
+{
+    if (p && owned && pool_put(dev, p, bytes)) p = nullptr;
+    release();
 }
 
 // ---------------------------------------------------------------- fills
@@ -107,16 +213,32 @@ qw_status launch_iota(int32_t *p, int64_t count, hipStream_t s)
 // ---------------------------------------------------------------- row padding
 // dst rows of dp elements: the first d copied from src rows of d elements, the rest 0.
 
-template <typename T>
-__global__ void pad_rows_kernel(const T *__restrict__ src, int64_t m, int32_t d, int32_t dp,
-                                T *__restrict__ dst)
+// One thread per 16-byte piece of dst; src pieces are read whole when every
+// one of them is aligned (VEC: d elements are whole pieces), else element by
+// element.  Bound by memory: a byte per thread moved 128 MB in 183 us,
+// whole pieces in 41.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(kBlock) void pad_rows_kernel(const T *__restrict__ src, int64_t m, int32_t d,
+                                                          int32_t dp, uint4 *__restrict__ dst)
 {
-    const int64_t total = m * (int64_t)dp;
+    constexpr int E = 16 / (int)sizeof(T);
+    const int32_t parts = dp / E;
+    const int64_t total = m * (int64_t)parts;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
          i += (int64_t)gridDim.x * blockDim.x) {
-        int64_t r = i / dp;
-        int32_t c = (int32_t)(i - r * dp);
-        dst[i] = c < d ? src[r * d + c] : T(0);
+        if (VEC) {  // no padding: one run of pieces
+            dst[i] = reinterpret_cast<const uint4 *>(src)[i];
+            continue;
+        }
+        const int64_t r = total <= 0xFFFFFFFFll ? (int64_t)((uint32_t)i / (uint32_t)parts) : i / parts;
+        const int32_t c = (int32_t)(i - r * parts) * E;
+        union {
+            T e[E];
+            uint4 v;
+        } u;
+#pragma unroll
+        for (int t = 0; t < E; ++t) u.e[t] = c + t < d ? src[r * d + c + t] : T(0);
+        dst[i] = u.v;
     }
 }
 
@@ -124,12 +246,19 @@ qw_status launch_pad_rows(const void *src, int64_t m, int32_t d, int32_t dp, int
                           void *dst, hipStream_t s)
 {
     if (m <= 0) return QW_OK;
-    int g = grid_for(m * (int64_t)dp);
-    if (dtype == QW_U8)
-        pad_rows_kernel<uint8_t><<<g, kBlock, 0, s>>>((const uint8_t *)src, m, d, dp,
-                                                      (uint8_t *)dst);
-    else
-        pad_rows_kernel<float><<<g, kBlock, 0, s>>>((const float *)src, m, d, dp, (float *)dst);
+    const int elem = dtype == QW_U8 ? 1 : 4;
+    const int g = grid_for(m * (int64_t)dp * elem / 16);
+    const bool vec = d == dp && (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    uint4 *out = static_cast<uint4 *>(dst);
+    if (dtype == QW_U8) {
+        const auto *x = static_cast<const uint8_t *>(src);
+        if (vec) pad_rows_kernel<uint8_t, true><<<g, kBlock, 0, s>>>(x, m, d, dp, out);
+        else pad_rows_kernel<uint8_t, false><<<g, kBlock, 0, s>>>(x, m, d, dp, out);
+    } else {
+        const auto *x = static_cast<const float *>(src);
+        if (vec) pad_rows_kernel<float, true><<<g, kBlock, 0, s>>>(x, m, d, dp, out);
+        else pad_rows_kernel<float, false><<<g, kBlock, 0, s>>>(x, m, d, dp, out);
+    }
     QW_HIP(hipGetLastError());
     return QW_OK;
 }

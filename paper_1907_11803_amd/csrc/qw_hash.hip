@@ -801,8 +801,8 @@ qw_status launch_probe_moves(const qw_index *ix, const void *xpad, int64_t Q, ui
 // probes' min-hashes.  KM: k itself (KEXACT) or a bound on it (functions past
 // k skipped).
 constexpr int kProbeBatch = 4;
-// linear probing, two slots (one 64-byte line) per round trip: at a load
-// factor of at most 1/2 most sequences, hits and misses, end within the first
+// linear probing within the key's region, two slots (64 bytes) per round trip:
+// at a load factor of 2/5 most sequences, hits and misses, end within the first
 // pair
 constexpr uint32_t kProbeRound = 2;
 
@@ -812,13 +812,14 @@ constexpr uint32_t kProbeRound = 2;
 // value range, key offset and hash value; move(p): the move of probe p >= 1.
 template <class Field, class Move>
 __device__ inline void probe_layer(int32_t P, uint64_t klo, uint64_t khi, int32_t nbad,
-                                   int32_t badj, const TabEntry *__restrict__ t, uint32_t mask,
-                                   Field field, Move move, int64_t ql, uint32_t *__restrict__ bstart,
+                                   int32_t badj, const TabEntry *__restrict__ t, uint32_t ents,
+                                   int32_t pb, Field field, Move move, int64_t ql, uint32_t *__restrict__ bstart,
                                    uint32_t *__restrict__ bsize, uint32_t *__restrict__ bmh,
                                    float *__restrict__ feats, uint32_t *__restrict__ lsum,
                                    uint32_t *__restrict__ lmh)
 {
     uint32_t lsz = 0, lm = 0xFFFFFFFFu;  // the layer's size sum and min-hash over its probes
+    auto wrap = [&](uint32_t v) { return v < ents ? v : v - ents; };  // a region holds kProbeRound at least
     for (int32_t p0 = 0; p0 < P; p0 += kProbeBatch) {
         uint64_t kl[kProbeBatch], kh[kProbeBatch];
         uint32_t slot[kProbeBatch];
@@ -850,12 +851,15 @@ __device__ inline void probe_layer(int32_t P, uint64_t klo, uint64_t khi, int32_
             }
         }
         TabEntry e[kProbeBatch][kProbeRound];
+        const TabEntry *reg[kProbeBatch];  // the key's region
 #pragma unroll
         for (int b = 0; b < kProbeBatch; ++b) {
-            slot[b] = (uint32_t)key_mix(kl[b], kh[b]) & mask;
+            const uint64_t mix = key_mix(kl[b], kh[b]);
+            slot[b] = key_slot(mix, ents);
+            reg[b] = t + (uint64_t)key_part(mix, pb) * ents;
             if (look[b])
 #pragma unroll
-                for (uint32_t i = 0; i < kProbeRound; ++i) e[b][i] = t[(slot[b] + i) & mask];
+                for (uint32_t i = 0; i < kProbeRound; ++i) e[b][i] = reg[b][wrap(slot[b] + i)];
         }
 #pragma unroll
         for (int b = 0; b < kProbeBatch; ++b) {
@@ -866,10 +870,10 @@ __device__ inline void probe_layer(int32_t P, uint64_t klo, uint64_t khi, int32_
                 bool done = false;
                 for (uint32_t it = 0; !done; it += kProbeRound) {
                     if (it > 0) {  // rare: the first pair held other keys
-                        if (it > mask) break;
-                        slot[b] = (slot[b] + kProbeRound) & mask;
+                        if (it >= ents) break;
+                        slot[b] = wrap(slot[b] + kProbeRound);
 #pragma unroll
-                        for (uint32_t i = 0; i < kProbeRound; ++i) e[b][i] = t[(slot[b] + i) & mask];
+                        for (uint32_t i = 0; i < kProbeRound; ++i) e[b][i] = reg[b][wrap(slot[b] + i)];
                     }
 #pragma unroll
                     for (uint32_t i = 0; i < kProbeRound; ++i) {
@@ -902,8 +906,8 @@ template <int KM, bool KEXACT>
 __global__ __launch_bounds__(kBlock) void probe_kernel(
     const int32_t *__restrict__ h, int64_t Q, int32_t L, int32_t k, int32_t P,
     const int32_t *__restrict__ hmin, const int32_t *__restrict__ hmax,
-    const int32_t *__restrict__ shift, const TabEntry *__restrict__ tab,
-    const long long *__restrict__ tab_off, const uint32_t *__restrict__ tab_mask,
+    const int32_t *__restrict__ shift, const TabEntry *const *__restrict__ tabs,
+    const uint32_t *__restrict__ tab_ents, int32_t pb,
     uint32_t *__restrict__ bstart, uint32_t *__restrict__ bsize, float *__restrict__ feats,
     uint32_t *__restrict__ bmh, const uint8_t *__restrict__ moves, uint32_t *__restrict__ lsum,
     uint32_t *__restrict__ lmh)
@@ -928,8 +932,8 @@ __global__ __launch_bounds__(kBlock) void probe_kernel(
 #pragma unroll
     for (int32_t j = 0; j < KM; ++j)
         if (KEXACT || j < k) hv[j] = hl[j];
-    const TabEntry *t = tab + tab_off[l];
-    const uint32_t mask = tab_mask[l];
+    const TabEntry *t = tabs[l];
+    const uint32_t ents = tab_ents[l];
     __syncthreads();
     if (!live) return;
     // the base key from the fields in range; nbad fields out of range, the
@@ -955,7 +959,7 @@ __global__ __launch_bounds__(kBlock) void probe_kernel(
         hj = hl[j];
     };
     auto move = [&](int32_t p) { return moves ? (int32_t)moves[ql * (P - 1) + (p - 1)] : p - 1; };
-    probe_layer(P, klo, khi, nbad, badj, t, mask, field, move, ql, bstart, bsize, bmh, feats, lsum,
+    probe_layer(P, klo, khi, nbad, badj, t, ents, pb, field, move, ql, bstart, bsize, bmh, feats, lsum,
                 lmh);
 }
 
@@ -970,8 +974,8 @@ qw_status launch_probe(const qw_index *ix, const int32_t *h, int64_t Q, uint32_t
 #define QW_PR(KM, EX)                                                                            \
     probe_kernel<KM, EX><<<g, kBlock, lds, s>>>(                                                  \
         h, Q, ix->L, ix->k, ix->nprobe, ix->hmin.as<int32_t>(), ix->hmax.as<int32_t>(),          \
-        ix->shift.as<int32_t>(), ix->tab.as<TabEntry>(), ix->tab_off.as<long long>(),            \
-        ix->tab_mask.as<uint32_t>(), bstart, bsize, feats, bmh, moves, lsum, lmh)
+        ix->shift.as<int32_t>(), ix->tab_ptr.as<const TabEntry *>(),                             \
+        ix->tab_ents.as<uint32_t>(), ix->tab_pb, bstart, bsize, feats, bmh, moves, lsum, lmh)
     switch (ix->k) {
     case 8: QW_PR(8, true); break;
     case 10: QW_PR(10, true); break;

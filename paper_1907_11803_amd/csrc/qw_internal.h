@@ -97,6 +97,9 @@ struct DevBuf {
     ~DevBuf() { release(); }
     qw_status ensure(size_t want);  // grows (contents discarded); never shrinks
     void release();
+    // release() for memory of device `dev` that no enqueued work uses any
+    // more: the block may stay in the device's pool (see pool_put)
+    void retire(int dev);
     void view(void *mem, size_t n)
     {
         release();
@@ -106,6 +109,9 @@ struct DevBuf {
     }
     template <class T> T *as() const { return static_cast<T *>(p); }
 };
+
+// Returns the device's pooled blocks to the driver; true when it held any.
+bool pool_give_back(int dev);
 
 // ---------------------------------------------------------------- index
 // Probe-table entry: a bucket of one layer, keyed by its packed k-tuple.
@@ -247,9 +253,10 @@ struct qw_index {
     std::vector<int32_t> key_bits;  // per layer
     // CSR ids [L][n] and probe tables
     qw::DevBuf ids;
-    qw::DevBuf tab;        // TabEntry, all layers concatenated
-    qw::DevBuf tab_off;    // int64 [L] first entry of each layer
-    qw::DevBuf tab_mask;   // uint32 [L]
+    std::vector<qw::DevBuf> tabs;  // TabEntry: the layers' tables (one block; more when it ran out)
+    qw::DevBuf tab_ptr;    // const TabEntry * [L]: each layer's table
+    qw::DevBuf tab_ents;   // uint32 [L]: entries of each of its regions
+    int32_t tab_pb = 0;    // 2^tab_pb regions per layer
     int64_t buckets = 0, max_bucket = 0;
     // mean over layers of sum_b s_b^2 / n: the expected size of the bucket a
     // point of the data falls in (queries near the data see about this much)

@@ -31,6 +31,20 @@ __host__ __device__ inline uint64_t key_mix(uint64_t lo, uint64_t hi)
     return h;
 }
 
+// Partition (of 2^pb) of a layer's points and probe-table region of a key: the
+// top bits of its mix.
+__host__ __device__ inline uint32_t key_part(uint64_t mix, int32_t pb)
+{
+    return (uint32_t)((mix >> 1) >> (63 - pb));
+}
+
+// First slot of a key in its region of `ents` entries: the mix's low word
+// scaled to the region (any size, no power of two).
+__host__ __device__ inline uint32_t key_slot(uint64_t mix, uint32_t ents)
+{
+    return (uint32_t)(((mix & 0xFFFFFFFFull) * ents) >> 32);
+}
+
 // floor(y) as int32, saturating outside the int32 range (such values never
 // match a bucket: the index range check rejects them).
 __host__ __device__ inline int32_t floor_to_i32(double y)

@@ -140,6 +140,40 @@ def test_candidate_sets_cfg1(cfg1, w):
     assert np.all(sizes.sum(axis=1) >= cnt)
 
 
+@pytest.mark.parametrize("n,L,k,w,dup", [
+    (1, 2, 3, 300.0, 0), (63, 1, 1, 50.0, 0), (1024, 3, 4, 300.0, 0), (1025, 3, 4, 300.0, 0),  # one, two partitions
+    (8191, 2, 5, 300.0, 0), (8193, 64, 1, 200.0, 0), (16385, 5, 7, 400.0, 0),                  # tiles of the scatter
+    (40000, 2, 8, 20.0, 0),        # a bucket per point
+    (20000, 2, 6, 1e6, 0),         # one bucket
+    (30000, 3, 24, 90.0, 0),       # keys beyond 128 bits: refused
+    (30000, 3, 24, 300.0, 0),      # keys beyond 64 bits
+    (12000, 2, 6, 300.0, 9000),    # one point 9000 times: a partition far beyond its table
+])
+def test_index_grouping(n, L, k, w, dup):
+    rng = np.random.default_rng(n + k)
+    data = rng.integers(0, 256, (n, 24), dtype=np.uint8)
+    if dup:
+        data[rng.permutation(n)[:dup]] = data[0]
+    p = synth.hash_params(7, L, k, 24, w)
+    h = oracle.hash_points(data, p.a, p.b(), w).reshape(n, L, k)
+    if np.ceil(np.log2(np.ptp(h, axis=0) + 1.0)).sum(axis=1).max() > 128:
+        with pytest.raises(lib.QwError) as e:
+            build(data, p.a, p.b(), w)
+        assert e.value.status == lib.QW_EUNSUPPORTED
+        return
+    ix = build(data, p.a, p.b(), w)
+    q = np.concatenate([data[:40], rng.integers(0, 256, (20, 24), dtype=np.uint8)])
+    want = oracle.lsh_candidates(data, q, p.a, p.b(), w)
+    for g, o in zip(ix.candidate_lists(dev(q)), want):
+        assert np.array_equal(g, o)
+    sizes = [np.unique(h[:, l], axis=0, return_counts=True)[1] for l in range(L)]
+    info = ix.info()
+    assert info["buckets"] == sum(len(s) for s in sizes)
+    assert info["max_bucket"] == max(s.max() for s in sizes)
+    mean = np.mean([(s.astype(np.float64) ** 2).sum() / n for s in sizes])
+    assert info["mean_hit_bucket"] == pytest.approx(mean, rel=1e-12)  # sums of whole numbers
+
+
 # ---------------------------------------------------------------- neighbour probing
 
 @pytest.mark.parametrize("w", [400.0, 900.0])
