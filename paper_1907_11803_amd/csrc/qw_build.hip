@@ -707,8 +707,7 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
     QW_HIP(hipGetLastError());
 
     // data copy with padded rows
-    const size_t elem = dtype == QW_U8 ? 1 : 4;
-    QW_TRY(ix->data.ensure(elem * (size_t)n * dp));
+    QW_TRY(ix->data.ensure(row_data_bytes(ix.get())));
     QW_TRY(launch_pad_rows(data, n, d, dp, dtype, ix->data.p, s));
     QW_TRY(launch_fill_u32(dmax, 0u, 1, s));
     if (dtype == QW_F32) {
@@ -759,7 +758,7 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
     // partitions per layer: about 512 to 1024 points each, up to 2048 before
     // their number outgrows the LDS counters (10M points: scattering point by
     // point to 2^14 partitions took 2.4 ms for 2 layers, reordered tiles to
-    // 2^13 take 0.43 counted in)
+    // 2^13 take 0.43 ms)
     int pb = 0;
     while ((n >> pb) > (pb < kLdsPart ? 1024 : 2048)) ++pb;
     const size_t cn = (size_t)(n * chunk_layers);

@@ -29,14 +29,17 @@ constexpr int kMaxClasses = 16;
 enum {
     C_UNUSED = 0, C_UNIQUE, C_PROBEHIT, C_CANDTOT, C_CLASS /* .. C_CLASS+15 */,
     C_ALLOC = 20 /* .. +kXcd-1 */, C_FAIL = 28 /* .. +kXcd-1 */, C_SPARE = 36,
-    C_RECOMP = 40 /* .. +kRecompSlots-1 */, kC64 = C_RECOMP + kRecompSlots
+    C_GALLOC = 72 /* .. +kXcd-1 */, C_RECOMP = 40 /* .. +kRecompSlots-1 */, kC64 = C_GALLOC + kXcd
 };
 // u32: overflow-queue lengths per class (queue i holds queries that overflowed
 // class i-1), fallback queue, misc, then kXcd work counters per class
-enum { W_CLSDONE = 0, W_TOPK2 = 1, W_WORK = 2 /* .. 5: counting split counts; .. 15 unused */, W_QCNT = 16 /* .. 32 */, W_SIMPLE = 33, W_MAX = 34,
+enum { W_CLSDONE = 0, W_TOPK2 = 1, W_WORK = 2 /* .. 5: counting split counts */, W_GEXTRA = 8 /* .. 15 unused */, W_QCNT = 16 /* .. 32 */, W_SIMPLE = 33, W_MAX = 34,
        W_DUMMY = 35, W_QMERGED = 36, W_FB = 44, W_FBWORK = 45, W_STAGE = 46, W_XWORK = 48,
        kC32 = W_XWORK + kXcd * (kMaxClasses + 1) };
 constexpr int kQueueMerged = kMaxClasses + 1;  // overflow queue of the merged launch
+// Classes the several-queries kernel serves: sets of up to 2^14 slots by their
+// bound, about half of it distinct (its own set takes 6,144 ids).
+constexpr int kGroupedSetLog2 = 14;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
 constexpr int64_t kCandPerQuery = 4096;  // pair space reserved per query (beyond: fallback)
@@ -118,9 +121,12 @@ Plan make_plan(qw_index *ix, int K)
     return p;
 }
 
+// Records of the groups, then the label tables.
+size_t group_state_bytes(int64_t Q) { return group_rec_bytes(Q) + 2 * sizeof(uint32_t) * kLabelSlots; }
+
 // Grow the query workspace for Q queries (keys: the key list of the select
 // kernel); drops captured graphs when any buffer moves.
-qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false)
+qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false, int64_t group_q = 0)
 {
     Workspace &w = ix->ws;
     auto ptrs = [&w]() {
@@ -130,7 +136,7 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
                                    w.binoff.p, w.counters.p, w.ovf.p, w.gscratch.p, w.mlpout.p,
                                    w.order.p,
                                    w.hist.p, w.scan.p, w.ucount.p, w.coff.p, w.flag.p,
-                                   w.pkeys.p, w.fb.p};
+                                   w.pkeys.p, w.fb.p, w.glist.p, w.grecs.p};
     };
     const std::vector<void *> before = ptrs();
     // two passes: the first adds up what the buffers must grow by and refuses
@@ -190,10 +196,22 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
             const int64_t slack = (int64_t)kXcd * kXcdChunk * (plan->ncls + 1);
             const int64_t cand_cap = std::max<int64_t>((q + slack) * kCandPerQuery, 1 << 20);
             QW_TRY(grow(w.coff, sizeof(unsigned long long) * q));
-            QW_TRY(grow(w.flag, sizeof(uint32_t) * q));
+            QW_TRY(grow(w.flag, 3 * sizeof(uint32_t) * q));
             if (keys) QW_TRY(grow(w.pkeys, sizeof(unsigned long long) * cand_cap));
             QW_TRY(grow(w.fb, sizeof(int32_t) * q));
         }
+    }
+    // groups of queries: where the memory is there (they are answered one by
+    // one otherwise)
+    if (plan && group_q > 0) {
+        size_t free_b = 0, total_b = 0;
+        const size_t want = group_list_bytes(group_q) + group_state_bytes(group_q);
+        const bool held = w.glist.bytes >= group_list_bytes(group_q) && w.grecs.bytes >= group_state_bytes(group_q);
+        if (!held && hipMemGetInfo(&free_b, &total_b) == hipSuccess && want < free_b / 4) {
+            (void)w.glist.ensure(group_list_bytes(group_q));
+            (void)w.grecs.ensure(group_state_bytes(group_q));
+        }
+        (void)hipGetLastError();
     }
     if (before != ptrs()) drop_graphs(ix);
     return QW_OK;
@@ -546,6 +564,13 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     const bool stage = o.stage_split > 0;
     const int topk = !stage && o.topk_keep >= 0 ? plan.topk : 0;  // in-kernel top K
     const bool learned = o.sched == QW_SCHED_LEARNED && !ix->mlp.empty();
+    // float rows in the grouped order: neighbours of one region share a
+    // workgroup, over every class whose bound a group's set may hold half of
+    // (the listed ids repeat across layers); a group beyond its set goes query
+    // by query to the largest such class's LDS sets
+    const int gmax = std::min(kGroupedSetLog2 - kCmin, plan.ncls - 2);
+    const bool use_grouped = o.group && !stage && gmax >= 2 && group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max) &&
+                             w.glist.bytes >= group_list_bytes(Q) && w.grecs.bytes >= group_state_bytes(Q);
     // the binning kernel runs the count model itself; the grouped schedule
     // takes the predictions from the inference kernel
     QW_TRY(front(ix, queries, Q, QW_FORM_FAST, s, ev,
@@ -567,16 +592,31 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             *order = w.order.as<int32_t>();
             return QW_OK;
         }
-        QW_TRY(launch_classify(Q, ix->L, ix->n, layer_mh(ix),
-                               layer_sizes(ix), ex, pl, ix->mlp_margin, force_max, kCmin,
-                               plan.cfloor, plan.cmax, plan.ncls, o.group, w.keys.as<unsigned long long>(),
-                               w.vals.as<int32_t>(), ccount, s));
+        auto *keys = w.keys.as<unsigned long long>();
+        if (use_grouped)
+            QW_TRY(launch_classify_groups(
+                Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin, force_max, kCmin,
+                plan.cfloor, plan.cmax, plan.ncls,
+                reinterpret_cast<uint32_t *>(w.grecs.as<char>() + group_rec_bytes(Q)), keys,
+                w.vals.as<int32_t>(), ccount, s));
+        else
+            QW_TRY(launch_classify(Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin,
+                                   force_max, kCmin, plan.cfloor, plan.cmax, plan.ncls, o.group, keys,
+                                   w.vals.as<int32_t>(), ccount, s));
+        if (Q <= kSmallOrder) {
+            QW_TRY(launch_small_order(keys, w.vals.as<int32_t>(), Q, ccount, plan.ncls, seg, gmax,
+                                      use_grouped ? w.order.as<uint32_t>() : nullptr, s));
+            *order = w.vals.as<int32_t>();
+            return QW_OK;
+        }
         bool alt = false;
-        QW_TRY(radix_sort_pairs(w.keys.as<unsigned long long>(), w.vals.as<int32_t>(), Q,
-                                o.group ? 0 : 16, 24, w.keys2.as<unsigned long long>(),
-                                w.vals2.as<int32_t>(), w.hist, s, &alt));
+        QW_TRY(radix_sort_pairs(keys, w.vals.as<int32_t>(), Q, 0, use_grouped ? 40 : 24,
+                                w.keys2.as<unsigned long long>(), w.vals2.as<int32_t>(), w.hist, s, &alt));
         *order = alt ? w.vals2.as<int32_t>() : w.vals.as<int32_t>();
         QW_TRY(launch_segments(ccount, plan.ncls, seg, s));
+        if (use_grouped)
+            QW_TRY(launch_group_runs(alt ? w.keys2.as<unsigned long long>() : keys, seg, gmax,
+                                     w.order.as<uint32_t>(), s));
         return QW_OK;
     };
     // Classes run from the smallest hash set to the global one.  Each launch
@@ -714,7 +754,8 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.ucount = w.ucount.as<uint32_t>();
             return launch_dedup_wave(a, plan.wgrid, s);
         }
-        const int merged = std::max(0, std::min(plan.cfloor - kCmin, plan.ncls - 2));
+        const bool grouped = use_grouped && !count_only;
+        const int merged = grouped ? gmax : std::max(0, std::min(plan.cfloor - kCmin, plan.ncls - 2));
         const int glob = plan.ncls - 1;
         // with two or more global-class workgroups, the side stream's global
         // class and the merged launch's overflow each take half of them (and
@@ -730,12 +771,50 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
                                 queues + (int64_t)(i + 1) * Q, c32(ix) + W_QCNT + i + 1, i, 0,
                                 ix->side, i == glob ? gsplit : 0));
         }
-        QW_TRY(launch_range(0, merged, nullptr, nullptr, queues + (int64_t)kQueueMerged * Q,
-                            c32(ix) + W_QMERGED, merged, 0, s));
+        if (grouped) {
+            GroupedArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.order = order;
+            a.groups = w.order.as<uint32_t>();  // free with grouping: [kMaxClasses * Q] words
+            a.xwork = c32(ix) + W_XWORK + kXcd * merged;
+            a.xwork2 = c32(ix) + W_XWORK;  // class 0's, served here
+            a.xchunk = o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk;
+            a.bstart = w.bstart.as<uint32_t>();
+            a.bsize = w.bsize.as<uint32_t>();
+            a.ids = ix->ids.as<int32_t>();
+            a.n = ix->n;
+            a.nl = ix->nl;
+            a.pmagic = ix->pmagic;
+            a.dp = ix->dp;
+            a.data = ix->data.as<float>();
+            a.queries = static_cast<const float *>(w.qrows);
+            a.keys = w.pkeys.as<unsigned long long>();
+            a.alloc = c64(ix) + C_ALLOC;
+            a.fail = c64(ix) + C_FAIL;
+            a.region = (unsigned long long)(cand_cap / kXcd);
+            a.ucount = w.ucount.as<uint32_t>();
+            a.coff = w.coff.as<unsigned long long>();
+            a.flag = w.flag.as<uint32_t>();
+            a.abs_err = w.flag.as<float>() + Q;
+            a.ovf_count = c32(ix) + W_QMERGED;
+            a.ovf_list = queues + (int64_t)kQueueMerged * Q;
+            a.kpos = w.flag.as<uint32_t>() + 2 * Q;
+            a.recs = w.grecs.p;
+            a.extra = c32(ix) + W_GEXTRA;
+            a.glist = w.glist.as<uint2>();
+            a.galloc = c64(ix) + C_GALLOC;
+            a.gregion = (unsigned long long)(w.glist.bytes / sizeof(uint2) / kXcd);
+            QW_TRY(launch_grouped(a, ix->cus, ix->lds_max, s));
+            QW_TRY(launch_range(merged, merged, a.ovf_list, a.ovf_count, queues, c32(ix) + W_QCNT, 1, 1, s));
+        } else {
+            QW_TRY(launch_range(0, merged, nullptr, nullptr, queues + (int64_t)kQueueMerged * Q,
+                                c32(ix) + W_QMERGED, merged, 0, s));
+        }
         QW_HIP(hipEventRecord(ix->fork[1], ix->side));
         if (!gsplit) QW_HIP(hipStreamWaitEvent(s, ix->fork[1], 0));
         // overflow of the merged launch (usually none): the global class, queue only
-        QW_TRY(launch_range(glob, glob, queues + (int64_t)kQueueMerged * Q, c32(ix) + W_QMERGED,
+        QW_TRY(launch_range(glob, glob, grouped ? queues : queues + (int64_t)kQueueMerged * Q,
+                            c32(ix) + (grouped ? W_QCNT : W_QMERGED),
                             queues + (int64_t)(glob + 1) * Q, c32(ix) + W_DUMMY, kMaxClasses, 1, s,
                             gsplit ? 2 : 0));
         if (gsplit) QW_HIP(hipStreamWaitEvent(s, ix->fork[1], 0));
@@ -758,7 +837,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         pred_log = w.mlpout.as<float>();
     }
     QW_TRY(schedule(exact, pred_log, o.sched == QW_SCHED_NONE, &order));
-    if (!topk) QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, Q, s));  // read by the select kernel
+    if (!topk) QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, 3 * Q, s));  // read by the select kernel
     if (ev) QW_HIP(hipEventRecord(ev[3], s));
     QW_TRY(dedup_classes(order, 0));
     if (ev) QW_HIP(hipEventRecord(ev[6], s));
@@ -768,12 +847,13 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     m.coff = w.coff.as<unsigned long long>();
     m.ucount = w.ucount.as<uint32_t>();
     m.flag = w.flag.as<uint32_t>();
+    m.abs_err = use_grouped ? w.flag.as<float>() + Q : nullptr;
     m.K = K;
     m.LC = plan.LC;
     m.dtype = ix->dtype;
     m.dp = ix->dp;
     m.d = ix->d;
-    m.eps = plan.eps;
+    m.eps = use_grouped ? std::max(plan.eps, group_eps(ix->dp)) : plan.eps;
     m.fb_count = c32(ix) + W_FB;
     m.fb_list = w.fb.as<int32_t>();
     m.out_ids = out_ids;
@@ -1008,7 +1088,7 @@ void qw_free_index(qw_index *ix)
     if (hipGetDevice(&dev) == hipSuccess && dev == ix->device) {
         Workspace &w = ix->ws;
         for (DevBuf *b : {&ix->data, &ix->ids, &w.qpad, &w.h, &w.bstart, &w.bsize, &w.ovf, &w.gscratch,
-                          &w.order, &w.pkeys, &w.bf_min, &w.bf_keys})
+                          &w.order, &w.pkeys, &w.glist, &w.grecs, &w.bf_min, &w.bf_keys})
             b->retire(dev);
         for (DevBuf &t : ix->tabs) t.retire(dev);
     }
@@ -1157,7 +1237,10 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             if (ix->nl > 64 || rb > kStageMaxRow || stage_lds_bytes(rb, eff.stage_split, &icn, &dcn) > ix->lds_max)
                 eff.stage_split = -1;
         }
-        QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0));
+        QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,
+                         eff.group && eff.stage_split <= 0 &&
+                                 group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max)
+                             ? Q : 0));
         if (opt.timing || !opt.graph) {
             QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, s, out_ids, out_dist,
                                 opt.timing ? ix->ev : nullptr));

@@ -139,7 +139,8 @@ struct Workspace {
     DevBuf qpad, h, bstart, bsize, bmh, lsum, lmh, moves, pred, feats, keys, keys2, vals,
         vals2, hist, order, binoff, counters, ovf, gscratch, mlpout, scan;
     // flat pipeline
-    DevBuf ucount, coff, flag, pkeys, fb;
+    DevBuf ucount, coff, flag, pkeys, fb;  // flag: [3 Q], then the keys' absolute errors, then key counts
+    DevBuf glist, grecs;  // groups of queries: their candidate rows, their records
     // brute force: stream minima, per-query state, key lists
     DevBuf bf_min, bf_state, bf_keys;
     // the query rows the kernels of the current call read: the caller's own
@@ -296,6 +297,13 @@ struct qw_index {
 
 namespace qw {
 
+// Device bytes of the point rows: a wave may load up to 256 bytes past the
+// last row (columns it does not use).
+inline size_t row_data_bytes(const qw_index *ix)
+{
+    return (size_t)(ix->dtype == QW_U8 ? 1 : 4) * (size_t)ix->n * (size_t)ix->dp + 256;
+}
+
 // ---------------------------------------------------------------- tuning
 // Key of a workload in the tuning cache (a hash of the index's shape and
 // settings, Q, K and the schedule); desc (nullable) receives a readable form.
@@ -448,6 +456,15 @@ int verify_per_iter(int dp, int dtype);
 int verify_blocks_per_cu(int dp, int dtype, size_t lds);
 
 // ---------------------------------------------------------------- scheduling
+// Keys of queries that share workgroups (tag: 2 * kLabelSlots words): class << 32 |
+// group key, whose low kGroupOrderBits bits only order its run.
+constexpr uint32_t kLabelSlots = 1u << 18;
+constexpr int kGroupOrderBits = 12;
+qw_status launch_classify_groups(int64_t Q, int32_t L, int64_t n, const uint32_t *bmh, const uint32_t *bsize,
+                                 const int32_t *exact, const float *pred_log, float margin, int32_t force_max,
+                                 int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t *tag,
+                                 unsigned long long *keys, int32_t *vals, unsigned long long *class_count,
+                                 hipStream_t s);
 qw_status launch_classify(int64_t Q, int32_t L, int64_t n,
                           const uint32_t *bmh, const uint32_t *bsize, const int32_t *exact,
                           const float *pred_log, float margin, int32_t force_max, int32_t cmin,
@@ -532,7 +549,50 @@ struct DedupArgs {
 };
 
 
+// Several queries per workgroup over float rows (qw_group.hip).
+struct GroupedArgs {
+    const int32_t *order;
+    const uint32_t *groups;      // [0]: groups; then each group's first item; then the items
+    uint32_t *xwork, *xwork2;    // per-XCD counters of the two kernels (zeroed)
+    uint32_t xchunk;             // consecutive items dealt to one XCD
+    const uint32_t *bstart, *bsize;
+    const int32_t *ids;
+    int64_t n;
+    int32_t nl;
+    uint32_t pmagic;
+    int32_t dp;
+    const float *data, *queries;
+    unsigned long long *keys, *alloc, *fail, region;  // as the dedup kernel's
+    uint32_t *ucount;
+    unsigned long long *coff;
+    uint32_t *flag;
+    float *abs_err;              // [Q]: absolute part of the keys' error
+    uint32_t *kpos;              // [Q], zeroed: keys written (groups in pieces)
+    uint32_t *ovf_count;
+    int32_t *ovf_list;
+    void *recs;                  // group_rec_bytes
+    uint32_t *extra;             // records beyond the groups' first (zeroed)
+    uint2 *glist;                // candidate rows in kXcd equal regions
+    unsigned long long *galloc, gregion;  // their allocators (zeroed) and size
+};
+bool group_applies(int dtype, int dp, int nl, size_t lds_max);
+float group_eps(int dp);         // relative part of the keys' error
+size_t group_rec_bytes(int64_t Q);
+size_t group_list_bytes(int64_t Q);
+// A workload of at most kSmallOrder queries: keys (below 2^52) and vals sorted in
+// place, the class segments, and (groups non-null) the groups as below, in one
+// launch.
+constexpr int64_t kSmallOrder = 4096;
+qw_status launch_small_order(unsigned long long *keys, int32_t *vals, int64_t Q,
+                             const unsigned long long *class_count, int32_t ncls, unsigned long long *seg,
+                             int cls, uint32_t *groups, hipStream_t s);
+// Groups of equal classes and labels over the order's classes 0 .. cls.
+qw_status launch_group_runs(const unsigned long long *keys, const unsigned long long *seg, int cls,
+                            uint32_t *groups, hipStream_t s);
+qw_status launch_grouped(GroupedArgs a, int cus, size_t lds_max, hipStream_t s);
+
 struct SelectArgs {
+    const float *abs_err;        // nullable: absolute part of each query's key error (float data)
     const unsigned long long *keys;
     const unsigned long long *coff;
     const uint32_t *ucount;

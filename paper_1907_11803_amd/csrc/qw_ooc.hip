@@ -777,7 +777,9 @@ qw_status ooc_enable(qw_index *ix, const qw_ooc_opts &o, hipStream_t s)
             st->dev_rows = ix->ooc->dev_rows;
             st->host_bytes = ix->ooc->host_bytes;
         } else {
-            const size_t ib = ix->ids.bytes, db = ix->data.bytes;
+            auto rounded = [](size_t v) { return (v + 255) & ~size_t(255); };
+            const size_t ib = rounded(sizeof(int32_t) * (size_t)ix->L * (size_t)ix->n);
+            const size_t db = rounded(row_data_bytes(ix) - 256);
             if (hipHostMalloc(&st->host_ids, ib, hipHostMallocMapped) != hipSuccess) {
                 (void)hipGetLastError();
                 st->host_ids = nullptr;
@@ -827,7 +829,7 @@ qw_status ooc_disable(qw_index *ix, hipStream_t s)
                       &st.bstart2})
         b->release();
     QW_TRY(ix->ids.ensure(ib));
-    QW_TRY(ix->data.ensure(db));
+    QW_TRY(ix->data.ensure(row_data_bytes(ix)));
     QW_HIP(hipMemcpyAsync(ix->ids.p, st.host_ids, ib, hipMemcpyHostToDevice, s));
     QW_HIP(hipMemcpyAsync(ix->data.p, st.host_rows, db, hipMemcpyHostToDevice, s));
     QW_HIP(hipStreamSynchronize(s));

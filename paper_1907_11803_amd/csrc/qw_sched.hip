@@ -53,6 +53,122 @@ __device__ inline int class_of(uint64_t tsum, int64_t n, const int32_t *__restri
     return c <= cmax ? c - cmin : ncls - 1;
 }
 
+// Groups of queries that share a workgroup need a key that all the queries of a
+// region have in common.  The min-hash of C(q) alone is not: for about one
+// query in forty (1M x 960, w = 12) it is a point from elsewhere that collided
+// by chance in one layer.  The smallest minimum of at least two layers, t(q),
+// is a point near the query, but misses the region's smallest where that one
+// collided once.  So the queries vote: for each recurring minimum v of a query,
+// label[v] = the smallest t over the queries that have v; a query's key is the
+// label of t(q), followed twice.  A workload beyond kLabelSample queries is
+// sampled evenly.  (Simulated on clusters of 2,000 points: keyed by the
+// min-hash, 95 % of a cluster's queries agree, by t 77 to 84 %, by the label all.)
+// tag[slot] holds the v that owns the slot; a v whose slot is another's keeps
+// its own value.
+constexpr int64_t kLabelSample = 8192;
+__device__ inline uint32_t label_slot(uint32_t v, uint32_t slots) { return mix32(v) & (slots - 1u); }
+
+// One wave per query, lane l holding layer l's minimum v (0xFFFFFFFF: a miss, or
+// no layer): whether two layers at least hold it, and the smallest such value
+// in *t (0xFFFFFFFF: none).
+__device__ inline bool recurs(uint32_t v, int32_t L, uint32_t *t)
+{
+    int same = 0;
+    for (int32_t i = 0; i < L; ++i) same += (uint32_t)__builtin_amdgcn_readlane((int)v, i) == v ? 1 : 0;
+    const bool r = same >= 2 && v != 0xFFFFFFFFu;
+    uint32_t m = r ? v : 0xFFFFFFFFu;
+    for (int o = 32; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o));
+    *t = m;
+    return r;
+}
+
+__global__ __launch_bounds__(kBlock) void label_kernel(int64_t Q, int32_t L, int32_t step,
+                                                       const uint32_t *__restrict__ bmh, uint32_t slots,
+                                                       uint32_t *__restrict__ tag, uint32_t *__restrict__ label)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t q = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * step;
+    if (q >= Q) return;
+    const uint32_t v = lane < L ? bmh[q * L + lane] : 0xFFFFFFFFu;
+    uint32_t t;
+    if (!recurs(v, L, &t)) return;
+    const uint32_t s = label_slot(v, slots);
+    uint32_t o = tag[s];
+    if (o == 0xFFFFFFFFu) {
+        o = atomicCAS(&tag[s], 0xFFFFFFFFu, v);
+        if (o == 0xFFFFFFFFu) o = v;
+    }
+    if (o == v && label[s] > t) atomicMin(&label[s], t);
+}
+
+// Key = class << 32 | group key (see label_kernel) of every query, one wave per
+// query: the label's bits decide the run, t's the order within it.
+__global__ __launch_bounds__(kBlock) void classify_group_kernel(
+    int64_t Q, int32_t L, int64_t n, const uint32_t *__restrict__ bmh, const uint32_t *__restrict__ bsize,
+    const int32_t *__restrict__ exact, const float *__restrict__ pred_log, float margin, int32_t force_max,
+    int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t slots,
+    const uint32_t *__restrict__ tag, unsigned long long *__restrict__ keys, int32_t *__restrict__ vals,
+    unsigned long long *class_count)
+{
+    __shared__ uint32_t hist[32];
+    if (threadIdx.x < 32) hist[threadIdx.x] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int64_t q = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); q < Q;
+         q += (int64_t)gridDim.x * (kBlock / 64)) {
+        const uint32_t v = lane < L ? bmh[q * L + lane] : 0xFFFFFFFFu;
+        uint64_t tsum = lane < L ? bsize[q * L + lane] : 0u;
+        uint32_t m = v, t;
+        for (int o = 32; o > 0; o >>= 1) {
+            tsum += __shfl_xor(tsum, o);
+            m = min(m, (uint32_t)__shfl_xor((int)m, o));
+        }
+        (void)recurs(v, L, &t);
+        uint32_t lb = t;
+        for (int i = 0; i < 2 && lb != 0xFFFFFFFFu; ++i) {
+            const uint32_t s = label_slot(lb, slots);
+            if (tag[s] == lb) lb = min(lb, tag[slots + s]);
+        }
+        if (t == 0xFFFFFFFFu) t = lb = m;
+        constexpr uint32_t low = (1u << kGroupOrderBits) - 1u;
+        const uint32_t g = (mix32(lb) & ~low) | (mix32(t) & low);
+        if (lane == 0) {
+            const int cls = class_of(tsum, n, exact, q, pred_log != nullptr, pred_log ? pred_log[q] : 0.f,
+                                     margin, force_max, cmin, cfloor, cmax, ncls);
+            keys[q] = ((unsigned long long)cls << 32) | g;
+            vals[q] = (int32_t)q;
+            atomicAdd(&hist[cls], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < ncls && hist[threadIdx.x])
+        atomicAdd(&class_count[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
+}
+
+// Label tables and keys of a workload whose queries share workgroups.  tag: the
+// slots' owners, then their labels (64 slots a query, kLabelSlots at most).
+qw_status launch_classify_groups(int64_t Q, int32_t L, int64_t n, const uint32_t *bmh, const uint32_t *bsize,
+                                 const int32_t *exact, const float *pred_log, float margin, int32_t force_max,
+                                 int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t *tag,
+                                 unsigned long long *keys, int32_t *vals, unsigned long long *class_count,
+                                 hipStream_t s)
+{
+    if (Q <= 0) return QW_OK;
+    if (L > 64) return QW_EINTERNAL;
+    uint32_t slots = 1024;
+    while (slots < kLabelSlots && (int64_t)slots < 64 * Q) slots <<= 1;
+    QW_TRY(launch_fill_u32(tag, 0xFFFFFFFFu, 2 * (int64_t)slots, s));
+    constexpr int wpb = kBlock / 64;
+    const int32_t step = (int32_t)std::max<int64_t>(1, Q / kLabelSample);
+    label_kernel<<<(unsigned)ceil_div(ceil_div(Q, step), wpb), kBlock, 0, s>>>(Q, L, step, bmh, slots, tag, tag + slots);
+    QW_HIP(hipGetLastError());
+    classify_group_kernel<<<(unsigned)std::min<int64_t>(2048, ceil_div(Q, wpb)), kBlock, 0, s>>>(
+        Q, L, n, bmh, bsize, exact, pred_log, margin, force_max, cmin, cfloor, cmax, ncls, slots, tag, keys,
+        vals, class_count);
+    QW_HIP(hipGetLastError());
+    return QW_OK;
+}
+
 // Key = class << 16 | 16-bit group of every query, for the radix sort.
 __global__ __launch_bounds__(kBlock) void classify_kernel(
     int64_t Q, int32_t L, int64_t n,

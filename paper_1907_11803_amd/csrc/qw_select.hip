@@ -9,11 +9,14 @@
 
 namespace qw {
 
-// Band threshold F_K * (1 + eps) / (1 - eps), rounded up to float: every key
-// of the exact top-K has an FP32 distance at most this (see the verify kernel).
-__device__ inline float band_threshold(float FK, float eps)
+// Band threshold, rounded up to float: with keys F of |F - D| <= eps D + err,
+// the K-th distance is at most (F_K + err) / (1 - eps), so every key of the
+// exact top-K is at most (F_K + err) (1 + eps) / (1 - eps) + err.  Keys near
+// FP32's end may stand for larger distances: no bound.
+__device__ inline float band_threshold(float FK, float eps, float err)
 {
-    const double t = (double)FK * (1.0 + (double)eps) / (1.0 - (double)eps) + 0x1p-100;
+    if (!(FK < 1e37f)) return INFINITY;
+    const double t = ((double)FK + (double)err) * (1.0 + (double)eps) / (1.0 - (double)eps) + (double)err + 0x1p-100;
     float f = (float)t;
     if ((double)f < t) f = nextafterf(f, INFINITY);
     return f;
@@ -56,6 +59,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
     const uint32_t bad = A.flag[q];
     const uint32_t U = A.ucount[q];
     const unsigned long long coff = A.coff[q];
+    const float err = DT == QW_F32 && A.abs_err ? A.abs_err[q] : 0.f;
     if (bad) {  // uniform
         if (tid == 0) A.fb_list[atomicAdd(A.fb_count, 1u)] = (int32_t)q;
         return;
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
         __syncthreads();
         thr = s_thr;
         if (DT != QW_U8 && thr != ~0ull) {
-            const float bt = band_threshold(__uint_as_float((uint32_t)(thr >> 32)), A.eps);
+            const float bt = band_threshold(__uint_as_float((uint32_t)(thr >> 32)), A.eps, err);
             thr = ((unsigned long long)__float_as_uint(bt) << 32) | 0xFFFFFFFFull;
         }
         __syncthreads();  // every thread has read s_thr
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
     __syncthreads();
     unsigned long long bthr = ~0ull;
     if (c >= K) {
-        const float bt = band_threshold(__uint_as_float((uint32_t)(s_kth >> 32)), A.eps);
+        const float bt = band_threshold(__uint_as_float((uint32_t)(s_kth >> 32)), A.eps, err);
         bthr = ((unsigned long long)__float_as_uint(bt) << 32) | 0xFFFFFFFFull;
     }
     const int cap_b = A.LC / 2;

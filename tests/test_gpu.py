@@ -559,6 +559,54 @@ def test_bruteforce_matrix_cores_key_lists(kind):
     check_topk(ids, dist, ids_o, dist_o, True)
 
 
+def grouped_workload(seed, n, d, Q, ncl, spread, far=0):
+    """Float clusters and queries near few of them, so that candidate sets overlap."""
+    rng = np.random.default_rng(seed)
+    c = rng.random((ncl, d), dtype=np.float32)
+    data = c[rng.integers(0, ncl, n)] + rng.normal(0, spread, (n, d)).astype(np.float32)
+    q = c[rng.integers(0, max(1, ncl // 2), Q)] + rng.normal(0, spread, (Q, d)).astype(np.float32)
+    q[:far] = rng.random((far, d), dtype=np.float32) * 3
+    return np.clip(data, 0, 1).astype(np.float32), q.astype(np.float32)
+
+
+@pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K", [
+    (3000, 16, 1, 4, 6, 4, 1.0, 10), (3000, 17, 33, 3, 6, 4, 1.0, 1),       # one query; one past a group
+    (4000, 64, 200, 6, 8, 6, 2.0, 10), (4000, 100, 130, 5, 8, 6, 2.5, 100),  # whole chunk; ragged row, long list
+    (2500, 960, 100, 4, 6, 5, 9.0, 10), (1500, 1152, 70, 3, 5, 5, 10.0, 10),  # longest rows of a group
+    (1500, 1300, 70, 3, 5, 5, 10.0, 10),                                     # beyond it
+    (5000, 48, 90, 1, 3, 2, 50.0, 10),       # every point a candidate of every query
+    (9000, 32, 50, 1, 3, 2, 50.0, 10),       # more candidates than a group's set
+    (6000, 24, 600, 300, 4, 3, 0.8, 5),      # small sets, many groups
+    (2000, 40, 40, 2, 64, 2, 1.5, 10),       # 64 lists per query
+])
+def test_grouped_float_queries(n, d, Q, ncl, L, k, w, K):
+    data, q = grouped_workload(n + d, n, d, Q, ncl, 0.05, far=min(3, Q - 1))
+    p = synth.hash_params(5, L, k, d, w)
+    ix = build(data, p.a, p.b(), w)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    for sched in (lib.QW_SCHED_SUM, lib.QW_SCHED_ACTUAL):
+        for graph in (0, 1):
+            ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1, sched=sched, graph=graph), stats=True)
+            check_topk(ids, dist, ids_o, dist_o, False)
+            assert st["cand_unique"] == int(cnt_o.sum())
+
+
+def test_grouped_float_queries_ties_and_extremes():
+    # repeated rows (ties by id), and queries with an element that no hash
+    # function reads: very large, infinite or not a number
+    data, q = grouped_workload(9, 3000, 64, 120, 2, 0.05)
+    data[1::3] = data[::3]
+    p = synth.hash_params(5, 6, 4, 64, 2.0)
+    p.a[:, :, -1] = 0
+    q[5, -1], q[40, -1], q[77, -1], q[78, -1] = 1e25, np.inf, np.nan, -3e4
+    ix = build(data, p.a, p.b(), 2.0)
+    want = ix.query(dev(q), 10, lib.make_opts(form=lib.QW_FORM_PLAIN_FP32))
+    for _ in range(3):
+        got = ix.query(dev(q), 10, lib.make_opts(group=1))
+        for g, w in zip(got, want):
+            assert np.array_equal(g.cpu().numpy(), w.cpu().numpy(), equal_nan=True)
+
+
 def test_huge_w_equals_bruteforce():
     """Every point in one bucket per layer: LSH top-K equals exact kNN."""
     rng = np.random.default_rng(61)
