@@ -40,6 +40,9 @@ constexpr int kQueueMerged = kMaxClasses + 1;  // overflow queue of the merged l
 // Classes the several-queries kernel serves: sets of up to 2^14 slots by their
 // bound, about half of it distinct (its own set takes 6,144 ids).
 constexpr int kGroupedSetLog2 = 14;
+// Keys held per query of a group: about 16 K pass the bound of a group's first
+// rows; a query with more goes to the fallback.
+constexpr uint32_t kGroupedKeys = 2048;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
 constexpr int64_t kCandPerQuery = 4096;  // pair space reserved per query (beyond: fallback)
@@ -196,7 +199,7 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
             const int64_t slack = (int64_t)kXcd * kXcdChunk * (plan->ncls + 1);
             const int64_t cand_cap = std::max<int64_t>((q + slack) * kCandPerQuery, 1 << 20);
             QW_TRY(grow(w.coff, sizeof(unsigned long long) * q));
-            QW_TRY(grow(w.flag, 3 * sizeof(uint32_t) * q));
+            QW_TRY(grow(w.flag, 4 * sizeof(uint32_t) * q));
             if (keys) QW_TRY(grow(w.pkeys, sizeof(unsigned long long) * cand_cap));
             QW_TRY(grow(w.fb, sizeof(int32_t) * q));
         }
@@ -786,8 +789,11 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.nl = ix->nl;
             a.pmagic = ix->pmagic;
             a.dp = ix->dp;
-            a.data = ix->data.as<float>();
-            a.queries = static_cast<const float *>(w.qrows);
+            a.data = ix->data.p;
+            a.queries = w.qrows;
+            a.K = K;
+            a.eps = std::max(plan.eps, group_eps(ix->dp));
+            a.keep = K <= group_filter_topk() ? kGroupedKeys : 0xFFFFFFFFu;
             a.keys = w.pkeys.as<unsigned long long>();
             a.alloc = c64(ix) + C_ALLOC;
             a.fail = c64(ix) + C_FAIL;
@@ -799,6 +805,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.ovf_count = c32(ix) + W_QMERGED;
             a.ovf_list = queues + (int64_t)kQueueMerged * Q;
             a.kpos = w.flag.as<uint32_t>() + 2 * Q;
+            a.kroom = w.flag.as<uint32_t>() + 3 * Q;
             a.recs = w.grecs.p;
             a.extra = c32(ix) + W_GEXTRA;
             a.glist = w.glist.as<uint2>();
@@ -837,7 +844,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         pred_log = w.mlpout.as<float>();
     }
     QW_TRY(schedule(exact, pred_log, o.sched == QW_SCHED_NONE, &order));
-    if (!topk) QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, 3 * Q, s));  // read by the select kernel
+    if (!topk) QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, (use_grouped ? 4 : 1) * Q, s));  // read by the select kernel
     if (ev) QW_HIP(hipEventRecord(ev[3], s));
     QW_TRY(dedup_classes(order, 0));
     if (ev) QW_HIP(hipEventRecord(ev[6], s));
@@ -848,6 +855,8 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     m.ucount = w.ucount.as<uint32_t>();
     m.flag = w.flag.as<uint32_t>();
     m.abs_err = use_grouped ? w.flag.as<float>() + Q : nullptr;
+    m.kcount = use_grouped ? w.flag.as<uint32_t>() + 2 * Q : nullptr;
+    m.kroom = use_grouped ? w.flag.as<uint32_t>() + 3 * Q : nullptr;
     m.K = K;
     m.LC = plan.LC;
     m.dtype = ix->dtype;

@@ -57,8 +57,10 @@ __device__ inline double exact_dist_row(const float *__restrict__ x, const float
 // rows go through LDS in chunks of kStageCols elements: every thread loads
 // 16-byte pieces of the rows (coalesced; kStageAhead chunks in flight), forms
 // their rounded squares t * t in FP64 and stores them to LDS; the dependent
-// sums then run on lanes 0-3 of the four waves (row r on wave r % 4), one add
-// per element, so four SIMDs share the chains.
+// sums then run on lanes 0-15 of one wave (row r on lane r), one add per
+// element for all rows.  With several workgroups on a CU the adds' issue counts,
+// not one chain's latency: 100,000 queries of 960 columns, K = 10, spend 1.70 ms
+// in the select kernel; spread over lanes 0-3 of all four waves 2.27.
 constexpr int kStageRows = 16;
 constexpr int kStageCols = 64;
 constexpr int kStageAhead = 6;
@@ -72,12 +74,14 @@ __device__ inline void exact_dists_staged(const float *__restrict__ data, int dp
                                           const float *qs, double *stage, IdOf id_of, Put put)
 {
 #pragma clang fp contract(off)
-    static_assert(kStageRows <= 4 * 4 && kStageRows % 4 == 0, "rows on lanes 0-3 of 4 waves");
+    static_assert(kStageRows <= 64 && kBlock == 256, "rows on one of four waves");
     constexpr int kPer = kStageRows * kStageCols / 4 / kBlock;  // pieces per thread per chunk
     static_assert(kPer * kBlock * 4 == kStageRows * kStageCols, "whole chunks per thread");
     constexpr int kC4 = kStageCols / 4;
     const int tid = threadIdx.x;
-    const int my = (tid & 63) * 4 + (tid >> 6);  // chain of row `my` of the batch (lanes 0-3)
+    // chain of row `my` of the batch: lanes 0-15 of one wave, another one in the
+    // next workgroup (neighbours share a CU: its SIMDs share the chains)
+    const int my = (tid >> 6) == (int)(blockIdx.x & 3) ? tid & 63 : kStageRows;
     const int nch = (dp + kStageCols - 1) / kStageCols;
     for (int b0 = 0; b0 < nb; b0 += kStageRows) {
         const int nr = nb - b0 < kStageRows ? nb - b0 : kStageRows;

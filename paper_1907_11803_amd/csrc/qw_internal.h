@@ -561,13 +561,16 @@ struct GroupedArgs {
     int32_t nl;
     uint32_t pmagic;
     int32_t dp;
-    const float *data, *queries;
+    const void *data, *queries;
+    int32_t K;
+    float eps;                   // relative part of the keys' error (float rows)
+    uint32_t keep;               // keys held per query at most
     unsigned long long *keys, *alloc, *fail, region;  // as the dedup kernel's
     uint32_t *ucount;
     unsigned long long *coff;
     uint32_t *flag;
     float *abs_err;              // [Q]: absolute part of the keys' error
-    uint32_t *kpos;              // [Q], zeroed: keys written (groups in pieces)
+    uint32_t *kpos, *kroom;      // [Q], zeroed: keys written, room for them (0: not in a group)
     uint32_t *ovf_count;
     int32_t *ovf_list;
     void *recs;                  // group_rec_bytes
@@ -579,6 +582,7 @@ bool group_applies(int dtype, int dp, int nl, size_t lds_max);
 float group_eps(int dp);         // relative part of the keys' error
 size_t group_rec_bytes(int64_t Q);
 size_t group_list_bytes(int64_t Q);
+int group_filter_topk();         // K up to which few keys are written
 // A workload of at most kSmallOrder queries: keys (below 2^52) and vals sorted in
 // place, the class segments, and (groups non-null) the groups as below, in one
 // launch.
@@ -596,6 +600,7 @@ struct SelectArgs {
     const unsigned long long *keys;
     const unsigned long long *coff;
     const uint32_t *ucount;
+    const uint32_t *kcount, *kroom;  // nullable: queries of groups (kroom > 0): keys written, their room
     const uint32_t *flag;
     int32_t K, LC, dtype, dp, d;
     float eps;

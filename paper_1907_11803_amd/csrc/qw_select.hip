@@ -3,24 +3,12 @@
 // Section 3); for float data every key within the proven FP32 error band of
 // the K-th is re-ranked by its FP64 index-order distance.  Queries that do not
 // fit (list or band capacity) go to the fallback.
+#include "qw_band.h"
 #include "qw_exact.h"
 #include "qw_internal.h"
 #include "qw_wave.h"
 
 namespace qw {
-
-// Band threshold, rounded up to float: with keys F of |F - D| <= eps D + err,
-// the K-th distance is at most (F_K + err) / (1 - eps), so every key of the
-// exact top-K is at most (F_K + err) (1 + eps) / (1 - eps) + err.  Keys near
-// FP32's end may stand for larger distances: no bound.
-__device__ inline float band_threshold(float FK, float eps, float err)
-{
-    if (!(FK < 1e37f)) return INFINITY;
-    const double t = ((double)FK + (double)err) * (1.0 + (double)eps) / (1.0 - (double)eps) + (double)err + 0x1p-100;
-    float f = (float)t;
-    if ((double)f < t) f = nextafterf(f, INFINITY);
-    return f;
-}
 
 constexpr int kSelRegs = 8;  // keys per thread held in registers
 
@@ -57,10 +45,12 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
     const unsigned long long lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     // the flag, the count and the range offset load together (uniform)
     const uint32_t bad = A.flag[q];
-    const uint32_t U = A.ucount[q];
+    // keys written: the candidates, or fewer (queries that shared a workgroup)
+    const uint32_t room = A.kroom ? A.kroom[q] : 0u;
+    const uint32_t U = room ? A.kcount[q] : A.ucount[q];
     const unsigned long long coff = A.coff[q];
     const float err = DT == QW_F32 && A.abs_err ? A.abs_err[q] : 0.f;
-    if (bad) {  // uniform
+    if (bad || (room && U > room)) {  // uniform
         if (tid == 0) A.fb_list[atomicAdd(A.fb_count, 1u)] = (int32_t)q;
         return;
     }

@@ -607,6 +607,21 @@ def test_grouped_float_queries_ties_and_extremes():
             assert np.array_equal(g.cpu().numpy(), w.cpu().numpy(), equal_nan=True)
 
 
+@pytest.mark.parametrize("K,n,Q", [(1, 5000, 64), (48, 5000, 64), (49, 5000, 64),  # edge of the bounded keys
+                                   (10, 383, 40), (10, 385, 40), (37, 30, 40)])     # its first rows; fewer than K
+@pytest.mark.parametrize("same", [False, True])  # True: equal rows, every key within the bound
+def test_group_key_bound(K, n, Q, same):
+    data, q = grouped_workload(K + n, n, 48, Q, 1, 0.05)
+    if same:
+        data[:] = data[0]
+    p = synth.hash_params(5, 3, 2, 48, 50.0)
+    ix = build(data, p.a, p.b(), 50.0)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), 50.0, K)
+    ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1), stats=True)
+    check_topk(ids, dist, ids_o, dist_o, False)
+    assert st["cand_unique"] == int(cnt_o.sum())
+
+
 def test_huge_w_equals_bruteforce():
     """Every point in one bucket per layer: LSH top-K equals exact kNN."""
     rng = np.random.default_rng(61)
