@@ -33,16 +33,25 @@ enum {
 };
 // u32: overflow-queue lengths per class (queue i holds queries that overflowed
 // class i-1), fallback queue, misc, then kXcd work counters per class
-enum { W_CLSDONE = 0, W_TOPK2 = 1, W_WORK = 2 /* .. 5: counting split counts */, W_GEXTRA = 8 /* .. 15 unused */, W_QCNT = 16 /* .. 32 */, W_SIMPLE = 33, W_MAX = 34,
+enum { W_CLSDONE = 0, W_TOPK2 = 1, W_WORK = 2 /* .. 5: counting split counts */, W_GEXTRA = 8, W_GCOUNT = 9 /* .. 14; 15 unused */, W_QCNT = 16 /* .. 32 */, W_SIMPLE = 33, W_MAX = 34,
        W_DUMMY = 35, W_QMERGED = 36, W_FB = 44, W_FBWORK = 45, W_STAGE = 46, W_XWORK = 48,
-       kC32 = W_XWORK + kXcd * (kMaxClasses + 1) };
+       W_GWORK = W_XWORK + kXcd * (kMaxClasses + 1) /* .. groups' kernels, their overflow */,
+       kC32 = W_GWORK + 3 * kXcd };
 constexpr int kQueueMerged = kMaxClasses + 1;  // overflow queue of the merged launch
 // Classes the several-queries kernel serves: sets of up to 2^14 slots by their
 // bound, about half of it distinct (its own set takes 6,144 ids).
 constexpr int kGroupedSetLog2 = 14;
-// Keys held per query of a group: about 16 K pass the bound of a group's first
-// rows; a query with more goes to the fallback.
-constexpr uint32_t kGroupedKeys = 2048;
+// uint8 rows: a label gives groups from kMinRun queries on, and a group shares a
+// workgroup where its queries list kShareGain times as many ids as their distinct
+// buckets hold: below, the per-query kernel answers as fast, or faster.
+// (50,000 queries over 1M x 128, 50 a cluster, two probes, listing 3 times as
+// many: 1.06 ms query by query, 1.20 shared; without probes the sets overflow,
+// 2.1 and 4.9.  100,000 skewed queries over 10M x 96, listing 6 to 14 times as
+// many: 3.0 ms query by query, 1.5 shared from gain 4 on, 1.6 from 8.)  Queries
+// of few candidates cost little by themselves: 51,000 skewed ones that list 790
+// ids each (150,000 x 50) took 0.58 ms query by query, 0.73 shared; 59,000 that
+// list 1,660 (460,000 x 73) 1.24 and 0.79.
+constexpr uint32_t kMinRun = 8, kShareGain = 8, kShareListed = 1024;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
 constexpr int64_t kCandPerQuery = 4096;  // pair space reserved per query (beyond: fallback)
@@ -125,11 +134,35 @@ Plan make_plan(qw_index *ix, int K)
 }
 
 // Records of the groups, then the label tables.
-size_t group_state_bytes(int64_t Q) { return group_rec_bytes(Q) + 2 * sizeof(uint32_t) * kLabelSlots; }
+size_t group_state_bytes(int64_t Q) { return group_rec_bytes(Q) + group_table_bytes(Q); }
+bool group_held(const qw_index *ix, int64_t Q)
+{
+    return ix->ws.glist.bytes >= group_list_bytes(ix->dtype, Q) && ix->ws.grecs.bytes >= group_state_bytes(Q);
+}
 
-// Grow the query workspace for Q queries (keys: the key list of the select
-// kernel); drops captured graphs when any buffer moves.
-qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false, int64_t group_q = 0)
+// Keys held per query of a group: about 16 K pass the bound of a group's first
+// rows; a query with more goes to the fallback.  Beyond the bound's K, all.
+uint32_t grouped_keys(int dtype, int K)
+{
+    return K <= group_filter_topk(dtype) ? (uint32_t)std::min(2048, std::max(512, 64 * K)) : 0xFFFFFFFFu;
+}
+
+// Do a workload's queries share workgroups?  In the grouped order, of float rows
+// always (what a row's reuse saves is large), of uint8 rows those groups whose
+// queries list the same buckets often enough (kShareGain) -- and only where a
+// query lists enough ids for it to pay (a data point of the collection lists
+// L * mean_hit_bucket; finding the groups costs 30 us more than the plain order).
+bool group_shares(const qw_index *ix, int32_t K, const qw_opts &eff)
+{
+    if (eff.stage_split > 0 || !group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max)) return false;
+    if (!eff.group) return false;
+    if (ix->dtype == QW_F32) return true;
+    return eff.topk_keep >= 0 && K <= group_filter_topk(ix->dtype) &&
+           (double)ix->L * ix->mean_hit_bucket >= (double)kShareListed;
+}
+
+qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false, int64_t group_q = 0,
+                    int group_k = 0)
 {
     Workspace &w = ix->ws;
     auto ptrs = [&w]() {
@@ -195,12 +228,17 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
             const size_t g = (size_t)plan->grid_g * (size_t(1) << plan->cap_g) * 4;
             QW_TRY(grow(w.gscratch, g));
             // one equal region per XCD, each with room for its share of the
-            // queries plus one chunk of items per dedup launch (at most ncls + 1)
-            const int64_t slack = (int64_t)kXcd * kXcdChunk * (plan->ncls + 1);
-            const int64_t cand_cap = std::max<int64_t>((q + slack) * kCandPerQuery, 1 << 20);
+            // queries plus one chunk of items per dedup launch (at most ncls + 1),
+            // but no more than all of them (few queries: 600 MB of slack otherwise)
+            const int64_t share = std::min<int64_t>(q, ceil_div(q, kXcd) + (int64_t)kXcdChunk * (plan->ncls + 1));
+            const int64_t cand_cap = std::max<int64_t>(kXcd * share * kCandPerQuery, 1 << 20);
             QW_TRY(grow(w.coff, sizeof(unsigned long long) * q));
             QW_TRY(grow(w.flag, 4 * sizeof(uint32_t) * q));
             if (keys) QW_TRY(grow(w.pkeys, sizeof(unsigned long long) * cand_cap));
+            // queries of groups alone write keys: the most of each, a quarter
+            // for the XCDs' uneven shares
+            else if (group_q > 0)
+                QW_TRY(grow(w.pkeys, sizeof(unsigned long long) * (size_t)grouped_keys(ix->dtype, group_k) * (size_t)(q + q / 4 + 4096)));
             QW_TRY(grow(w.fb, sizeof(int32_t) * q));
         }
     }
@@ -208,10 +246,9 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
     // one otherwise)
     if (plan && group_q > 0) {
         size_t free_b = 0, total_b = 0;
-        const size_t want = group_list_bytes(group_q) + group_state_bytes(group_q);
-        const bool held = w.glist.bytes >= group_list_bytes(group_q) && w.grecs.bytes >= group_state_bytes(group_q);
-        if (!held && hipMemGetInfo(&free_b, &total_b) == hipSuccess && want < free_b / 4) {
-            (void)w.glist.ensure(group_list_bytes(group_q));
+        const size_t want = group_list_bytes(ix->dtype, group_q) + group_state_bytes(group_q);
+        if (!group_held(ix, group_q) && hipMemGetInfo(&free_b, &total_b) == hipSuccess && want < free_b / 4) {
+            (void)w.glist.ensure(group_list_bytes(ix->dtype, group_q));
             (void)w.grecs.ensure(group_state_bytes(group_q));
         }
         (void)hipGetLastError();
@@ -554,7 +591,7 @@ qw_status check_index(const qw_index *ix)
 // that verify their candidates and either select the top K themselves or
 // write keys into per-XCD regions for the select kernel, then the fallback.
 qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int64_t Q, int K,
-                       const qw_opts &o, hipStream_t s, int32_t *out_ids, void *out_dist,
+                       const qw_opts &o, bool share, hipStream_t s, int32_t *out_ids, void *out_dist,
                        hipEvent_t *ev)
 {
     Workspace &w = ix->ws;
@@ -567,26 +604,26 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     const bool stage = o.stage_split > 0;
     const int topk = !stage && o.topk_keep >= 0 ? plan.topk : 0;  // in-kernel top K
     const bool learned = o.sched == QW_SCHED_LEARNED && !ix->mlp.empty();
-    // float rows in the grouped order: neighbours of one region share a
-    // workgroup, over every class whose bound a group's set may hold half of
-    // (the listed ids repeat across layers); a group beyond its set goes query
-    // by query to the largest such class's LDS sets
+    // neighbours of one region share a workgroup, over every class whose bound a
+    // group's set may hold half of (the listed ids repeat across layers); a
+    // group beyond its set goes query by query to the largest such class's sets
     const int gmax = std::min(kGroupedSetLog2 - kCmin, plan.ncls - 2);
-    const bool use_grouped = o.group && !stage && gmax >= 2 && group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max) &&
-                             w.glist.bytes >= group_list_bytes(Q) && w.grecs.bytes >= group_state_bytes(Q);
+    const bool use_grouped = share && gmax >= 2 && group_held(ix, Q);
+    const uint32_t minrun = ix->dtype == QW_F32 ? 1u : kMinRun;
     // the binning kernel runs the count model itself; the grouped schedule
     // takes the predictions from the inference kernel
     QW_TRY(front(ix, queries, Q, QW_FORM_FAST, s, ev,
-                 learned && o.group ? w.feats.as<float>() : nullptr,
-                 o.group ? w.bmh.as<uint32_t>() : nullptr, clear_in_moves));
+                 learned && (o.group || use_grouped) ? w.feats.as<float>() : nullptr,
+                 o.group || use_grouped ? w.bmh.as<uint32_t>() : nullptr, clear_in_moves));
     if (ev) QW_HIP(hipEventRecord(ev[2], s));
     unsigned long long *seg = w.binoff.as<unsigned long long>();
     unsigned long long *ccount = c64(ix) + C_CLASS;
     int32_t *queues = w.ovf.as<int32_t>();
     const int64_t cand_cap = (int64_t)(w.pkeys.bytes / sizeof(unsigned long long));
-    auto schedule = [&](const int32_t *ex, const float *pl, int force_max,
+    auto schedule = [&](const int32_t *ex, const float *pl, int force_max, bool counting,
                         const int32_t **order) -> qw_status {
-        if (!o.group) {  // classes only: one binning kernel (with the count model)
+        const bool grouped = use_grouped && !counting;
+        if (!o.group && !grouped) {  // classes only: one binning kernel (with the count model)
             QW_TRY(launch_classify_bin(Q, ix->L, ix->n, layer_sizes(ix), ex,
                                        learned && !ex ? ix->mlp_lane.as<uint32_t>() : nullptr,
                                        ix->mlp_margin, force_max, kCmin, plan.cfloor, plan.cmax,
@@ -595,31 +632,43 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             *order = w.order.as<int32_t>();
             return QW_OK;
         }
-        auto *keys = w.keys.as<unsigned long long>();
-        if (use_grouped)
-            QW_TRY(launch_classify_groups(
-                Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin, force_max, kCmin,
-                plan.cfloor, plan.cmax, plan.ncls,
-                reinterpret_cast<uint32_t *>(w.grecs.as<char>() + group_rec_bytes(Q)), keys,
-                w.vals.as<int32_t>(), ccount, s));
-        else
-            QW_TRY(launch_classify(Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin,
-                                   force_max, kCmin, plan.cfloor, plan.cmax, plan.ncls, o.group, keys,
-                                   w.vals.as<int32_t>(), ccount, s));
-        if (Q <= kSmallOrder) {
-            QW_TRY(launch_small_order(keys, w.vals.as<int32_t>(), Q, ccount, plan.ncls, seg, gmax,
-                                      use_grouped ? w.order.as<uint32_t>() : nullptr, s));
-            *order = w.vals.as<int32_t>();
-            return QW_OK;
+        if (grouped) {
+            GroupOrderArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.Q = Q;
+            a.n = ix->n;
+            a.L = ix->L;
+            a.bmh = layer_mh(ix);
+            a.bsize = layer_sizes(ix);
+            a.exact = ex;
+            a.pred_log = pl;
+            a.margin = ix->mlp_margin;
+            a.force_max = force_max;
+            a.cmin = kCmin;
+            a.cfloor = plan.cfloor;
+            a.cmax = plan.cmax;
+            a.ncls = plan.ncls;
+            a.gmax = gmax;
+            a.minrun = minrun;
+            a.bin = w.keys2.as<uint2>();
+            a.cls = w.vals.as<int32_t>();
+            a.order = w.order.as<int32_t>();
+            a.seg = seg;
+            a.class_count = ccount;
+            a.gorder = w.vals2.as<int32_t>();
+            a.groups = w.keys.as<uint2>();
+            a.gcount = c32(ix) + W_GCOUNT;
+            *order = a.order;
+            return launch_group_order(a, reinterpret_cast<uint32_t *>(w.grecs.as<char>() + group_rec_bytes(Q)), s);
         }
+        QW_TRY(launch_classify(Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin,
+                               force_max, kCmin, plan.cfloor, plan.cmax, plan.ncls, o.group,
+                               w.keys.as<unsigned long long>(), w.vals.as<int32_t>(), ccount, s));
         bool alt = false;
-        QW_TRY(radix_sort_pairs(keys, w.vals.as<int32_t>(), Q, 0, use_grouped ? 40 : 24,
+        QW_TRY(radix_sort_pairs(w.keys.as<unsigned long long>(), w.vals.as<int32_t>(), Q, 0, 24,
                                 w.keys2.as<unsigned long long>(), w.vals2.as<int32_t>(), w.hist, s, &alt));
         *order = alt ? w.vals2.as<int32_t>() : w.vals.as<int32_t>();
         QW_TRY(launch_segments(ccount, plan.ncls, seg, s));
-        if (use_grouped)
-            QW_TRY(launch_group_runs(alt ? w.keys2.as<unsigned long long>() : keys, seg, gmax,
-                                     w.order.as<uint32_t>(), s));
         return QW_OK;
     };
     // Classes run from the smallest hash set to the global one.  Each launch
@@ -675,7 +724,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.queue_only = queue_only;
             a.cap_base = kCmin;
             a.xchunk = o.group ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
-            a.xwork = c32(ix) + W_XWORK + kXcd * slot;
+            a.xwork = slot < 0 ? c32(ix) + W_GWORK + 2 * kXcd : c32(ix) + W_XWORK + kXcd * slot;
             a.in_list = in_list;
             a.in_count = in_count;
             a.ovf_list = ovf_list;
@@ -724,7 +773,66 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             return launch_dedup(a, plan.dgrid[hi], st);
         };
         const bool wave = plan.wgrid > 0 && o.dedup == 2;  // o: settings resolved by the caller
-        if (wave && topk && !count_only) {
+        const bool wave_all = wave && topk && !count_only;  // serves every class by itself
+        const bool grouped = use_grouped && !count_only;
+        // all queries of the classes up to gmax are in groups
+        const bool only_groups = grouped && minrun <= 1u;
+        auto groups = [&]() -> qw_status {
+            GroupedArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.dtype = ix->dtype;
+            a.order = w.vals2.as<int32_t>();
+            a.groups = w.keys.as<uint2>();
+            a.gcount = c32(ix) + W_GCOUNT;
+            a.xwork = c32(ix) + W_GWORK;
+            a.xwork2 = c32(ix) + W_GWORK + kXcd;
+            a.xchunk = o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk;
+            a.bstart = w.bstart.as<uint32_t>();
+            a.bsize = w.bsize.as<uint32_t>();
+            a.ids = ix->ids.as<int32_t>();
+            a.n = ix->n;
+            a.nl = ix->nl;
+            a.pmagic = ix->pmagic;
+            a.dp = ix->dp;
+            a.data = ix->data.p;
+            a.queries = w.qrows;
+            a.K = K;
+            a.eps = std::max(plan.eps, group_eps(ix->dp));
+            a.keep = grouped_keys(ix->dtype, K);
+            a.keys = w.pkeys.as<unsigned long long>();
+            a.alloc = c64(ix) + C_ALLOC;
+            a.fail = c64(ix) + C_FAIL;
+            a.region = (unsigned long long)(cand_cap / kXcd);
+            a.ucount = w.ucount.as<uint32_t>();
+            a.coff = w.coff.as<unsigned long long>();
+            a.flag = w.flag.as<uint32_t>();
+            a.abs_err = w.flag.as<float>() + Q;
+            if (only_groups) {
+                a.ovf_list = queues;
+                a.ovf_count = c32(ix) + W_QCNT;
+            } else {  // the classes are served next
+                a.ovf_list = w.order.as<int32_t>();
+                a.cls = w.vals.as<int32_t>();
+                a.seg = seg;
+                a.gain = kShareGain;
+                a.gain_listed = kShareListed;
+                a.groups2 = w.keys2.as<uint2>();
+                a.qlist2 = w.pred.as<int32_t>();
+                a.Q = Q;
+                a.minrun = minrun;
+            }
+            a.ovf_flag = topk ? 2u : 0u;
+            a.kpos = w.flag.as<uint32_t>() + 2 * Q;
+            a.kroom = w.flag.as<uint32_t>() + 3 * Q;
+            a.recs = w.grecs.p;
+            a.extra = c32(ix) + W_GEXTRA;
+            a.glist = w.glist.as<uint2>();
+            a.galloc = c64(ix) + C_GALLOC;
+            a.gregion = (unsigned long long)(w.glist.bytes / sizeof(uint2) / kXcd);
+            return launch_grouped(a, ix->cus, ix->lds_max, s);
+        };
+        if (wave_all) {
+            if (grouped) QW_TRY(groups());
             // one wave per query over every class, largest first; sets that
             // overflow split into id-hash passes inside the kernel
             DedupArgs a;
@@ -757,14 +865,14 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.ucount = w.ucount.as<uint32_t>();
             return launch_dedup_wave(a, plan.wgrid, s);
         }
-        const bool grouped = use_grouped && !count_only;
-        const int merged = grouped ? gmax : std::max(0, std::min(plan.cfloor - kCmin, plan.ncls - 2));
+        const int merged = only_groups ? gmax : std::max(0, std::min(plan.cfloor - kCmin, plan.ncls - 2));
         const int glob = plan.ncls - 1;
         // with two or more global-class workgroups, the side stream's global
         // class and the merged launch's overflow each take half of them (and
         // of their scratch sets), so the latter follows the merged launch on
         // its own stream instead of waiting for the side stream first
         const int gsplit = plan.grid_g >= 2 ? 1 : 0;
+        if (grouped && !only_groups) QW_TRY(groups());  // may add to any class
         QW_HIP(hipEventRecord(ix->fork[0], s));
         QW_HIP(hipStreamWaitEvent(ix->side, ix->fork[0], 0));
         for (int i = merged + 1; i < plan.ncls; ++i) {
@@ -774,45 +882,10 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
                                 queues + (int64_t)(i + 1) * Q, c32(ix) + W_QCNT + i + 1, i, 0,
                                 ix->side, i == glob ? gsplit : 0));
         }
-        if (grouped) {
-            GroupedArgs a;
-            std::memset(&a, 0, sizeof(a));
-            a.order = order;
-            a.groups = w.order.as<uint32_t>();  // free with grouping: [kMaxClasses * Q] words
-            a.xwork = c32(ix) + W_XWORK + kXcd * merged;
-            a.xwork2 = c32(ix) + W_XWORK;  // class 0's, served here
-            a.xchunk = o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk;
-            a.bstart = w.bstart.as<uint32_t>();
-            a.bsize = w.bsize.as<uint32_t>();
-            a.ids = ix->ids.as<int32_t>();
-            a.n = ix->n;
-            a.nl = ix->nl;
-            a.pmagic = ix->pmagic;
-            a.dp = ix->dp;
-            a.data = ix->data.p;
-            a.queries = w.qrows;
-            a.K = K;
-            a.eps = std::max(plan.eps, group_eps(ix->dp));
-            a.keep = K <= group_filter_topk() ? kGroupedKeys : 0xFFFFFFFFu;
-            a.keys = w.pkeys.as<unsigned long long>();
-            a.alloc = c64(ix) + C_ALLOC;
-            a.fail = c64(ix) + C_FAIL;
-            a.region = (unsigned long long)(cand_cap / kXcd);
-            a.ucount = w.ucount.as<uint32_t>();
-            a.coff = w.coff.as<unsigned long long>();
-            a.flag = w.flag.as<uint32_t>();
-            a.abs_err = w.flag.as<float>() + Q;
-            a.ovf_count = c32(ix) + W_QMERGED;
-            a.ovf_list = queues + (int64_t)kQueueMerged * Q;
-            a.kpos = w.flag.as<uint32_t>() + 2 * Q;
-            a.kroom = w.flag.as<uint32_t>() + 3 * Q;
-            a.recs = w.grecs.p;
-            a.extra = c32(ix) + W_GEXTRA;
-            a.glist = w.glist.as<uint2>();
-            a.galloc = c64(ix) + C_GALLOC;
-            a.gregion = (unsigned long long)(w.glist.bytes / sizeof(uint2) / kXcd);
-            QW_TRY(launch_grouped(a, ix->cus, ix->lds_max, s));
-            QW_TRY(launch_range(merged, merged, a.ovf_list, a.ovf_count, queues, c32(ix) + W_QCNT, 1, 1, s));
+        if (only_groups) {
+            QW_TRY(groups());
+            QW_TRY(launch_range(gmax, gmax, queues, c32(ix) + W_QCNT, queues + (int64_t)kQueueMerged * Q,
+                                c32(ix) + W_QMERGED, -1, 1, s));
         } else {
             QW_TRY(launch_range(0, merged, nullptr, nullptr, queues + (int64_t)kQueueMerged * Q,
                                 c32(ix) + W_QMERGED, merged, 0, s));
@@ -820,8 +893,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         QW_HIP(hipEventRecord(ix->fork[1], ix->side));
         if (!gsplit) QW_HIP(hipStreamWaitEvent(s, ix->fork[1], 0));
         // overflow of the merged launch (usually none): the global class, queue only
-        QW_TRY(launch_range(glob, glob, grouped ? queues : queues + (int64_t)kQueueMerged * Q,
-                            c32(ix) + (grouped ? W_QCNT : W_QMERGED),
+        QW_TRY(launch_range(glob, glob, queues + (int64_t)kQueueMerged * Q, c32(ix) + W_QMERGED,
                             queues + (int64_t)(glob + 1) * Q, c32(ix) + W_DUMMY, kMaxClasses, 1, s,
                             gsplit ? 2 : 0));
         if (gsplit) QW_HIP(hipStreamWaitEvent(s, ix->fork[1], 0));
@@ -831,20 +903,21 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     const int32_t *exact = nullptr;
     const float *pred_log = nullptr;
     if (o.sched == QW_SCHED_ACTUAL) {  // extra counting pass: exact |C(q)|
-        QW_TRY(schedule(nullptr, nullptr, 0, &order));
+        QW_TRY(schedule(nullptr, nullptr, 0, true, &order));
         QW_TRY(dedup_classes(order, 1));
         QW_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(ccount), 0u, 2 * kMaxClasses, s));
         QW_TRY(launch_fill_u32(c32(ix) + W_CLSDONE, 0u, W_SIMPLE - W_CLSDONE, s));
         QW_TRY(launch_fill_u32(c32(ix) + W_XWORK, 0u, kXcd * (kMaxClasses + 1), s));
         QW_TRY(launch_fill_u32(c32(ix) + W_QMERGED, 0u, 1, s));
         exact = reinterpret_cast<const int32_t *>(w.ucount.p);
-    } else if (learned && o.group) {
+    } else if (learned && (o.group || use_grouped)) {
         QW_TRY(launch_mlp_predict_bf16(ix->mlp_dev.as<float>(), ix->L, w.feats.as<float>(), Q,
                                        w.mlpout.as<float>(), s));
         pred_log = w.mlpout.as<float>();
     }
-    QW_TRY(schedule(exact, pred_log, o.sched == QW_SCHED_NONE, &order));
-    if (!topk) QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, (use_grouped ? 4 : 1) * Q, s));  // read by the select kernel
+    QW_TRY(schedule(exact, pred_log, o.sched == QW_SCHED_NONE, false, &order));
+    if (!topk || use_grouped)
+        QW_TRY(launch_fill_u32(w.flag.as<uint32_t>(), 0u, (use_grouped ? 4 : 1) * Q, s));  // read by the select kernel
     if (ev) QW_HIP(hipEventRecord(ev[3], s));
     QW_TRY(dedup_classes(order, 0));
     if (ev) QW_HIP(hipEventRecord(ev[6], s));
@@ -869,7 +942,11 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     m.out_dist = out_dist;
     m.data = ix->data.p;
     m.queries = w.qrows;
-    if (!topk) QW_TRY(launch_select(m, Q, s));
+    if (topk && use_grouped) {  // the others have their top K
+        m.qlist = w.pred.as<int32_t>();
+        m.qcount = c32(ix) + W_GCOUNT + kGroupCounts + 1;
+    }
+    if (!topk || use_grouped) QW_TRY(launch_select(m, Q, s));
     if (ev) QW_HIP(hipEventRecord(ev[4], s));
     // queries flagged on the way (list space, ties or band wider than the list):
     // the fused per-query kernel with a global hash set answers them
@@ -1246,12 +1323,11 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             if (ix->nl > 64 || rb > kStageMaxRow || stage_lds_bytes(rb, eff.stage_split, &icn, &dcn) > ix->lds_max)
                 eff.stage_split = -1;
         }
+        const bool share = group_shares(ix, K, eff);
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,
-                         eff.group && eff.stage_split <= 0 &&
-                                 group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max)
-                             ? Q : 0));
+                         share ? Q : 0, K));
         if (opt.timing || !opt.graph) {
-            QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, s, out_ids, out_dist,
+            QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, share, s, out_ids, out_dist,
                                 opt.timing ? ix->ev : nullptr));
         } else {
             GraphKey key;
@@ -1262,6 +1338,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             key.dedup = eff.dedup;
             key.xchunk = eff.xchunk;
             key.split = eff.stage_split;
+            key.share = share && group_held(ix, Q);
             auto it = ix->graphs.find(key);
             if (it == ix->graphs.end()) {
                 hipStream_t cs;
@@ -1272,7 +1349,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
                     (void)hipStreamDestroy(cs);
                     return QW_EDEVICE;
                 }
-                rc = enqueue_fast(ix, plan, queries, Q, K, eff, cs, out_ids, out_dist, nullptr);
+                rc = enqueue_fast(ix, plan, queries, Q, K, eff, share, cs, out_ids, out_dist, nullptr);
                 hipError_t ec = hipStreamEndCapture(cs, &g);
                 (void)hipStreamDestroy(cs);
                 if (rc != QW_OK) {

@@ -1,8 +1,11 @@
-// Candidate work for float rows, several queries per workgroup: queries whose
-// candidate sets overlap (neighbours of the grouped order with the same
-// min-hash) form their union together and verify every row of it once, on the
-// matrix cores -- the bucket's points are staged once and reused by the
-// queries that hit it (Sections 4 and 5.1).
+// Candidate work of several queries per workgroup: queries whose candidate sets
+// overlap (neighbours of the grouped order with the same label) form their
+// union together and verify every row of it once, on the matrix cores -- the
+// bucket's points are staged once and reused by the queries that hit it
+// (Sections 4 and 5.1).
+//
+// group_gain_kernel (uint8 rows) keeps the groups whose queries list the same
+// buckets often enough.
 //
 // group_union_kernel, one workgroup per group of at most 32 queries: the queries'
 // buckets, each once with a mask of the queries that list it, then their ids into
@@ -13,10 +16,11 @@
 // off.
 //
 // group_verify_kernel, one workgroup per group, or per piece of a group's rows
-// where there are few groups: 16 x 16 blocks of rows x queries,
-// v_mfma_f32_16x16x4f32 over x' = x - q0 and q' = q - q0 (q0: one query of the
-// group), give F = |x'|^2 + |q'|^2 - 2 x'.q', and each (row, query) pair of the
-// mask that may be among the query's K nearest writes its (F, id) key for the
+// where there are few groups, 16 x 16 blocks of rows x queries: distances by
+// v_mfma_i32_16x16x64_i8 (uint8 rows: exact, x - 128 and q - 128 are signed
+// bytes), or v_mfma_f32_16x16x4f32 over x' = x - q0 and q' = q - q0 (q0: one
+// query of the group), F = |x'|^2 + |q'|^2 - 2 x'.q'.  Each (row, query) pair of
+// the mask that may be among the query's K nearest writes its (F, id) key for the
 // select kernel.
 //
 // Error of F against the exact squared distance D (u = 2^-24, c = 2 (dp + 16) u,
@@ -37,7 +41,10 @@
 // Measured (1M x 960, w = 12): 100,000 clustered queries took 63 ms query by
 // query; the unions now take 0.75 ms (2.25 when every query inserted its ids by
 // itself), the verification 7.4, the select kernel 1.7 (2.3 when all candidates
-// wrote keys); 1,000 scattered queries 2.3 ms before, 0.08, 0.99 and 0.03 now.
+// wrote keys); 1,000 scattered queries 2.3 ms before, 0.08, 0.75 and 0.03 now.
+// uint8 (10M x 96, 100,000 skewed queries): 2.9 ms query by query, now the unions
+// 0.34, the verification 0.37 (bound by the work on its outputs), the select
+// kernel 0.24 and the queries given back 0.34.
 #include <algorithm>
 #include <type_traits>
 
@@ -50,8 +57,14 @@ namespace {
 
 constexpr int kGB = 512;                                // threads per workgroup
 constexpr int kGW = kGB / 64;                           // waves
-constexpr int kVB = 768, kVW = kVB / 64;                // of the verification
-constexpr int kGQ = 32;                                 // queries per group
+// of the verification (float rows: the queries fill LDS, one workgroup per CU;
+// uint8: 256 threads took 0.67 ms where 512 take 0.46 and 1024 0.48)
+template <int DT> constexpr int kVB = DT == QW_F32 ? 768 : 512;
+template <int DT> constexpr int kVW = kVB<DT> / 64;
+// minima per query: wave, quarter of its lanes, 16-row block
+template <int DT> constexpr int kVCells = kVW<DT> * 8;
+template <int DT> constexpr int kGFilterK = kVCells<DT> / 2;  // K up to which they bound the K-th key
+constexpr int kGQ = kGroupMax;                          // queries per group
 constexpr int kGSetLog2 = 13;                           // set slots
 constexpr uint32_t kGLimit = (1u << kGSetLog2) / 4 * 3;  // rows of a group at most (load <= 3/4)
 constexpr int kGRound = 4;                              // listed ids per thread per round
@@ -85,130 +98,6 @@ constexpr uint32_t kGParts = 1536;                      // bucket parts of a gro
 constexpr size_t kUnionLds = (size_t(8) << kGSetLog2) + size_t(kGParts) * 10;
 static_assert((size_t(12) << kGMapLog2) <= (size_t(8) << kGSetLog2), "the bucket map lies in the set");
 static_assert(64 * kGQ <= 1 << (kGMapLog2 - 1), "the bucket map never fills");
-// Groups of the order's first seg[2 cls + 1] items: a group starts where the
-// class or label changes (a run) and at every kGQ-th item of a run.  out[0] = their
-// number, out[1 + g] = first item of group g, out[1 + number] = the items'
-// number.  One workgroup; the keys are read once, in order.
-constexpr int kRunBlock = 1024, kRunItems = 4;
-template <class Key>
-__device__ inline void find_groups(Key keys, int64_t N, uint32_t *__restrict__ out)
-{
-    __shared__ uint32_t wsum[kRunBlock / 64], wrun[kRunBlock / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t carry = 0, crun = 0;  // groups so far, start of the run before this round (+ 1)
-    for (int64_t b = 0; b < N; b += kRunBlock * kRunItems) {
-        const int64_t i0 = b + (int64_t)tid * kRunItems;
-        unsigned long long k[kRunItems], prev = i0 > 0 && i0 < N ? keys(i0 - 1) >> kGroupOrderBits : 0ull;
-#pragma unroll
-        for (int r = 0; r < kRunItems; ++r) k[r] = i0 + r < N ? keys(i0 + r) >> kGroupOrderBits : 0ull;
-        // the last run start at or before each item: within the thread, then a
-        // running maximum over the threads before it
-        uint32_t start[kRunItems], last = 0;  // position + 1; 0: before this thread
-#pragma unroll
-        for (int r = 0; r < kRunItems; ++r) {
-            if (i0 + r < N && (i0 + r == 0 || k[r] != prev)) last = (uint32_t)(i0 + r) + 1u;
-            prev = k[r];
-            start[r] = last;
-        }
-        uint32_t x = last;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = (uint32_t)__shfl_up((int)x, off);
-            if (lane >= off) x = max(x, y);
-        }
-        uint32_t before = (uint32_t)__shfl_up((int)x, 1);
-        if (lane == 0) before = 0u;
-        __syncthreads();  // the previous round's values have been read
-        if (lane == 63) wrun[wv] = x;
-        __syncthreads();
-        uint32_t all = crun;
-        before = max(before, crun);
-        for (int w = 0; w < kRunBlock / 64; ++w) {
-            before = w < wv ? max(before, wrun[w]) : before;
-            all = max(all, wrun[w]);
-        }
-        crun = all;
-        uint32_t flags = 0;
-#pragma unroll
-        for (int r = 0; r < kRunItems; ++r) {
-            const uint32_t st = (start[r] ? start[r] : before) - 1u;
-            if (i0 + r < N && ((uint32_t)(i0 + r) - st) % kGQ == 0u) flags |= 1u << r;
-        }
-        const uint32_t c = (uint32_t)__popc(flags);
-        x = c;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = (uint32_t)__shfl_up((int)x, off);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wv] = x;
-        __syncthreads();
-        uint32_t at = carry + x - c;
-        for (int w = 0; w < kRunBlock / 64; ++w) {
-            at += w < wv ? wsum[w] : 0u;
-            carry += wsum[w];
-        }
-#pragma unroll
-        for (int r = 0; r < kRunItems; ++r)
-            if ((flags >> r) & 1u) out[1 + at++] = (uint32_t)(i0 + r);
-    }
-    if (tid == 0) {
-        out[0] = carry;
-        out[1 + carry] = (uint32_t)N;
-    }
-}
-
-__global__ __launch_bounds__(kRunBlock) void group_runs_kernel(const unsigned long long *__restrict__ keys,
-                                                               const unsigned long long *__restrict__ seg,
-                                                               int32_t cls, uint32_t *__restrict__ out)
-{
-    find_groups([&](int64_t i) { return keys[i]; }, (int64_t)seg[2 * cls + 1], out);
-}
-
-// The whole order of a small workload in one workgroup: a bitonic sort of (key,
-// query) words in LDS, the class segments, the groups.  (Radix passes are three
-// launches each: five of them took 95 us for 1,000 queries, this 18.)
-__global__ __launch_bounds__(kRunBlock) void small_order_kernel(
-    unsigned long long *__restrict__ keys, int32_t *__restrict__ vals, int32_t Q,
-    const unsigned long long *__restrict__ class_count, int32_t ncls, unsigned long long *__restrict__ seg,
-    int32_t cls, uint32_t *__restrict__ groups)
-{
-    __shared__ unsigned long long w[kSmallOrder];
-    __shared__ unsigned long long s_end;
-    const int tid = threadIdx.x;
-    int n2 = 2;
-    while (n2 < Q) n2 <<= 1;
-    // vals[i] = i: the key with the query below it sorts as the stable order
-    for (int i = tid; i < n2; i += kRunBlock) w[i] = i < Q ? keys[i] << 12 | (unsigned)i : ~0ull;
-    __syncthreads();
-    for (int size = 2; size <= n2; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = tid; i < n2 / 2; i += kRunBlock) {
-                const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
-                const unsigned long long a = w[lo], b = w[hi];
-                if ((b < a) == ((lo & size) == 0)) {
-                    w[lo] = b;
-                    w[hi] = a;
-                }
-            }
-            __syncthreads();
-        }
-    for (int i = tid; i < Q; i += kRunBlock) {
-        keys[i] = w[i] >> 12;
-        vals[i] = (int32_t)(w[i] & 4095u);
-    }
-    if (tid == 0) {
-        unsigned long long off = 0;
-        s_end = 0;
-        for (int c = 0; c < ncls; ++c) {
-            seg[2 * c] = off;
-            off += class_count[c];
-            seg[2 * c + 1] = off;
-            if (c == cls) s_end = off;
-        }
-    }
-    __syncthreads();
-    if (groups) find_groups([&](int64_t i) { return w[i] >> 12; }, (int64_t)s_end, groups);
-}
-
 // Adds bits[r] to the masks of the valid ids, inserting those not yet in the
 // set; returns how many were new, sets `full` when one found no slot.  Most ids
 // are there already (a candidate recurs across layers), so a slot is read
@@ -262,6 +151,124 @@ struct GroupRec {
     uint32_t group;
 };
 
+// Whole wave, a query per lane (q < 0: none): these queries are answered one by
+// one, from a queue or their classes' segments.  Queries of one class go there
+// together, so they stay neighbours.
+__device__ inline void group_give_back(const GroupedArgs &A, int32_t q)
+{
+    const int lane = threadIdx.x & 63;
+    if (q >= 0 && A.ovf_flag) A.flag[q] = A.ovf_flag;
+    const int c = q < 0 ? -1 : A.seg ? A.cls[q] : 0;
+    for (unsigned long long left = __ballot(c >= 0); left;) {
+        const int k = __shfl(c, __ffsll((long long)left) - 1);
+        const unsigned long long same = __ballot(c == k);
+        const int lead = __ffsll((long long)same) - 1;
+        unsigned long long at = 0;
+        if (lane == lead)
+            at = A.seg ? atomicAdd(&A.seg[2 * k + 1], (unsigned long long)__popcll(same))
+                       : atomicAdd(A.ovf_count, (uint32_t)__popcll(same));
+        at = __shfl(at, lead);
+        if (c == k) A.ovf_list[at + (unsigned long long)__popcll(same & (lane ? ~0ull >> (64 - lane) : 0ull))] = q;
+        left &= ~same;
+    }
+}
+
+// Which groups share a workgroup: over kGainLists of the lists, the ids that the
+// queries list (enough per query, too) against the ids of the distinct buckets.
+// One wave per group, two lists of its queries at a time.  Marks the group and
+// counts its queries.
+constexpr int kGainLists = 8, kGainBlock = 1024, kGainGroups = kGainBlock / 64;
+constexpr uint32_t kGainMark = 0x80000000u;
+constexpr uint32_t kGainQueries = 4;  // a quarter of the queries at least
+__global__ __launch_bounds__(kGainBlock) void group_gain_kernel(GroupedArgs A)
+{
+    __shared__ uint32_t s_queries;
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, half = lane & 32;
+    const uint32_t ng = A.gcount[0], g = blockIdx.x * kGainGroups + (tid >> 6);
+    if (blockIdx.x * kGainGroups >= ng) return;  // uniform
+    if (tid == 0) s_queries = 0u;
+    __syncthreads();
+    const uint2 gr = g < ng ? A.groups[g] : uint2{0u, 0u};
+    const int32_t q = (uint32_t)j < gr.y ? A.order[gr.x + j] : -1;
+    uint32_t st[kGainLists / 2], sz[kGainLists / 2];
+#pragma unroll
+    for (int i = 0; i < kGainLists / 2; ++i) {
+        const int r = 2 * i + (half ? 1 : 0);
+        const int l = A.nl <= kGainLists ? r : r * A.nl / kGainLists;
+        const bool in = q >= 0 && l < A.nl;
+        st[i] = in ? A.bstart[(int64_t)q * A.nl + l] : 0u;
+        sz[i] = in ? min(A.bsize[(int64_t)q * A.nl + l], 1u << 16) : 0u;
+        if (sz[i] == 0u) st[i] = 0xFFFFFFFFu;  // no bucket starts there
+    }
+    uint32_t listed = 0, once = 0;
+#pragma unroll
+    for (int i = 0; i < kGainLists / 2; ++i) {
+        bool first = true;
+#pragma unroll
+        for (int k = 0; k < 31; ++k) {
+            const uint32_t os = (uint32_t)__shfl((int)st[i], half | k);
+            first = first && !(k < j && os == st[i]);
+        }
+        listed += sz[i];
+        once += first ? sz[i] : 0u;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        listed += (uint32_t)__shfl_xor((int)listed, off);
+        once += (uint32_t)__shfl_xor((int)once, off);
+    }
+    // uniform in the wave; listed <= 2^24
+    const uint64_t all = (uint64_t)listed * (uint32_t)A.nl / (uint32_t)min(A.nl, kGainLists);
+    if (g < ng && listed >= A.gain * once && all >= (uint64_t)A.gain_listed * gr.y && lane == 0) {
+        A.groups[g].y = gr.y | kGainMark;
+        atomicAdd(&s_queries, gr.y);
+    }
+    __syncthreads();
+    if (tid == 0 && s_queries) atomicAdd(A.gcount + kGroupCounts + 2, s_queries);
+}
+
+// The marked groups become groups2, their queries qlist2 -- unless they are few:
+// the two kernels take about 60 us for any number of them.  The other groups'
+// queries are given back.  What a workgroup's groups take of a counter they take
+// together: thousands of atomics on one address take 20 ns each (50,000 queries,
+// 1,600 groups given back: 65 us group by group, 10 so).
+__global__ __launch_bounds__(kGainBlock) void group_split_kernel(GroupedArgs A)
+{
+    __shared__ uint32_t s_cls[32], s_groups, s_queries;
+    __shared__ unsigned long long s_base[32];
+    constexpr int per = kGainBlock / 32;
+    const int tid = threadIdx.x, j = tid & 31;
+    const uint32_t ng = A.gcount[0], g = blockIdx.x * per + (tid >> 5);
+    if (blockIdx.x * per >= ng) return;  // uniform
+    if (tid < 32) s_cls[tid] = 0u;
+    if (tid == 0) s_groups = s_queries = 0u;
+    __syncthreads();
+    uint2 gr = g < ng ? A.groups[g] : uint2{0u, 0u};
+    const bool share = (gr.y & kGainMark) && (uint64_t)A.gcount[kGroupCounts + 2] * kGainQueries >= (uint64_t)A.Q;
+    gr.y &= ~kGainMark;
+    const int32_t q = (uint32_t)j < gr.y ? A.order[gr.x + j] : -1;
+    const int c = q >= 0 ? A.cls[q] : 0;
+    const bool rest = !share && q >= 0;
+    uint32_t at = 0, qat = 0;
+    if (rest) {
+        at = atomicAdd(&s_cls[c], 1u);
+        if (A.ovf_flag) A.flag[q] = A.ovf_flag;
+    } else if (share && j == 0) {
+        at = atomicAdd(&s_groups, 1u);
+        qat = atomicAdd(&s_queries, gr.y);
+    }
+    __syncthreads();
+    if (tid < 32 && s_cls[tid]) s_base[tid] = atomicAdd(&A.seg[2 * tid + 1], (unsigned long long)s_cls[tid]);
+    if (tid == 32 && s_groups) s_groups = atomicAdd(A.gcount + kGroupCounts, s_groups);
+    if (tid == 33 && s_queries) s_queries = atomicAdd(A.gcount + kGroupCounts + 1, s_queries);
+    __syncthreads();
+    if (rest) A.ovf_list[s_base[c] + at] = q;
+    qat = (uint32_t)__shfl((int)qat, tid & 32);
+    if (share) {
+        if (j == 0) A.groups2[s_groups + at] = gr;
+        if (q >= 0) A.qlist2[s_queries + qat + j] = q;
+    }
+}
+
 __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -278,8 +285,10 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
     constexpr uint32_t nmap = 1u << kGMapLog2;
     uint32_t *mkey = reinterpret_cast<uint32_t *>(smem), *mmask = mkey + nmap, *msize = mmask + nmap;
     GroupRec *recs = static_cast<GroupRec *>(A.recs);
-    const uint32_t ng = A.groups[0];
+    const uint32_t ng = *A.gcount;
+    if (ng == 0) return;
     const int xcd = blockIdx.x % kXcd;
+    auto overflow = [&](int32_t q) { group_give_back(A, q); };  // wave 0
     auto item_of = [&](uint32_t k) -> uint32_t {  // the k-th group of this XCD
         const uint64_t it = ((uint64_t)(k / A.xchunk) * kXcd + xcd) * A.xchunk + k % A.xchunk;
         return it < ng ? (uint32_t)it : ng;
@@ -289,7 +298,7 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
     while (true) {
         const uint32_t g = s_next;
         if (g >= ng) return;  // uniform
-        const uint32_t i0 = A.groups[1 + g], m = A.groups[2 + g] - i0;  // 1 <= m <= kGQ
+        const uint32_t i0 = A.groups[g].x, m = A.groups[g].y;  // 1 <= m <= kGQ
         __syncthreads();
         if (tid == 0) s_next = item_of(atomicAdd(A.xwork + xcd, 1u));
         if (tid < kGQ) {
@@ -345,12 +354,18 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
         __syncthreads();
         const uint32_t nb = s_nb;
         const bool many = nb > kGParts || s_full;  // uniform
+        if (many) {
+            if (tid == 0) recs[g] = GroupRec{0ull, 0u, 0u, 0, g};
+            if (wv == 0) overflow(lane < (int)m ? s_q[lane] : -1);
+            __syncthreads();
+            continue;
+        }
         for (uint32_t i = 2 * tid; i < (1u << kGSetLog2); i += 2 * kGB)
             *reinterpret_cast<uint4 *>(tab + i) = uint4{kEmpty, 0u, kEmpty, 0u};
         __syncthreads();
         // the union: each half of a wave takes part after part, 32 ids at a
         // time, the next round's ids loading while this one's are inserted
-        if (!many) {
+        {
             const uint32_t hl = lane & 31;
             uint32_t off = 0, mk = 0, rem = 0;  // the half's part: its next id, mask, ids left
             bool more = true;
@@ -404,9 +419,9 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
             }
         }
         __syncthreads();
-        if (many || s_full || s_u > kGLimit) {  // uniform: beyond the set
+        if (s_full || s_u > kGLimit) {  // uniform: beyond the set
             if (tid == 0) recs[g] = GroupRec{0ull, 0u, 0u, 0, g};
-            if (tid < (int)m) A.ovf_list[atomicAdd(A.ovf_count, 1u)] = s_q[tid];
+            if (wv == 0) overflow(lane < (int)m ? s_q[lane] : -1);
             __syncthreads();
             continue;
         }
@@ -464,11 +479,7 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
                 }
                 const uint32_t tot = (uint32_t)__shfl((int)x, 63);
                 unsigned long long at = 0, off = 0;
-                uint32_t slot = g;
-                if (lane == 0) {
-                    at = atomicAdd(A.galloc + xcd, (unsigned long long)U);
-                    if (!first) slot = ng + atomicAdd(A.extra, 1u);
-                }
+                if (lane == 0) at = atomicAdd(A.galloc + xcd, (unsigned long long)U);
                 at = __shfl(at, 0);
                 const bool room = at + U <= A.gregion;
                 if (lane == 0 && room) off = atomicAdd(A.alloc + xcd, (unsigned long long)tot);
@@ -477,18 +488,17 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
                 if (room && !ok && lane == 0) atomicMax(A.fail + xcd, ~off);
                 if (in) {
                     const int32_t q = s_q[l32];
-                    if (!room) {  // beyond the list space
-                        A.ovf_list[atomicAdd(A.ovf_count, 1u)] = q;
-                    } else {
+                    if (room) {
                         A.ucount[q] = ok ? s_cnt[l32] : 0u;
                         A.kroom[q] = cnt;
                         A.coff[q] = off + (unsigned long long)xcd * A.region + (x - cnt);
                         if (!ok) A.flag[q] = 1u;  // no key space: answered by the fallback
                     }
                 }
+                if (!room) overflow(in ? s_q[l32] : -1);  // beyond the list space
                 at += (unsigned long long)xcd * A.gregion;
                 if (lane == 0) {
-                    recs[slot] = GroupRec{at, ok ? U : 0u, keep, j0, g};
+                    recs[first ? g : ng + atomicAdd(A.extra, 1u)] = GroupRec{at, ok ? U : 0u, keep, j0, g};
                     s_rows = ok ? at : ~0ull;
                 }
             }
@@ -505,8 +515,8 @@ __global__ __launch_bounds__(kGB, 4) void group_union_kernel(GroupedArgs A)
                     at += (unsigned long long)__popcll(b);
                 }
             }
-            first = false;
             __syncthreads();
+            first = false;
         }
         if (first && tid == 0) recs[g] = GroupRec{0ull, 0u, 0u, 0, g};
         __syncthreads();
@@ -524,7 +534,7 @@ struct VerifyGroup {
     const unsigned char *qp;   // q' [kGQ][ldq bytes]
     const float *q0s;          // q0 (float rows)
     const uint32_t *qn;        // |q'|^2 per query
-    uint32_t *minima;          // [kGQ][kVCells]
+    uint32_t *minima;          // [kGQ][kVCells<DT>]
     uint32_t *thr;             // per query: keys beyond it are not needed
     const float *err;          // absolute part of the keys' error (float rows)
     const unsigned long long *base;
@@ -533,9 +543,6 @@ struct VerifyGroup {
     const int32_t *q;
     bool pieces;
 };
-constexpr int kVCells = kVW * 8;  // minima per query: wave, quarter of its lanes, 16-row block
-constexpr int kGFilterK = kVCells / 2;  // K up to which the minima bound the K-th key
-
 // Bytes of a row per step (a 16-byte part per quarter of the lanes), and steps
 // whose loads are in flight together.
 constexpr int kStepBytes = 64;
@@ -551,8 +558,8 @@ template <int DT> __host__ __device__ inline int verify_ldq(int dp)
 // bytes of them load while the current ones multiply.
 //
 // Few of a query's rows are among its K nearest, so few keys are written: after
-// the waves' first tiles (384 rows, in the order of the ids' hash) the K-th
-// smallest of a query's 96 minima over disjoint parts of them bounds its K-th
+// the waves' first tiles (32 rows each, in the order of the ids' hash) the K-th
+// smallest of a query's minima over disjoint parts of them bounds its K-th
 // key; rows beyond that bound (float rows: beyond its error band) give no key.
 template <int DT, int CB>
 __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
@@ -574,9 +581,9 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
     // kept where fewer than K minima lie below
     auto bounds = [&]() {
         __syncthreads();
-        for (int j = wv; j < 16 * CB; j += kVW) {  // uniform
-            const uint32_t *c = G.minima + j * kVCells;
-            const uint32_t v0 = c[lane], v1 = lane + 64 < kVCells ? c[lane + 64] : kNoKey;
+        for (int j = wv; j < 16 * CB; j += kVW<DT>) {  // uniform
+            const uint32_t *c = G.minima + j * kVCells<DT>;
+            const uint32_t v0 = lane < kVCells<DT> ? c[lane] : kNoKey, v1 = lane + 64 < kVCells<DT> ? c[lane + 64] : kNoKey;
             uint32_t t = 0;
             for (int b = 31; b >= 0; --b) {
                 const uint32_t x = t | 1u << b;
@@ -589,10 +596,10 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
         }
         __syncthreads();
     };
-    static_assert(kVCells <= 128, "two minima per lane");
+    static_assert(kVCells<DT> <= 128, "two minima per lane");
     if (wv >= ntile) {  // no tile: its minima are empty
-        if (A.K <= kGFilterK) {
-            for (int i = lane; i < 16 * CB * 8; i += 64) G.minima[(i >> 3) * kVCells + wv * 8 + (i & 7)] = kNoKey;
+        if (A.K <= kGFilterK<DT>) {
+            for (int i = lane; i < 16 * CB * 8; i += 64) G.minima[(i >> 3) * kVCells<DT> + wv * 8 + (i & 7)] = kNoKey;
             bounds();
         }
         return;
@@ -603,9 +610,9 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
         return uint2{e.x, r < U ? e.y & G.keep : 0u};  // rows past the end: nobody's
     };
     uint2 e0 = entry(wv, 0), e1 = entry(wv, 1), n0 = e0, n1 = e1;
-    if (wv + kVW < ntile) {
-        n0 = entry(wv + kVW, 0);
-        n1 = entry(wv + kVW, 1);
+    if (wv + kVW<DT> < ntile) {
+        n0 = entry(wv + kVW<DT>, 0);
+        n1 = entry(wv + kVW<DT>, 1);
     }
     const unsigned char *p0 = data + (int64_t)e0.x * rb + kg * 16;
     const unsigned char *p1 = data + (int64_t)e1.x * rb + kg * 16;
@@ -724,7 +731,7 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
     auto load_next = [&](acc_t (&b)[2 * NS]) {
         if (++lc == nch) {
             lc = 0;
-            lt += kVW;
+            lt += kVW<DT>;
             if (lt >= ntile) return;  // uniform
             p0 = data + (int64_t)n0.x * rb + kg * 16;
             p1 = data + (int64_t)n1.x * rb + kg * 16;
@@ -738,12 +745,12 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
         if (++c == nch) {
             tile_keys(e0, acc0, xn0, key[0]);
             tile_keys(e1, acc1, xn1, key[1]);
-            if (t == wv && A.K <= kGFilterK) {  // uniform in the workgroup: every wave's first tile
+            if (t == wv && A.K <= kGFilterK<DT>) {  // uniform in the workgroup: every wave's first tile
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int b = 0; b < CB; ++b)
-                        G.minima[(b * 16 + row16) * kVCells + wv * 8 + kg * 2 + h] =
+                        G.minima[(b * 16 + row16) * kVCells<DT> + wv * 8 + kg * 2 + h] =
                             min(min(key[h][b][0], key[h][b][1]), min(key[h][b][2], key[h][b][3]));
                 bounds();
             }
@@ -752,12 +759,12 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
             for (int b = 0; b < CB; ++b) acc0[b] = acc1[b] = acc_t{0, 0, 0, 0};
             xn0 = xn1 = 0;
             c = 0;
-            t += kVW;
+            t += kVW<DT>;
             e0 = n0;
             e1 = n1;
-            if (t + kVW < ntile) {
-                n0 = entry(t + kVW, 0);
-                n1 = entry(t + kVW, 1);
+            if (t + kVW<DT> < ntile) {
+                n0 = entry(t + kVW<DT>, 0);
+                n1 = entry(t + kVW<DT>, 1);
             }
         }
     };
@@ -772,7 +779,7 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
 }
 
 template <int DT>
-__global__ __launch_bounds__(kVB, kVB / 256) void group_verify_kernel(GroupedArgs A)
+__global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_kernel(GroupedArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int32_t s_q[kGQ];
@@ -783,10 +790,10 @@ __global__ __launch_bounds__(kVB, kVB / 256) void group_verify_kernel(GroupedArg
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int dp = A.dp, ldq = verify_ldq<DT>(dp);
     uint32_t *minima = reinterpret_cast<uint32_t *>(smem);
-    unsigned char *qp = smem + sizeof(uint32_t) * kGQ * kVCells;  // q' [kGQ][ldq]
+    unsigned char *qp = smem + sizeof(uint32_t) * kGQ * kVCells<DT>;  // q' [kGQ][ldq]
     float *q0s = reinterpret_cast<float *>(qp + (size_t)kGQ * ldq);
     const GroupRec *recs = static_cast<const GroupRec *>(A.recs);
-    const uint32_t nrec = A.groups[0] + *A.extra;
+    const uint32_t nrec = *A.gcount + *A.extra;
     if (nrec == 0) return;
     // few records: pieces of their rows, four per workgroup of the launch
     const uint32_t np = nrec >= 4u * gridDim.x ? 1u : min(16u, (4u * gridDim.x + nrec - 1u) / nrec);
@@ -805,7 +812,7 @@ __global__ __launch_bounds__(kVB, kVB / 256) void group_verify_kernel(GroupedArg
         const uint32_t ri = (rk / blk * kXcd + xcd) * blk + rk % blk;
         GroupRec rec = {0ull, 0u, 0u, 0, 0u};
         if (ri < nrec) rec = recs[ri];
-        const uint32_t i0 = A.groups[1 + rec.group], m = A.groups[2 + rec.group] - i0;
+        const uint32_t i0 = A.groups[rec.group].x, m = A.groups[rec.group].y;
         __syncthreads();
         if (tid == 0) s_next = atomicAdd(A.xwork2 + xcd, 1u);
         // this piece's rows, whole tiles of 32
@@ -826,9 +833,9 @@ __global__ __launch_bounds__(kVB, kVB / 256) void group_verify_kernel(GroupedArg
         const int64_t rb = (int64_t)dp * (DT == QW_F32 ? 4 : 1);
         const float *q0 = reinterpret_cast<const float *>(queries + (int64_t)s_q[rec.j0] * rb);
         if constexpr (DT == QW_F32)
-            for (int i = tid; i < dp; i += kVB) q0s[i] = q0[i];
+            for (int i = tid; i < dp; i += kVB<DT>) q0s[i] = q0[i];
         const int cols = (keep >> 16) ? 32 : 16;
-        for (int j = wv; j < cols; j += kVW) {
+        for (int j = wv; j < cols; j += kVW<DT>) {
             const bool in = (keep >> j) & 1u;  // uniform
             const int32_t q = in ? s_q[j] : s_q[rec.j0];
             if constexpr (DT == QW_F32) {
@@ -895,53 +902,52 @@ int blocks_per_cu(const void *fn, int threads, size_t lds)
 // minima | q' rows | q0 (float rows)
 static size_t verify_lds(int dtype, int dp)
 {
-    const size_t m = sizeof(uint32_t) * kGQ * kVCells;
-    return dtype == QW_F32 ? m + size_t(kGQ) * verify_ldq<QW_F32>(dp) + ga16(size_t(dp) * 4)
-                           : m + size_t(kGQ) * verify_ldq<QW_U8>(dp);
+    const size_t m = sizeof(uint32_t) * kGQ;
+    return dtype == QW_F32 ? m * kVCells<QW_F32> + size_t(kGQ) * verify_ldq<QW_F32>(dp) + ga16(size_t(dp) * 4)
+                           : m * kVCells<QW_U8> + size_t(kGQ) * verify_ldq<QW_U8>(dp);
 }
 
 float group_eps(int dp) { return 4.f * (float)(dp + 16) * 0x1p-24f * 1.01f; }
 
-// Workspace for Q queries: a record per group, and candidate rows (kGRows per
-// query; a group beyond the space goes to the per-query kernel).
-constexpr int64_t kGRows = 2048;
-size_t group_rec_bytes(int64_t Q) { return sizeof(GroupRec) * (size_t)Q; }
-int group_filter_topk() { return kGFilterK; }
-size_t group_list_bytes(int64_t Q) { return sizeof(uint2) * (size_t)std::max<int64_t>(Q * kGRows, 8 * 65536); }
+// Workspace for Q queries: a record per group, and candidate rows (a group
+// beyond the space goes to the per-query kernel).
+size_t group_rec_bytes(int64_t Q) { return (sizeof(GroupRec) * (size_t)Q + 255) & ~size_t(255); }
+int group_filter_topk(int dtype) { return dtype == QW_F32 ? kGFilterK<QW_F32> : kGFilterK<QW_U8>; }
+size_t group_list_bytes(int dtype, int64_t Q)
+{
+    const int64_t rows = dtype == QW_U8 ? 1024 : 2048;  // uint8: groups of several queries only
+    return sizeof(uint2) * (size_t)std::max<int64_t>(Q * rows, 8 * 65536);
+}
 
-// Float rows whose group of queries fits LDS; at most 64 lists per query.
+// Rows whose group of queries fits LDS (uint8 distances fit 31 bits); at most 64
+// lists per query.
 bool group_applies(int dtype, int dp, int nl, size_t lds_max)
 {
-    return dtype == QW_F32 && nl >= 1 && nl <= 64 && verify_lds(dtype, dp) + 2048 <= lds_max &&
+    return nl >= 1 && nl <= 64 && dp <= 4096 && verify_lds(dtype, dp) + 2048 <= lds_max &&
            kUnionLds + 1024 <= lds_max / 2;
-}
-
-qw_status launch_group_runs(const unsigned long long *keys, const unsigned long long *seg, int cls,
-                            uint32_t *groups, hipStream_t s)
-{
-    group_runs_kernel<<<1, kRunBlock, 0, s>>>(keys, seg, cls, groups);
-    QW_HIP(hipGetLastError());
-    return QW_OK;
-}
-
-qw_status launch_small_order(unsigned long long *keys, int32_t *vals, int64_t Q,
-                             const unsigned long long *class_count, int32_t ncls, unsigned long long *seg,
-                             int cls, uint32_t *groups, hipStream_t s)
-{
-    if (Q < 1 || Q > kSmallOrder) return QW_EINTERNAL;
-    small_order_kernel<<<1, kRunBlock, 0, s>>>(keys, vals, (int32_t)Q, class_count, ncls, seg, cls, groups);
-    QW_HIP(hipGetLastError());
-    return QW_OK;
 }
 
 qw_status launch_grouped(GroupedArgs a, int cus, size_t lds_max, hipStream_t s)
 {
-    if (!group_applies(QW_F32, a.dp, a.nl, lds_max) || a.dp % 16 != 0) return QW_EINTERNAL;
+    if (!group_applies(a.dtype, a.dp, a.nl, lds_max) || a.dp % 16 != 0) return QW_EINTERNAL;
     a.xchunk = std::max(1u, a.xchunk / kGQ);  // in groups
-    const size_t ul = kUnionLds, vl = verify_lds(QW_F32, a.dp);
-    group_union_kernel<<<blocks_per_cu((const void *)group_union_kernel, kGB, ul) * cus, kGB, ul, s>>>(a);
+    if (a.gain > 0) {
+        // groups have a.minrun / 2 queries at least (a label's are of even sizes)
+        const int64_t most = 2 * a.Q / std::max<int64_t>(1, a.minrun) + 1;
+        group_gain_kernel<<<(unsigned)ceil_div(most, kGainGroups), kGainBlock, 0, s>>>(a);
+        QW_HIP(hipGetLastError());
+        group_split_kernel<<<(unsigned)ceil_div(most, kGainBlock / 32), kGainBlock, 0, s>>>(a);
+        QW_HIP(hipGetLastError());
+        a.groups = a.groups2;
+        a.gcount += kGroupCounts;
+    }
+    const size_t vl = verify_lds(a.dtype, a.dp);
+    group_union_kernel<<<blocks_per_cu((const void *)group_union_kernel, kGB, kUnionLds) * cus, kGB, kUnionLds, s>>>(a);
     QW_HIP(hipGetLastError());
-    group_verify_kernel<QW_F32><<<blocks_per_cu((const void *)group_verify_kernel<QW_F32>, kVB, vl) * cus, kVB, vl, s>>>(a);
+    const void *fn = a.dtype == QW_F32 ? (const void *)group_verify_kernel<QW_F32> : (const void *)group_verify_kernel<QW_U8>;
+    const int grid = blocks_per_cu(fn, a.dtype == QW_F32 ? kVB<QW_F32> : kVB<QW_U8>, vl) * cus;
+    if (a.dtype == QW_F32) group_verify_kernel<QW_F32><<<grid, kVB<QW_F32>, vl, s>>>(a);
+    else group_verify_kernel<QW_U8><<<grid, kVB<QW_U8>, vl, s>>>(a);
     QW_HIP(hipGetLastError());
     return QW_OK;
 }

@@ -217,7 +217,7 @@ struct OocIo {
 
 struct GraphKey {
     const void *q; int64_t Q; int32_t K; int32_t *ids; void *dist;
-    int32_t form, sched, group, topk_keep, dedup, xchunk, split;
+    int32_t form, sched, group, topk_keep, dedup, xchunk, split, share;
     bool operator<(const GraphKey &o) const {
         return std::memcmp(this, &o, sizeof(GraphKey)) < 0;
     }
@@ -456,15 +456,30 @@ int verify_per_iter(int dp, int dtype);
 int verify_blocks_per_cu(int dp, int dtype, size_t lds);
 
 // ---------------------------------------------------------------- scheduling
-// Keys of queries that share workgroups (tag: 2 * kLabelSlots words): class << 32 |
-// group key, whose low kGroupOrderBits bits only order its run.
+// Order of a workload whose queries share workgroups.
 constexpr uint32_t kLabelSlots = 1u << 18;
-constexpr int kGroupOrderBits = 12;
-qw_status launch_classify_groups(int64_t Q, int32_t L, int64_t n, const uint32_t *bmh, const uint32_t *bsize,
-                                 const int32_t *exact, const float *pred_log, float margin, int32_t force_max,
-                                 int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t *tag,
-                                 unsigned long long *keys, int32_t *vals, unsigned long long *class_count,
-                                 hipStream_t s);
+constexpr uint32_t kGroupMax = 32;   // queries per group
+constexpr int kGroupCounts = 3;
+struct GroupOrderArgs {
+    int64_t Q, n;
+    int32_t L;
+    const uint32_t *bmh, *bsize;     // per (query, layer)
+    const int32_t *exact;            // nullable, as launch_classify's
+    const float *pred_log;
+    float margin;
+    int32_t force_max, cmin, cfloor, cmax, ncls;
+    int32_t gmax;                    // classes 0 .. gmax may be grouped
+    uint32_t minrun;                 // fewer queries of one label stay in their classes
+    uint2 *bin;                      // [Q] scratch
+    int32_t *cls;                    // [Q] scratch
+    int32_t *order;                  // [ncls][Q]: the classes' other queries
+    unsigned long long *seg, *class_count;
+    int32_t *gorder;                 // [Q]: the groups' queries
+    uint2 *groups;                   // [Q]: first item of gorder, queries
+    uint32_t *gcount;                // [kGroupCounts], zeroed: groups, their queries, gorder's queries without one
+};
+size_t group_table_bytes(int64_t Q);
+qw_status launch_group_order(const GroupOrderArgs &a, uint32_t *tab, hipStream_t s);
 qw_status launch_classify(int64_t Q, int32_t L, int64_t n,
                           const uint32_t *bmh, const uint32_t *bsize, const int32_t *exact,
                           const float *pred_log, float margin, int32_t force_max, int32_t cmin,
@@ -551,8 +566,13 @@ struct DedupArgs {
 
 // Several queries per workgroup over float rows (qw_group.hip).
 struct GroupedArgs {
+    int32_t dtype;
     const int32_t *order;
-    const uint32_t *groups;      // [0]: groups; then each group's first item; then the items
+    uint2 *groups;               // first item of the order, queries
+    uint32_t *gcount;            // [0]: groups; [kGroupCounts ..] (zeroed): those of groups2,
+                                 // their queries, the marked groups' queries
+    int64_t Q;
+    uint32_t minrun;             // as the order's
     uint32_t *xwork, *xwork2;    // per-XCD counters of the two kernels (zeroed)
     uint32_t xchunk;             // consecutive items dealt to one XCD
     const uint32_t *bstart, *bsize;
@@ -571,8 +591,18 @@ struct GroupedArgs {
     uint32_t *flag;
     float *abs_err;              // [Q]: absolute part of the keys' error
     uint32_t *kpos, *kroom;      // [Q], zeroed: keys written, room for them (0: not in a group)
+    // queries of groups beyond a set: to a queue, or (seg) to the ends of their
+    // classes' segments; ovf_flag: what their flag becomes (0: left as it is)
     uint32_t *ovf_count;
     int32_t *ovf_list;
+    const int32_t *cls;
+    unsigned long long *seg;
+    uint32_t ovf_flag;
+    // gain > 0: only groups whose queries list at least gain times the ids of
+    // their distinct buckets share a workgroup: groups2, their queries qlist2
+    uint32_t gain, gain_listed;  // and gain_listed ids per query
+    uint2 *groups2;
+    int32_t *qlist2;
     void *recs;                  // group_rec_bytes
     uint32_t *extra;             // records beyond the groups' first (zeroed)
     uint2 *glist;                // candidate rows in kXcd equal regions
@@ -581,18 +611,8 @@ struct GroupedArgs {
 bool group_applies(int dtype, int dp, int nl, size_t lds_max);
 float group_eps(int dp);         // relative part of the keys' error
 size_t group_rec_bytes(int64_t Q);
-size_t group_list_bytes(int64_t Q);
-int group_filter_topk();         // K up to which few keys are written
-// A workload of at most kSmallOrder queries: keys (below 2^52) and vals sorted in
-// place, the class segments, and (groups non-null) the groups as below, in one
-// launch.
-constexpr int64_t kSmallOrder = 4096;
-qw_status launch_small_order(unsigned long long *keys, int32_t *vals, int64_t Q,
-                             const unsigned long long *class_count, int32_t ncls, unsigned long long *seg,
-                             int cls, uint32_t *groups, hipStream_t s);
-// Groups of equal classes and labels over the order's classes 0 .. cls.
-qw_status launch_group_runs(const unsigned long long *keys, const unsigned long long *seg, int cls,
-                            uint32_t *groups, hipStream_t s);
+size_t group_list_bytes(int dtype, int64_t Q);
+int group_filter_topk(int dtype);         // K up to which few keys are written
 qw_status launch_grouped(GroupedArgs a, int cus, size_t lds_max, hipStream_t s);
 
 struct SelectArgs {
@@ -601,6 +621,8 @@ struct SelectArgs {
     const unsigned long long *coff;
     const uint32_t *ucount;
     const uint32_t *kcount, *kroom;  // nullable: queries of groups (kroom > 0): keys written, their room
+    const int32_t *qlist;        // nullable: the queries, *qcount of them (else all)
+    const uint32_t *qcount;
     const uint32_t *flag;
     int32_t K, LC, dtype, dp, d;
     float eps;

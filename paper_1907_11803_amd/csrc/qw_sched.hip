@@ -59,8 +59,8 @@ __device__ inline int class_of(uint64_t tsum, int64_t n, const int32_t *__restri
 // by chance in one layer.  The smallest minimum of at least two layers, t(q),
 // is a point near the query, but misses the region's smallest where that one
 // collided once.  So the queries vote: for each recurring minimum v of a query,
-// label[v] = the smallest t over the queries that have v; a query's key is the
-// label of t(q), followed twice.  A workload beyond kLabelSample queries is
+// label[v] = the smallest t over the queries that have v; a query's label is
+// that of t(q), followed twice.  A workload beyond kLabelSample queries is
 // sampled evenly.  (Simulated on clusters of 2,000 points: keyed by the
 // min-hash, 95 % of a cluster's queries agree, by t 77 to 84 %, by the label all.)
 // tag[slot] holds the v that owns the slot; a v whose slot is another's keeps
@@ -101,71 +101,231 @@ __global__ __launch_bounds__(kBlock) void label_kernel(int64_t Q, int32_t L, int
     if (o == v && label[s] > t) atomicMin(&label[s], t);
 }
 
-// Key = class << 32 | group key (see label_kernel) of every query, one wave per
-// query: the label's bits decide the run, t's the order within it.
-__global__ __launch_bounds__(kBlock) void classify_group_kernel(
-    int64_t Q, int32_t L, int64_t n, const uint32_t *__restrict__ bmh, const uint32_t *__restrict__ bsize,
-    const int32_t *__restrict__ exact, const float *__restrict__ pred_log, float margin, int32_t force_max,
-    int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t slots,
-    const uint32_t *__restrict__ tag, unsigned long long *__restrict__ keys, int32_t *__restrict__ vals,
-    unsigned long long *class_count)
+// Class, and bin of its label and t, of every query.  A bin is a hash of the
+// label with kSub finer ones by t's: queries of one label that agree on t too are
+// neighbours in the order.  (Counted bins instead of a sort: any order of the
+// bins will do.)  A wave finds kBinWave queries' t after each other, lane l on
+// layer l; then a thread per query looks its label up, and a bin's queries of
+// one workgroup take their places there with one atomic (a skewed workload has
+// one label for a seventh of its queries).
+constexpr uint32_t kSub = 4;
+constexpr int kBinWave = 8, kBinBlock = kBinWave * (kBlock / 64);
+__device__ inline uint32_t bin_count(uint32_t v) { return v + 1u; }  // they start at 0xFFFFFFFF, like the tables
+
+__global__ __launch_bounds__(kBlock) void group_bin_kernel(GroupOrderArgs A, uint32_t slots, uint32_t bins,
+                                                           const uint32_t *__restrict__ tag,
+                                                           uint32_t *__restrict__ count)
 {
-    __shared__ uint32_t hist[32];
-    if (threadIdx.x < 32) hist[threadIdx.x] = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    for (int64_t q = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); q < Q;
-         q += (int64_t)gridDim.x * (kBlock / 64)) {
-        const uint32_t v = lane < L ? bmh[q * L + lane] : 0xFFFFFFFFu;
-        uint64_t tsum = lane < L ? bsize[q * L + lane] : 0u;
-        uint32_t m = v, t;
-        for (int o = 32; o > 0; o >>= 1) {
-            tsum += __shfl_xor(tsum, o);
-            m = min(m, (uint32_t)__shfl_xor((int)m, o));
+    __shared__ uint32_t hist[32], s_t[kBinBlock], s_m[kBinBlock], s_bin[kBinBlock], s_at[kBinBlock], s_sum[kBinBlock];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, L = A.L;
+    const int64_t q0 = (int64_t)blockIdx.x * kBinBlock;
+    if (tid < 32) hist[tid] = 0;
+    constexpr int R = kBinWave < 8 ? kBinWave : 8;
+    for (int r0 = 0; r0 < kBinWave; r0 += R) {
+        uint32_t v[R], z[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t q = q0 + wv * kBinWave + r0 + r;
+            const bool in = lane < L && q < A.Q;
+            v[r] = in ? A.bmh[q * L + lane] : 0xFFFFFFFFu;
+            z[r] = in ? A.bsize[q * L + lane] : 0u;
         }
-        (void)recurs(v, L, &t);
-        uint32_t lb = t;
-        for (int i = 0; i < 2 && lb != 0xFFFFFFFFu; ++i) {
-            const uint32_t s = label_slot(lb, slots);
-            if (tag[s] == lb) lb = min(lb, tag[slots + s]);
-        }
-        if (t == 0xFFFFFFFFu) t = lb = m;
-        constexpr uint32_t low = (1u << kGroupOrderBits) - 1u;
-        const uint32_t g = (mix32(lb) & ~low) | (mix32(t) & low);
-        if (lane == 0) {
-            const int cls = class_of(tsum, n, exact, q, pred_log != nullptr, pred_log ? pred_log[q] : 0.f,
-                                     margin, force_max, cmin, cfloor, cmax, ncls);
-            keys[q] = ((unsigned long long)cls << 32) | g;
-            vals[q] = (int32_t)q;
-            atomicAdd(&hist[cls], 1u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t tsum = z[r];  // below 2^31: the layers hold n * L entries
+            uint32_t m = v[r], t;
+            for (int o = 32; o > 0; o >>= 1) {
+                tsum += (uint32_t)__shfl_xor((int)tsum, o);
+                m = min(m, (uint32_t)__shfl_xor((int)m, o));
+            }
+            (void)recurs(v[r], L, &t);
+            if (lane == 0) {
+                s_t[wv * kBinWave + r0 + r] = t;
+                s_m[wv * kBinWave + r0 + r] = m;
+                s_sum[wv * kBinWave + r0 + r] = tsum;
+            }
         }
     }
     __syncthreads();
-    if (threadIdx.x < ncls && hist[threadIdx.x])
-        atomicAdd(&class_count[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
+    const int64_t q = q0 + tid;
+    uint32_t bin = 0xFFFFFFFFu;
+    if (tid < kBinBlock) {
+        if (q < A.Q) {
+            uint32_t t = s_t[tid], lb = t;
+            for (int i = 0; i < 2 && lb != 0xFFFFFFFFu; ++i) {
+                const uint32_t s = label_slot(lb, slots);
+                if (tag[s] == lb) lb = min(lb, tag[slots + s]);
+            }
+            if (t == 0xFFFFFFFFu) t = lb = s_m[tid];
+            const int cls = class_of(s_sum[tid], A.n, A.exact, q, A.pred_log != nullptr, A.pred_log ? A.pred_log[q] : 0.f,
+                                     A.margin, A.force_max, A.cmin, A.cfloor, A.cmax, A.ncls);
+            atomicAdd(&hist[cls], 1u);
+            if (cls <= A.gmax) bin = (mix32(lb) & (bins - 1u)) * kSub + mix32(t) % kSub;
+            A.cls[q] = cls;
+        }
+        s_bin[tid] = bin;
+    }
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    int lead = 0;
+    if (bin != 0xFFFFFFFFu) {  // the first of the bin's queries here takes their places
+        lead = kBinBlock;
+        for (int i = 0; i < kBinBlock; ++i) {
+            const bool same = s_bin[i] == bin;
+            before += same && i < tid ? 1u : 0u;
+            all += same ? 1u : 0u;
+            lead = same && i < lead ? i : lead;
+        }
+        if (lead == tid) s_at[tid] = bin_count(atomicAdd(&count[bin], all));
+    }
+    __syncthreads();
+    if (tid < kBinBlock && q < A.Q) A.bin[q] = uint2{bin, bin != 0xFFFFFFFFu ? s_at[lead] + before : 0u};
+    if (tid < A.ncls && hist[tid]) atomicAdd(&A.class_count[tid], (unsigned long long)hist[tid]);
 }
 
-// Label tables and keys of a workload whose queries share workgroups.  tag: the
-// slots' owners, then their labels (64 slots a query, kLabelSlots at most).
-qw_status launch_classify_groups(int64_t Q, int32_t L, int64_t n, const uint32_t *bmh, const uint32_t *bsize,
-                                 const int32_t *exact, const float *pred_log, float margin, int32_t force_max,
-                                 int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, uint32_t *tag,
-                                 unsigned long long *keys, int32_t *vals, unsigned long long *class_count,
-                                 hipStream_t s)
+// A label with minrun queries at least gives groups of kGroupMax at most, of
+// even sizes, at the front of gorder; the other labels' queries go to its back.
+// count[] becomes the finer bins' places there (kBack: counted from the back).
+// The class segments start empty.
+constexpr uint32_t kBack = 0x80000000u;
+__global__ __launch_bounds__(kBlock) void group_place_kernel(GroupOrderArgs A, uint32_t bins,
+                                                             uint32_t *__restrict__ count)
 {
-    if (Q <= 0) return QW_OK;
-    if (L > 64) return QW_EINTERNAL;
+    __shared__ uint32_t wsum[3][kBlock / 64], s_base[3];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint32_t b = blockIdx.x * kBlock + tid;
+    if (blockIdx.x == 0 && tid < 2 * A.ncls) A.seg[tid] = (unsigned long long)(tid / 2) * (unsigned long long)A.Q;
+    uint4 *cw = reinterpret_cast<uint4 *>(count + (size_t)b * kSub);
+    uint32_t c[kSub], sum = 0;
+    static_assert(kSub == 4, "one load");
+    const uint4 v = b < bins ? cw[0] : uint4{~0u, ~0u, ~0u, ~0u};
+    c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
+#pragma unroll
+    for (uint32_t i = 0; i < kSub; ++i) sum += bin_count(c[i]);
+    const bool take = sum > 0u && sum >= A.minrun;
+    const uint32_t ng = take ? (sum + kGroupMax - 1u) / kGroupMax : 0u;
+    const uint32_t mine[3] = {ng, take ? sum : 0u, take ? 0u : sum};  // as gcount's words
+    uint32_t x[3] = {mine[0], mine[1], mine[2]};
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x[k], off);
+            if (lane >= off) x[k] += y;
+        }
+    if (lane == 63)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) wsum[k][wv] = x[k];
+    __syncthreads();
+    if (tid < 3) {
+        uint32_t t = 0;
+        for (int w = 0; w < kBlock / 64; ++w) t += wsum[tid][w];
+        s_base[tid] = t ? atomicAdd(A.gcount + tid, t) : 0u;
+    }
+    __syncthreads();
+    if (b >= bins) return;
+    uint32_t at[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        at[k] = s_base[k] + x[k] - mine[k];
+        for (int w = 0; w < wv; ++w) at[k] += wsum[k][w];
+    }
+    uint32_t first = at[1];
+    for (uint32_t i = 0; i < ng; ++i) {
+        const uint32_t size = sum / ng + (i < sum % ng ? 1u : 0u);
+        A.groups[at[0] + i] = uint2{first, size};
+        first += size;
+    }
+    uint32_t pos = take ? at[1] : kBack | at[2];
+#pragma unroll
+    for (uint32_t i = 0; i < kSub; ++i) {
+        const uint32_t n = bin_count(c[i]);
+        c[i] = pos;
+        pos += n;
+    }
+    cw[0] = uint4{c[0], c[1], c[2], c[3]};
+}
+
+// This workgroup's queries (q < 0: none) to the ends of their classes' segments
+// (class c's queries at order[c * Q ..)).  Whole workgroup.
+__device__ inline void append_classes(const GroupOrderArgs &A, int64_t q)
+{
+    __shared__ uint32_t hist[32];
+    __shared__ unsigned long long base[32];
+    const int tid = threadIdx.x;
+    if (tid < 32) hist[tid] = 0;
+    __syncthreads();
+    const int cls = q >= 0 ? A.cls[q] : 0;
+    const uint32_t p = q >= 0 ? atomicAdd(&hist[cls], 1u) : 0u;
+    __syncthreads();
+    if (tid < A.ncls && hist[tid]) base[tid] = atomicAdd(&A.seg[2 * tid + 1], (unsigned long long)hist[tid]);
+    __syncthreads();
+    if (q >= 0) A.order[base[cls] + p] = (int32_t)q;
+}
+
+// Every query with a bin to its place in gorder, the others to their classes.
+__global__ __launch_bounds__(kBlock) void group_scatter_kernel(GroupOrderArgs A, const uint32_t *__restrict__ place)
+{
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    bool rest = false;
+    if (q < A.Q) {
+        const uint2 b = A.bin[q];
+        rest = b.x == 0xFFFFFFFFu;
+        if (!rest) {
+            const uint32_t at = place[b.x] + b.y;
+            A.gorder[at & kBack ? A.Q - 1 - (int64_t)(at & ~kBack) : (int64_t)at] = (int32_t)q;
+        }
+    }
+    append_classes(A, rest ? q : -1);
+}
+
+// The queries at the back of gorder to their classes: queries of one label stay
+// together.
+__global__ __launch_bounds__(kBlock) void group_rest_kernel(GroupOrderArgs A)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x, n = A.gcount[2];
+    if (i - threadIdx.x >= n) return;  // uniform
+    append_classes(A, i < n ? A.gorder[A.Q - 1 - i] : -1);
+}
+
+// Enough for the labels (a query each at most) to seldom share a bin: two regions
+// in one group overflow its set.
+uint32_t group_bins(int64_t Q)
+{
+    uint32_t b = 1024;
+    while (b < (1u << 17) && (int64_t)b < 16 * Q) b <<= 1;
+    return b;
+}
+size_t group_table_bytes(int64_t Q)
+{
+    return sizeof(uint32_t) * (2 * (size_t)kLabelSlots + (size_t)group_bins(Q) * kSub);
+}
+
+// Order of a workload whose queries share workgroups.  tab: the slots' owners and
+// labels (64 slots a query, kLabelSlots at most), then the bins.  100,000 queries:
+// 0.12 ms (sorting them by class, label and t took 0.3).
+qw_status launch_group_order(const GroupOrderArgs &a, uint32_t *tab, hipStream_t s)
+{
+    if (a.Q <= 0) return QW_OK;
+    if (a.L > 64 || a.ncls > 32) return QW_EINTERNAL;
     uint32_t slots = 1024;
-    while (slots < kLabelSlots && (int64_t)slots < 64 * Q) slots <<= 1;
-    QW_TRY(launch_fill_u32(tag, 0xFFFFFFFFu, 2 * (int64_t)slots, s));
+    while (slots < kLabelSlots && (int64_t)slots < 64 * a.Q) slots <<= 1;
+    const uint32_t bins = group_bins(a.Q);
+    uint32_t *count = tab + 2 * (size_t)slots;
+    QW_TRY(launch_fill_u32(tab, 0xFFFFFFFFu, 2 * (int64_t)slots + (int64_t)bins * kSub, s));
     constexpr int wpb = kBlock / 64;
-    const int32_t step = (int32_t)std::max<int64_t>(1, Q / kLabelSample);
-    label_kernel<<<(unsigned)ceil_div(ceil_div(Q, step), wpb), kBlock, 0, s>>>(Q, L, step, bmh, slots, tag, tag + slots);
+    const int32_t step = (int32_t)std::max<int64_t>(1, a.Q / kLabelSample);
+    label_kernel<<<(unsigned)ceil_div(ceil_div(a.Q, step), wpb), kBlock, 0, s>>>(a.Q, a.L, step, a.bmh, slots, tab, tab + slots);
     QW_HIP(hipGetLastError());
-    classify_group_kernel<<<(unsigned)std::min<int64_t>(2048, ceil_div(Q, wpb)), kBlock, 0, s>>>(
-        Q, L, n, bmh, bsize, exact, pred_log, margin, force_max, cmin, cfloor, cmax, ncls, slots, tag, keys,
-        vals, class_count);
+    group_bin_kernel<<<(unsigned)ceil_div(a.Q, kBinBlock), kBlock, 0, s>>>(a, slots, bins, tab, count);
     QW_HIP(hipGetLastError());
+    group_place_kernel<<<(unsigned)ceil_div(bins, kBlock), kBlock, 0, s>>>(a, bins, count);
+    QW_HIP(hipGetLastError());
+    group_scatter_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a, count);
+    QW_HIP(hipGetLastError());
+    if (a.minrun > 1) {
+        group_rest_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a);
+        QW_HIP(hipGetLastError());
+    }
     return QW_OK;
 }
 

@@ -32,15 +32,13 @@ struct RankF {
 //    re-ranked by its FP64 index-order distance (the c-k-ANN output, Section 3).
 // A list or band beyond capacity sends the query to the fallback.
 template <int DT>
-__global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
+__device__ inline void select_query(const SelectArgs &A, const int64_t q, unsigned char *smem)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
     unsigned long long *lst = reinterpret_cast<unsigned long long *>(smem);
     RankF *rk = reinterpret_cast<RankF *>(smem + size_t(A.LC) * 8);
     unsigned long long *s_min = lst;  // the minima (K > 64) are dead before the list fills
     __shared__ unsigned long long s_thr, s_kth;
     __shared__ uint32_t s_cnt, s_nb;
-    const int64_t q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const unsigned long long lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     // the flag, the count and the range offset load together (uniform)
@@ -51,7 +49,8 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
     const unsigned long long coff = A.coff[q];
     const float err = DT == QW_F32 && A.abs_err ? A.abs_err[q] : 0.f;
     if (bad || (room && U > room)) {  // uniform
-        if (tid == 0) A.fb_list[atomicAdd(A.fb_count, 1u)] = (int32_t)q;
+        // (a flag above 1: answered by another kernel)
+        if (tid == 0 && bad <= 1u) A.fb_list[atomicAdd(A.fb_count, 1u)] = (int32_t)q;
         return;
     }
     const int K = A.K;
@@ -213,6 +212,15 @@ __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
         A.out_ids[o] = -1;
         reinterpret_cast<float *>(A.out_dist)[o] = INFINITY;
     }
+}
+
+template <int DT>
+__global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    // (one query per workgroup: looping over several cost a quarter more)
+    if (A.qlist && blockIdx.x >= *A.qcount) return;  // uniform
+    select_query<DT>(A, A.qlist ? A.qlist[blockIdx.x] : (int64_t)blockIdx.x, smem);
 }
 
 // The key list holds LC >= 4K entries (also room for the ceil(K / kBlock) *

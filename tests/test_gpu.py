@@ -622,6 +622,37 @@ def test_group_key_bound(K, n, Q, same):
     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K,probes", [
+    (6000, 32, 1024, 12, 6, 4, 600.0, 10, 0),   # the smallest workload that shares
+    (6000, 100, 1500, 12, 8, 6, 2000.0, 16, 0),  # ragged rows, largest in-kernel K
+    (6000, 64, 1100, 300, 8, 4, 400.0, 10, 0),  # few queries per region: most stay single
+    (6000, 128, 1100, 12, 8, 6, 2000.0, 17, 2),  # keys for all, probing
+    (6000, 48, 1100, 6, 8, 6, 1200.0, 32, 0), (6000, 48, 1100, 6, 8, 6, 1200.0, 33, 0),  # edge of the bounded keys
+    (5000, 16, 1100, 1, 3, 2, 5000.0, 1, 0),    # every point a candidate
+    (9000, 200, 1100, 1, 3, 2, 9000.0, 10, 0),  # more candidates than a group's set
+    (2000, 1040, 1100, 4, 6, 4, 4500.0, 10, 0),  # long rows
+])
+def test_grouped_uint8_queries(n, d, Q, ncl, L, k, w, K, probes):
+    data, q = grouped_workload(n + d, n, d, Q, ncl, 0.08)
+    data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+    p = synth.hash_params(5, L, k, d, w)
+    ix = build(data, p.a, p.b(), w)
+    if probes:
+        ix.set_probing(2, probes)
+        want = ix.query(dev(q), K, lib.make_opts(form=lib.QW_FORM_PLAIN_FP32))
+        ids_o, dist_o = (t.cpu().numpy() for t in want)
+    else:
+        ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    for sched in (lib.QW_SCHED_SUM, lib.QW_SCHED_ACTUAL):
+        for dedup in (1, 2):
+            for graph in (0, 1):
+                ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1, dedup=dedup, sched=sched, graph=graph),
+                                         stats=True)
+                check_topk(ids, dist, ids_o, dist_o, True)
+                if not probes:
+                    assert st["cand_unique"] == int(cnt_o.sum())
+
+
 def test_huge_w_equals_bruteforce():
     """Every point in one bucket per layer: LSH top-K equals exact kNN."""
     rng = np.random.default_rng(61)
