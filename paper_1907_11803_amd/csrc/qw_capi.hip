@@ -492,15 +492,9 @@ qw_status ooc_query(qw_index *ix, int64_t Q, int K, hipStream_t s, int32_t *out_
 // Room for one round of queries; false when the device has none, or when the
 // stream is being captured and the room is not there yet (the per-query
 // kernel, which needs no lists, answers then).
-bool ensure_brute(qw_index *ix, const BrutePlan &p, hipStream_t s)
+bool ensure_round(qw_index *ix, size_t bmin, size_t bkeys, size_t bstate, hipStream_t s)
 {
     Workspace &w = ix->ws;
-    const size_t q = (size_t)p.chunk;
-    const size_t bmin = sizeof(int32_t) * q * (size_t)p.streams;
-    const size_t bkeys = sizeof(unsigned long long) * q * (size_t)p.cap;
-    // per query: bound, count, flag, fallback entry, list offset; then the
-    // fallback queue's length and work counter
-    const size_t bstate = q * (4 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256;
     if (w.bf_min.bytes >= bmin && w.bf_keys.bytes >= bkeys && w.bf_state.bytes >= bstate) return true;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
@@ -514,6 +508,98 @@ bool ensure_brute(qw_index *ix, const BrutePlan &p, hipStream_t s)
     w.bf_keys.release();
     w.bf_state.release();
     return false;
+}
+
+bool ensure_brute(qw_index *ix, const BrutePlan &p, hipStream_t s)
+{
+    const size_t q = (size_t)p.chunk;
+    // state per query: bound, count, flag, fallback entry, list offset; then
+    // the fallback queue's length and work counter
+    return ensure_round(ix, sizeof(int32_t) * q * (size_t)p.streams, sizeof(unsigned long long) * q * (size_t)p.cap,
+                        q * (4 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256, s);
+}
+
+bool ensure_dense(qw_index *ix, const DensePlan &p, hipStream_t s)
+{
+    const size_t q = (size_t)p.chunk;
+    // state per query: list offset; flag, keys, error, room, bound, fallback
+    // entry; then the fallback queue's length and work counter
+    return ensure_round(ix, 0, sizeof(unsigned long long) * q * (size_t)p.cap,
+                        q * (6 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256, s);
+}
+
+// What both brute-force forms leave behind: the select kernel's setup for a
+// round, then the per-query kernel for the queries whose list overflowed.
+qw_status finish_round(qw_index *ix, SelectArgs m, VerifyArgs fb, int64_t Q, hipStream_t s)
+{
+    m.K = fb.K;
+    m.LC = pow2_at_least(std::max(512, 4 * fb.K));
+    m.dtype = ix->dtype;
+    m.dp = ix->dp;
+    m.d = ix->d;
+    QW_TRY(launch_select(m, Q, s));
+    fb.nitems = 0;
+    fb.in_list = m.fb_list;
+    fb.in_count = m.fb_count;
+    fb.counter = m.fb_count + 1;
+    fb.cap_log2 = 1;
+    fb.limit = 1;
+    fb.buf = (uint32_t)pow2_at_least(std::max(64, 2 * (fb.K + verify_per_iter(ix->dp, ix->dtype))));
+    fb.out_ids = m.out_ids;
+    fb.out_dist = m.out_dist;
+    return launch_verify(fb, (int)std::min<int64_t>(Q, 4 * ix->cus), s);
+}
+
+// Brute force over float rows, p.chunk queries a round.
+qw_status brute_dense(qw_index *ix, const DensePlan &p, VerifyArgs fb, int64_t Q, hipStream_t s,
+                      int32_t *out_ids, float *out_dist)
+{
+    Workspace &w = ix->ws;
+    const int64_t c = p.chunk;
+    auto *coff = w.bf_state.as<unsigned long long>();
+    auto *flag = reinterpret_cast<uint32_t *>(coff + c);
+    uint32_t *kpos = flag + c, *room = kpos + 2 * c, *bound = room + c;
+    auto *abs_err = reinterpret_cast<float *>(kpos + c);
+    auto *fb_list = reinterpret_cast<int32_t *>(bound + c);
+    uint32_t *fb_count = reinterpret_cast<uint32_t *>(fb_list) + c;  // length, work counter
+    for (int64_t q0 = 0; q0 < Q; q0 += c) {
+        GroupedArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.Q = std::min<int64_t>(c, Q - q0);
+        a.dtype = ix->dtype;
+        a.dp = ix->dp;
+        a.K = fb.K;
+        a.eps = group_eps(ix->dp);
+        a.data = ix->data.p;
+        a.queries = static_cast<const float *>(w.qrows) + q0 * ix->dp;
+        a.keys = w.bf_keys.as<unsigned long long>();
+        a.flag = flag;
+        a.abs_err = abs_err;
+        a.kpos = kpos;
+        a.kroom = room;
+        a.coff = coff;
+        a.ovf_count = fb_count;
+        QW_TRY(launch_dense(p, a, ix->n, bound, ix->cus, s));
+        SelectArgs m;
+        std::memset(&m, 0, sizeof(m));
+        m.keys = a.keys;
+        m.coff = coff;
+        m.ucount = kpos;
+        m.kcount = kpos;
+        m.kroom = room;
+        m.flag = flag;
+        m.abs_err = abs_err;
+        m.eps = a.eps;
+        m.data = ix->data.p;
+        m.queries = a.queries;
+        m.fb_count = fb_count;
+        m.fb_list = fb_list;
+        m.out_ids = out_ids + q0 * fb.K;
+        m.out_dist = out_dist + q0 * fb.K;
+        fb.queries = a.queries;
+        QW_TRY(finish_round(ix, m, fb, a.Q, s));
+    }
+    return QW_OK;
 }
 
 // Brute force on the matrix cores, p.chunk queries a round; `fb` is the
@@ -552,27 +638,12 @@ qw_status brute_mfma(qw_index *ix, const BrutePlan &p, VerifyArgs fb, int64_t Q,
         m.coff = coff;
         m.ucount = count;
         m.flag = flag;
-        m.K = K;
-        m.LC = pow2_at_least(std::max(512, 4 * K));
-        m.dtype = ix->dtype;
-        m.dp = ix->dp;
-        m.d = ix->d;
         m.fb_count = fb_count;
         m.fb_list = fb_list;
         m.out_ids = out_ids + q0 * K;
         m.out_dist = out_dist + q0 * K;
-        QW_TRY(launch_select(m, a.Q, s));
         fb.queries = a.queries;
-        fb.nitems = 0;
-        fb.in_list = fb_list;
-        fb.in_count = fb_count;
-        fb.counter = fb_count + 1;
-        fb.cap_log2 = 1;
-        fb.limit = 1;
-        fb.buf = (uint32_t)pow2_at_least(std::max(64, 2 * (K + verify_per_iter(ix->dp, ix->dtype))));
-        fb.out_ids = m.out_ids;
-        fb.out_dist = m.out_dist;
-        QW_TRY(launch_verify(fb, (int)std::min<int64_t>(a.Q, 4 * ix->cus), s));
+        QW_TRY(finish_round(ix, m, fb, a.Q, s));
     }
     return QW_OK;
 }
@@ -1506,6 +1577,9 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     BrutePlan bp;
     if (brute_plan(ix->n, ix->dtype, ix->dp, Q, K, &bp) && ensure_brute(ix, bp, s))
         return brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist));
+    DensePlan dp;
+    if (dense_plan(ix->n, ix->dtype, ix->dp, Q, K, ix->lds_max, &dp) && ensure_dense(ix, dp, s))
+        return brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));
     a.nitems = Q;
     a.cap_log2 = 1;
     a.limit = 1;

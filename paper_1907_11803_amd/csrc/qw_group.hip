@@ -542,6 +542,7 @@ struct VerifyGroup {
     uint32_t *pos;             // keys written by this workgroup
     const int32_t *q;
     bool pieces;
+    int64_t row0, stride;      // brute force: the rows' ids instead of `rows`
 };
 // Bytes of a row per step (a 16-byte part per quarter of the lanes), and steps
 // whose loads are in flight together.
@@ -561,7 +562,9 @@ template <int DT> __host__ __device__ inline int verify_ldq(int dp)
 // the waves' first tiles (32 rows each, in the order of the ids' hash) the K-th
 // smallest of a query's minima over disjoint parts of them bounds its K-th
 // key; rows beyond that bound (float rows: beyond its error band) give no key.
-template <int DT, int CB>
+// DENSE (brute force): row r is point row0 + r * stride, everybody's, and the bound
+// is given.
+template <int DT, int CB, bool DENSE>
 __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
 {
     constexpr int NS = verify_steps<DT>();
@@ -598,7 +601,7 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
     };
     static_assert(kVCells<DT> <= 128, "two minima per lane");
     if (wv >= ntile) {  // no tile: its minima are empty
-        if (A.K <= kGFilterK<DT>) {
+        if (!DENSE && A.K <= kGFilterK<DT>) {
             for (int i = lane; i < 16 * CB * 8; i += 64) G.minima[(i >> 3) * kVCells<DT> + wv * 8 + (i & 7)] = kNoKey;
             bounds();
         }
@@ -606,8 +609,10 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
     }
     auto entry = [&](int t, int h) -> uint2 {
         const uint32_t r = (uint32_t)(t * 32 + h * 16 + row16);
+        // rows past the end: nobody's
+        if (DENSE) return uint2{(uint32_t)(G.row0 + (int64_t)(r < U ? r : U - 1u) * G.stride), r < U ? G.keep : 0u};
         const uint2 e = G.rows[r < U ? r : U - 1u];
-        return uint2{e.x, r < U ? e.y & G.keep : 0u};  // rows past the end: nobody's
+        return uint2{e.x, r < U ? e.y & G.keep : 0u};
     };
     uint2 e0 = entry(wv, 0), e1 = entry(wv, 1), n0 = e0, n1 = e1;
     if (wv + kVW<DT> < ntile) {
@@ -745,7 +750,7 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
         if (++c == nch) {
             tile_keys(e0, acc0, xn0, key[0]);
             tile_keys(e1, acc1, xn1, key[1]);
-            if (t == wv && A.K <= kGFilterK<DT>) {  // uniform in the workgroup: every wave's first tile
+            if (!DENSE && t == wv && A.K <= kGFilterK<DT>) {  // uniform in the workgroup: every wave's first tile
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -775,6 +780,59 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
         if (t >= ntile) break;
         step(bb, ba);
         if (t >= ntile) break;
+    }
+}
+
+// q' of the group's queries (zeros in the columns of others) and |q'|^2; float
+// rows: q0 and the keys' error, once (`first`) for the select kernel too.
+template <int DT>
+__device__ inline void stage_queries(const GroupedArgs &A, const int32_t *s_q, uint32_t keep, int j0, bool first,
+                                     unsigned char *qp, float *q0s, uint32_t *s_qn, float *s_err)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int dp = A.dp, ldq = verify_ldq<DT>(dp), cols = (keep >> 16) ? 32 : 16;
+    const unsigned char *queries = static_cast<const unsigned char *>(A.queries);
+    const int64_t rb = (int64_t)dp * (DT == QW_F32 ? 4 : 1);
+    const float *q0 = reinterpret_cast<const float *>(queries + (int64_t)s_q[j0] * rb);
+    if constexpr (DT == QW_F32)
+        for (int i = tid; i < dp; i += kVB<DT>) q0s[i] = q0[i];
+    for (int j = wv; j < cols; j += kVW<DT>) {
+        const bool in = (keep >> j) & 1u;  // uniform
+        const int32_t q = in ? s_q[j] : s_q[j0];
+        if constexpr (DT == QW_F32) {
+            const float *qr = reinterpret_cast<const float *>(queries + (int64_t)q * rb);
+            float *qo = reinterpret_cast<float *>(qp + (size_t)j * ldq);
+            float acc = 0.f;
+            for (int i = lane; i < dp; i += 64) {
+                const float t = in ? qr[i] - q0[i] : 0.f;
+                qo[i] = t;
+                acc = fmaf(t, t, acc);
+            }
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+            // 8c Q^2, inflated past the rounding of |q'|^2; a query beyond
+            // FP32's range (or not a number) is left to the fallback
+            const float err = acc * (16.f * (float)(dp + 16) * 0x1p-24f * 1.01f);
+            if (lane == 0) {
+                s_qn[j] = __float_as_uint(acc);
+                s_err[j] = err;
+                if (in && first) {
+                    A.abs_err[q] = err;
+                    if (!(acc < 1e30f)) A.flag[q] = 1u;
+                }
+            }
+        } else {
+            const v4i *qr = reinterpret_cast<const v4i *>(queries + (int64_t)q * rb);
+            v4i *qo = reinterpret_cast<v4i *>(qp + (size_t)j * ldq);
+            int acc = 0;
+            for (int i = lane; i < (ldq - 16) / 16; i += 64) {
+                const v4i t = in && i < dp / 16 ? signed_part(qr[i]) : v4i{0, 0, 0, 0};
+                qo[i] = t;
+                acc += norm_part(t);
+            }
+            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+            if (lane == 0) s_qn[j] = (uint32_t)acc;
+        }
     }
 }
 
@@ -829,61 +887,132 @@ __global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_ke
             s_thr[tid] = kNoKey;
         }
         __syncthreads();
-        const unsigned char *queries = static_cast<const unsigned char *>(A.queries);
-        const int64_t rb = (int64_t)dp * (DT == QW_F32 ? 4 : 1);
-        const float *q0 = reinterpret_cast<const float *>(queries + (int64_t)s_q[rec.j0] * rb);
-        if constexpr (DT == QW_F32)
-            for (int i = tid; i < dp; i += kVB<DT>) q0s[i] = q0[i];
         const int cols = (keep >> 16) ? 32 : 16;
-        for (int j = wv; j < cols; j += kVW<DT>) {
-            const bool in = (keep >> j) & 1u;  // uniform
-            const int32_t q = in ? s_q[j] : s_q[rec.j0];
-            if constexpr (DT == QW_F32) {
-                const float *qr = reinterpret_cast<const float *>(queries + (int64_t)q * rb);
-                float *qo = reinterpret_cast<float *>(qp + (size_t)j * ldq);
-                float acc = 0.f;
-                for (int i = lane; i < dp; i += 64) {
-                    const float t = in ? qr[i] - q0[i] : 0.f;
-                    qo[i] = t;
-                    acc = fmaf(t, t, acc);
-                }
-                for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-                // 8c Q^2, inflated past the rounding of |q'|^2; a query beyond
-                // FP32's range (or not a number) is left to the fallback
-                const float err = acc * (16.f * (float)(dp + 16) * 0x1p-24f * 1.01f);
-                if (lane == 0) {
-                    s_qn[j] = __float_as_uint(acc);
-                    s_err[j] = err;
-                    if (in && pc == 0u) {
-                        A.abs_err[q] = err;
-                        if (!(acc < 1e30f)) A.flag[q] = 1u;
-                    }
-                }
-            } else {
-                const v4i *qr = reinterpret_cast<const v4i *>(queries + (int64_t)q * rb);
-                v4i *qo = reinterpret_cast<v4i *>(qp + (size_t)j * ldq);
-                int acc = 0;
-                for (int i = lane; i < (ldq - 16) / 16; i += 64) {
-                    const v4i t = in && i < dp / 16 ? signed_part(qr[i]) : v4i{0, 0, 0, 0};
-                    qo[i] = t;
-                    acc += norm_part(t);
-                }
-                for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-                if (lane == 0) s_qn[j] = (uint32_t)acc;
-            }
-            if (lane == 0 && in) {
+        stage_queries<DT>(A, s_q, keep, rec.j0, pc == 0u, qp, q0s, s_qn, s_err);
+        for (int j = tid; j < cols; j += kVB<DT>) {
+            const int32_t q = s_q[j];
+            if ((keep >> j) & 1u) {
                 s_base[j] = A.coff[q];
                 s_room[j] = A.kroom[q];
             }
         }
         __syncthreads();
         VerifyGroup G = {A.glist + rec.rows + r0, r1 - r0, keep, qp, q0s, s_qn, minima, s_thr, s_err,
-                         s_base, s_room, s_pos, s_q, np > 1u};
-        if (cols == 32) verify_rows<DT, 2>(A, G);
-        else verify_rows<DT, 1>(A, G);
+                         s_base, s_room, s_pos, s_q, np > 1u, 0, 0};
+        if (cols == 32) verify_rows<DT, 2, false>(A, G);
+        else verify_rows<DT, 1, false>(A, G);
         __syncthreads();  // every key is counted; q' is read before the next group's
         if (np == 1u && tid < cols && ((keep >> tid) & 1u)) A.kpos[s_q[tid]] = s_pos[tid];
         __syncthreads();  // the group's queries and counts are read before the next one's
+    }
+}
+
+// Empty lists of cap keys; ovf_count: the fallback queue's two words.
+__global__ __launch_bounds__(kBlock) void dense_init_kernel(GroupedArgs A, DenseArgs D)
+{
+    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (q < 2) A.ovf_count[q] = 0u;
+    if (q >= A.Q) return;
+    A.flag[q] = A.kpos[q] = 0u;
+    A.kroom[q] = D.cap;
+    A.coff[q] = (unsigned long long)q * D.cap;
+}
+
+// Brute force over float rows: 32 consecutive queries and a piece of the rows per
+// item, items of the same piece on one XCD (its L2 holds the rows while the
+// queries pass).  Bound by the matrix cores' FP32 rate from 32 queries on, by the
+// rows' bytes below; rows beyond about 1,100 columns (LDS) stay with the
+// per-query kernel, one workgroup per query.
+// Measured (whole calls): 25 queries over 186,000 x 512: 44 ms with a workgroup
+// per query, 0.30 here (the rows once: 0.08 ms at 4.9 TB/s); 120 over 200,000 x
+// 280: 42 and 0.33; one over 64,000 x 418: 14 and 0.10.
+__global__ __launch_bounds__(kVB<QW_F32>, 3) void dense_verify_kernel(GroupedArgs A, DenseArgs D)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int32_t s_q[kGQ];
+    __shared__ uint32_t s_room[kGQ], s_thr[kGQ], s_qn[kGQ];
+    __shared__ unsigned long long s_base[kGQ];
+    __shared__ float s_err[kGQ];
+    const int tid = threadIdx.x;
+    unsigned char *qp = smem;  // q' [kGQ][ldq]
+    float *q0s = reinterpret_cast<float *>(qp + (size_t)kGQ * verify_ldq<QW_F32>(A.dp));
+    const uint32_t ng = (uint32_t)((A.Q + kGQ - 1) / kGQ), items = ng * D.pieces;
+    const uint32_t per = (items + kXcd - 1u) / kXcd;
+    const int64_t tiles = (D.rows + 31) / 32;
+    for (uint32_t i = blockIdx.x; i < per * kXcd; i += gridDim.x) {
+        const uint32_t it = i % kXcd * per + i / kXcd;
+        if (it >= items) continue;  // uniform
+        const uint32_t pc = it / ng, g = it - pc * ng;
+        const int64_t r0 = min(D.rows, tiles * pc / D.pieces * 32), r1 = min(D.rows, tiles * (pc + 1) / D.pieces * 32);
+        const int32_t m = (int32_t)min((int64_t)kGQ, A.Q - (int64_t)g * kGQ);
+        const uint32_t keep = m == 32 ? ~0u : (1u << m) - 1u;
+        if (r1 == r0) continue;  // uniform
+        if (tid < kGQ) {
+            const int32_t q = (int32_t)(g * kGQ) + tid;
+            s_q[tid] = tid < m ? q : -1;
+            s_thr[tid] = tid < m && D.bound ? D.bound[q] : kNoKey;
+            s_room[tid] = D.cap;
+            s_base[tid] = (unsigned long long)q * D.cap;
+        }
+        __syncthreads();
+        stage_queries<QW_F32>(A, s_q, keep, 0, !D.bound && pc == 0u, qp, q0s, s_qn, s_err);
+        __syncthreads();
+        VerifyGroup G = {nullptr, (uint32_t)(r1 - r0), keep, qp, q0s, s_qn, nullptr, s_thr, s_err,
+                         s_base, s_room, nullptr, s_q, true, r0 * D.stride, D.stride};
+        if (m > 16) verify_rows<QW_F32, 2, true>(A, G);
+        else verify_rows<QW_F32, 1, true>(A, G);
+        __syncthreads();  // q' is read before the next item's
+    }
+}
+
+// One workgroup per query: the K-th smallest key of a sample of the rows, widened
+// by the keys' error, bounds the query's K-th key; its key list is empty again.
+// Radix select over the keys' high words in LDS, a byte at a time.
+__global__ __launch_bounds__(kBlock) void dense_bound_kernel(GroupedArgs A, DenseArgs D)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint32_t *v = reinterpret_cast<uint32_t *>(smem);  // [D.rows]
+    __shared__ uint32_t hist[256], s_pick, s_left;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t q = blockIdx.x;
+    const uint32_t n = min(A.kpos[q], (uint32_t)D.rows);
+    const unsigned long long *keys = A.keys + q * D.cap;
+    for (uint32_t i = tid; i < n; i += kBlock) v[i] = (uint32_t)(keys[i] >> 32);
+    uint32_t t = 0, left = (uint32_t)A.K;  // the K-th smallest's bits so far; its rank among their equals
+    if (n >= left)                         // uniform
+        for (int sh = 24; sh >= 0; sh -= 8) {
+            hist[tid] = 0;
+            __syncthreads();
+            for (uint32_t i = tid; i < n; i += kBlock)
+                if (sh == 24 || v[i] >> (sh + 8) == t >> (sh + 8)) atomicAdd(&hist[v[i] >> sh & 255u], 1u);
+            __syncthreads();
+            if (tid < 64) {  // four bins per lane
+                uint32_t h[4], sum = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum += h[i] = hist[4 * lane + i];
+                uint32_t x = sum;
+                for (int off = 1; off < 64; off <<= 1) {
+                    const uint32_t y = (uint32_t)__shfl_up((int)x, off);
+                    if (lane >= off) x += y;
+                }
+                uint32_t before = x - sum;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (before < left && left <= before + h[i]) {
+                        s_pick = (uint32_t)(4 * lane + i);
+                        s_left = left - before;
+                    }
+                    before += h[i];
+                }
+            }
+            __syncthreads();
+            t |= s_pick << sh;
+            left = s_left;
+            __syncthreads();
+        }
+    if (tid == 0) {
+        D.bound[q] = n >= (uint32_t)A.K ? __float_as_uint(band_threshold(__uint_as_float(t), A.eps, A.abs_err[q])) : kNoKey;
+        A.kpos[q] = 0u;
     }
 }
 
@@ -950,6 +1079,53 @@ qw_status launch_grouped(GroupedArgs a, int cus, size_t lds_max, hipStream_t s)
     else group_verify_kernel<QW_U8><<<grid, kVB<QW_U8>, vl, s>>>(a);
     QW_HIP(hipGetLastError());
     return QW_OK;
+}
+
+// Brute force: the sample holds `sample` rows, every list cap keys.  With s rows
+// sampled about K n / s keys pass their bound; s near sqrt(K n) makes both small.
+bool dense_plan(int64_t n, int32_t dtype, int32_t dp, int64_t Q, int32_t K, size_t lds_max, DensePlan *p)
+{
+    if (dtype != QW_F32 || n < 2048 || Q < 1 || dp % 16 != 0 || verify_lds(QW_F32, dp) + 2048 > lds_max) return false;
+    int64_t s = 2048;
+    while (s < kDenseSample && s * s < (int64_t)K * n) s += s / 2 / 32 * 32;
+    s = std::min(s, kDenseSample);
+    p->sample = n <= 2 * s ? n : s;  // few rows: their keys all, without a bound
+    p->cap = (uint32_t)std::max<int64_t>(p->sample, 4 * K * n / s + 1024);
+    if (p->sample == n) p->cap = (uint32_t)n;
+    // queries per round: their lists stay within 256 MiB, whole groups
+    p->chunk = std::min<int64_t>(Q, std::max<int64_t>(kGQ, ((int64_t)256 << 20) / (8 * (int64_t)p->cap) / kGQ * kGQ));
+    return true;
+}
+
+// a.Q <= p.chunk queries.
+qw_status launch_dense(const DensePlan &p, GroupedArgs a, int64_t n, uint32_t *bound, int cus, hipStream_t s)
+{
+    if (a.Q < 1 || a.Q > p.chunk || a.dp % 16 != 0 || p.sample > n || p.sample < 1) return QW_EINTERNAL;
+    const size_t lds = verify_lds(QW_F32, a.dp);
+    const int64_t ng = ceil_div(a.Q, kGQ);
+    auto pass = [&](int64_t rows, int64_t stride, uint32_t *b) -> qw_status {
+        DenseArgs d;
+        d.rows = rows;
+        d.stride = stride;
+        d.bound = b;
+        d.cap = p.cap;
+        // about two pieces per CU in all, a tile for every wave of each
+        const int64_t most = std::max<int64_t>(1, rows / (32 * kVW<QW_F32>));
+        d.pieces = (uint32_t)std::min<int64_t>(most, std::max<int64_t>(1, 2 * cus / ng));
+        const int64_t items = ng * d.pieces;
+        const int grid = (int)std::min<int64_t>(ceil_div(items, kXcd) * kXcd, ceil_div(cus, kXcd) * kXcd);
+        dense_verify_kernel<<<grid, kVB<QW_F32>, lds, s>>>(a, d);
+        QW_HIP(hipGetLastError());
+        return QW_OK;
+    };
+    const DenseArgs d = {p.sample, 0, bound, p.cap, 0};
+    dense_init_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a, d);
+    QW_HIP(hipGetLastError());
+    if (p.sample == n) return pass(n, 1, nullptr);
+    QW_TRY(pass(p.sample, n / p.sample, nullptr));
+    dense_bound_kernel<<<(unsigned)a.Q, kBlock, sizeof(uint32_t) * (size_t)p.sample, s>>>(a, d);
+    QW_HIP(hipGetLastError());
+    return pass(n, 1, bound);
 }
 
 }  // namespace qw

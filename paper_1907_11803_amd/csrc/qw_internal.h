@@ -613,6 +613,20 @@ float group_eps(int dp);         // relative part of the keys' error
 size_t group_rec_bytes(int64_t Q);
 size_t group_list_bytes(int dtype, int64_t Q);
 int group_filter_topk(int dtype);         // K up to which few keys are written
+// Brute force over float rows (qw_group.hip): rounds of `chunk` queries, lists of
+// cap keys, a sample of the rows for a first bound.
+constexpr int64_t kDenseSample = 8192;
+struct DensePlan {
+    int64_t sample, chunk;
+    uint32_t cap;
+};
+struct DenseArgs {
+    int64_t rows, stride;        // row i is point i * stride
+    uint32_t *bound;             // nullable: keys beyond it are not needed
+    uint32_t cap, pieces;
+};
+bool dense_plan(int64_t n, int32_t dtype, int32_t dp, int64_t Q, int32_t K, size_t lds_max, DensePlan *p);
+qw_status launch_dense(const DensePlan &p, GroupedArgs a, int64_t n, uint32_t *bound, int cus, hipStream_t s);
 qw_status launch_grouped(GroupedArgs a, int cus, size_t lds_max, hipStream_t s);
 
 struct SelectArgs {

@@ -533,6 +533,53 @@ def test_bruteforce_matrix_cores(n, d, Q, K):
         check_topk(ids, dist, ids_o, dist_o, True)
 
 
+@pytest.mark.parametrize("n,d,Q,K", [
+    (2048, 16, 1, 1), (4096, 20, 33, 10), (2047, 30, 5, 10),             # every key; not applicable
+    (4097, 17, 16, 10), (5001, 64, 17, 1), (9000, 100, 64, 64),          # sampled
+    (20001, 48, 65, 100), (30011, 32, 3, 1024),                          # long lists
+    (4500, 1100, 40, 10), (3000, 1300, 6, 5),                            # longest rows; beyond them
+    (8200, 24, 9000, 3),                                                 # rounds of queries
+])
+def test_bruteforce_float(n, d, Q, K):
+    data, q = grouped_workload(n + d, n, d, min(Q, 300), 7, 0.05)
+    q = np.tile(q, (-(-Q // len(q)), 1))[:Q]
+    p = synth.hash_params(3, 1, 1, d, 1000.0)
+    ix = build(data, p.a, p.b(), 1000.0)
+    ids_o, dist_o = oracle.bruteforce(data, q[:300], K)
+    reps = -(-Q // len(ids_o))
+    ids_o, dist_o = np.tile(ids_o, (reps, 1))[:Q], np.tile(dist_o, (reps, 1))[:Q]
+    for _ in range(2):
+        ids, dist = ix.bruteforce(dev(q), K)
+        check_topk(ids, dist, ids_o, dist_o, False)
+
+
+@pytest.mark.parametrize("kind", ["equal", "sorted", "large", "unhashed"])
+def test_bruteforce_float_key_lists(kind):
+    # equal rows overflow every key list (the per-query kernel answers); near rows
+    # in one place, where the sample may miss them; magnitudes near FP32's end
+    data, q = grouped_workload(8, 30000, 40, 50, 3, 0.05)
+    if kind == "equal":
+        data[:] = data[0]
+        q[::2] = data[0]
+    elif kind == "sorted":
+        q[:] = 0.5
+        data[5001:5013] = 0.51
+    p = synth.hash_params(3, 1, 1, 40, 1000.0)
+    if kind == "large":  # hash values out of range: refused
+        for a in (p.a, p.a * (np.arange(40) < 39)):
+            data[::1000, -1] = 1e18
+            with pytest.raises(lib.QwError):
+                build(data, np.ascontiguousarray(a, np.float32), p.b(), 1000.0)
+        return
+    if kind == "unhashed":  # queries large in a column that no hash function reads
+        p.a[:, :, -1] = 0
+        q[7, -1], q[8, -1] = 1e18, 1e16
+    ix = build(data, p.a, p.b(), 1000.0)
+    ids_o, dist_o = oracle.bruteforce(data, q, 10)
+    ids, dist = ix.bruteforce(dev(q), 10)
+    check_topk(ids, dist, ids_o, dist_o, False)
+
+
 @pytest.mark.parametrize("kind", ["equal", "extreme", "sorted"])
 def test_bruteforce_matrix_cores_key_lists(kind):
     # equal rows overflow every key list (the per-query kernel answers); rows
