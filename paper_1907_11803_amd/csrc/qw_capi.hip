@@ -1288,7 +1288,7 @@ qw_status qw_get_index_info(const qw_index *ix, qw_index_info *info)
                                 &o.moff, &o.mnoff, &o.mneed, &o.owner, &o.freel, &o.dir,
                                 &o.rstamp, &o.rneed, &o.missd, &o.copyl, &o.ckeys,
                                 &o.ckeys2, &o.cvals, &o.cvals2, &o.csz, &o.cscan, &o.sort_hist,
-                                &o.scan_tmp, &o.bstart2, &o.ctr})
+                                &o.scan_tmp, &o.bstart2, &o.ctr, &o.digits})
             info->device_bytes += (int64_t)b->bytes;
     }
     return QW_OK;

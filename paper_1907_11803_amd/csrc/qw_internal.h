@@ -194,7 +194,7 @@ struct OocState {
     DevBuf rows, owner;       // C_D: cap_rows rows and the id held by each slot (-1 free)
     DevBuf dir, rstamp, rneed, rmiss;  // per point: slot (-1), last use, batch tags
     DevBuf missd, ckeys, cvals, ckeys2, cvals2, csz, cscan, sort_hist, scan_tmp, copyl, freel,
-        bstart2, ctr;
+        bstart2, ctr, digits;
     int64_t cand_cap = 0;     // entries of the candidate lists
     uint32_t tag = 0;         // batch attempt counter (tags are never reused)
     int64_t rows_used = 0;    // resident rows (host mirror)
@@ -276,7 +276,7 @@ struct qw_index {
     // side stream (default priority) and fork/join events: the larger size
     // classes run beside the merged launch
     hipStream_t side = nullptr;
-    hipEvent_t fork[2] = {};
+    hipEvent_t fork[3] = {};
     // tuning cache: the file last named by a call, read once, and the
     // device's architecture name
     std::string tune_path, tune_arch;

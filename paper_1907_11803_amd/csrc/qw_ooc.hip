@@ -22,10 +22,15 @@
 //     fit; read the missing rows from host memory into free slots;
 //  3. the plain form's per-query kernel (union, verification, top-K) reads
 //     the lists from the arena and the rows through the slot directory.
+// The reads of a batch's rows and its step 3 run on the side stream while the
+// next batch is planned: the next batch touches what they read -- an arena, the
+// directory, the slots -- after they have finished only.  (10,000 queries over
+// 1M x 128 in batches of 1,000, a 64 MB cache: 55 ms one after the other, 40 so;
+// the link takes 25 of them, the verification 6.)
 // Recency: query q's layer-l bucket is used at q * L + l + 1, a row of C(q) at
 // q + 1, q counting the queries answered since the caches were last emptied
-// (across calls when they persist); an item's stamp is its largest use.  The host reads a few counters
-// back after each marking step (misses, resident totals, candidates) to decide
+// (across calls when they persist); an item's stamp is its largest use.  The
+// host reads a few counters back after each marking step (misses, resident totals, candidates) to decide
 // whether the batch fits; a batch that does not fit is answered as two halves
 // (the index phase of a batch whose rows did not fit stays done).
 #include <hip/hip_runtime.h>
@@ -55,6 +60,7 @@ enum {
     O_ICAND,                     // bucket eviction candidates
     O_COPY,                      // buckets placed in the new arena
     O_RMISS,                     // missing rows
+    O_RHIT,                      // rows that this batch needs and that are resident
     O_RCAND,                     // row eviction candidates
     O_FREE,                      // free row slots
     O_WORDS
@@ -94,7 +100,7 @@ __device__ inline int64_t map_slot(unsigned long long *key, unsigned long long m
 // The scans below give each block one contiguous range of the items, so a
 // block reserves the places of all its items with one atomic (one per wave
 // would serialise thousands of atomics on one address).
-constexpr int kScanGrid = 256;
+constexpr int kScanGrid = 512;
 
 __device__ inline void block_range(int64_t N, int64_t *lo, int64_t *hi)
 {
@@ -394,8 +400,14 @@ __global__ __launch_bounds__(kOocBlock) void miss_rows_kernel(const uint32_t *__
                                                               int64_t n, uint32_t tag,
                                                               int32_t *missd, unsigned long long *ctr)
 {
+    __shared__ unsigned long long red[kOocBlock / 64];
     int64_t lo, hi;
     block_range(n, &lo, &hi);
+    unsigned long long hits = 0;
+    for (int64_t id = lo + threadIdx.x; id < hi; id += kOocBlock)
+        hits += rneed[id] == tag && dir[id] >= 0 ? 1ull : 0ull;
+    hits = block_sum(hits, red);
+    if (threadIdx.x == 0 && hits) atomicAdd(&ctr[O_RHIT], hits);
     block_compact(
         lo, hi, &ctr[O_RMISS], [&](int64_t id) { return rneed[id] == tag && dir[id] < 0; },
         [&](unsigned long long o, int64_t id) { missd[o] = (int32_t)id; });
@@ -424,14 +436,88 @@ __global__ __launch_bounds__(kOocBlock) void row_cands_kernel(
     });
 }
 
-__global__ void evict_rows_kernel(const int32_t *__restrict__ cvals, int64_t count,
-                                  int32_t *owner, int32_t *dir)
+// The `deficit` smallest of the candidate keys (all different), found digit by
+// digit from the top: launch p counts the p-th digits of the keys that agree
+// with the prefix so far, which it first extends by the digit that launch p - 1's
+// counts give (every workgroup by itself; workgroup 0 keeps it for the next).
+// (Sorting them took 25 launches, 250 us for 230,000 rows; this takes P + 2.)
+constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits, kDigitPasses = 6;
+static_assert(kDigitBits * kDigitPasses >= 64, "any key");
+struct DigitState {
+    unsigned long long prefix;  // the digits found
+    unsigned long long rank;    // of the key sought among those with that prefix, from 1
+};
+
+// The state after p digits; whole workgroup (barriers inside).
+__device__ inline DigitState digit_state(int p, int bits, unsigned long long deficit, const uint32_t *hist,
+                                         DigitState *state)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const int32_t slot = cvals[i];
-    dir[owner[slot]] = -1;
-    owner[slot] = -1;
+    __shared__ DigitState out;
+    __shared__ unsigned long long wsum[kOocBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (p == 0) return DigitState{0ull, deficit};
+    const DigitState in = p == 1 ? DigitState{0ull, deficit} : state[p - 2];
+    const int width = min(kDigitBits, bits - (p - 1) * kDigitBits);
+    constexpr int per = kDigits / kOocBlock;
+    uint32_t h[per];
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) sum += h[i] = hist[(size_t)(p - 1) * kDigits + tid * per + i];
+    unsigned long long x = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long y = (unsigned long long)__shfl_up((long long)x, off);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) wsum[wv] = x;
+    if (tid == 0) out = in;
+    __syncthreads();
+    unsigned long long before = x - sum;
+    for (int w = 0; w < wv; ++w) before += wsum[w];
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        if (before < in.rank && in.rank <= before + h[i])
+            out = DigitState{(in.prefix << width) | (unsigned)(tid * per + i), in.rank - before};
+        before += h[i];
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) state[p - 1] = out;
+    return out;
+}
+
+__global__ __launch_bounds__(kOocBlock) void digit_kernel(const unsigned long long *__restrict__ ckeys,
+                                                          const unsigned long long *__restrict__ ctr, int p,
+                                                          int bits, unsigned long long deficit, uint32_t *hist,
+                                                          DigitState *state)
+{
+    __shared__ uint32_t cnt[kDigits];
+    for (int i = threadIdx.x; i < kDigits; i += kOocBlock) cnt[i] = 0;
+    const DigitState st = digit_state(p, bits, deficit, hist, state);
+    __syncthreads();
+    const int done = p * kDigitBits, width = min(kDigitBits, bits - done);
+    const int64_t count = (int64_t)ctr[O_RCAND], stride = (int64_t)gridDim.x * kOocBlock;
+    for (int64_t i = (int64_t)blockIdx.x * kOocBlock + threadIdx.x; i < count; i += stride) {
+        const unsigned long long k = ckeys[i];
+        if (done == 0 || k >> (bits - done) == st.prefix)
+            atomicAdd(&cnt[(k >> (bits - done - width)) & ((1u << width) - 1u)], 1u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kDigits; i += kOocBlock)
+        if (cnt[i]) atomicAdd(&hist[(size_t)p * kDigits + i], cnt[i]);
+}
+
+__global__ __launch_bounds__(kOocBlock) void evict_rows_kernel(
+    const unsigned long long *__restrict__ ckeys, const int32_t *__restrict__ cvals,
+    const unsigned long long *__restrict__ ctr, int passes, int bits, unsigned long long deficit,
+    const uint32_t *hist, DigitState *state, int32_t *owner, int32_t *dir)
+{
+    const DigitState st = digit_state(passes, bits, deficit, hist, state);
+    const int64_t count = (int64_t)ctr[O_RCAND], stride = (int64_t)gridDim.x * kOocBlock;
+    for (int64_t i = (int64_t)blockIdx.x * kOocBlock + threadIdx.x; i < count; i += stride)
+        if (ckeys[i] <= st.prefix) {
+            const int32_t slot = cvals[i];
+            dir[owner[slot]] = -1;
+            owner[slot] = -1;
+        }
 }
 
 __global__ __launch_bounds__(kOocBlock) void free_rows_kernel(const int32_t *__restrict__ owner,
@@ -445,36 +531,61 @@ __global__ __launch_bounds__(kOocBlock) void free_rows_kernel(const int32_t *__r
         [&](unsigned long long o, int64_t slot) { freel[o] = (int32_t)slot; });
 }
 
-// Data phase, reads: from the host copy into free slots (the data IO).  A
-// wave takes 64 / parts rows at once when rows are short (so every lane
-// moves 16 bytes), else one row in 64-lane strides.
-__global__ __launch_bounds__(kOocBlock) void fill_rows_kernel(
+// Data phase, assignment: the missing rows take free slots.
+__global__ __launch_bounds__(kOocBlock) void assign_rows_kernel(
     const int32_t *__restrict__ missd, const int32_t *__restrict__ freel,
-    const unsigned long long *__restrict__ ctr, int64_t parts, const uint4 *__restrict__ host_rows,
-    uint4 *__restrict__ rows, int32_t *owner, int32_t *dir, int64_t cap_rows)
+    const unsigned long long *__restrict__ ctr, int32_t *owner, int32_t *dir)
 {
     // the eviction leaves at least as many free slots as misses
     const int64_t count = (int64_t)min(ctr[O_RMISS], ctr[O_FREE]);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < count; e += stride) {
+        const int32_t id = missd[e], slot = freel[e];
+        owner[slot] = id;
+        dir[id] = slot;
+    }
+}
+
+// Data phase, reads: from the host copy into the slots (the data IO).  A wave
+// takes 64 / parts rows at once when rows are short (so every lane moves 16
+// bytes), else one row in 64-lane strides, kFillAhead of them in flight.
+// Bound by the link (48 GB/s of its 57): 1 MB in flight, from few CUs.  What else
+// crosses the link meanwhile -- the next batch's launches, its counters read back
+// -- waits behind the reads in flight (256 workgroups of 256 threads: a counter took
+// 450 us), and the other work on these CUs waits behind theirs.  10,000 queries,
+// whole calls: 256 workgroups 48.5 ms, 64 42.3, 32 41.0, 16 52; 16 of 1024
+// threads 40.2.
+constexpr int kFillAhead = 4, kFillBlock = 1024, kFillGrid = 16;
+__global__ __launch_bounds__(kFillBlock) void fill_rows_kernel(
+    const int32_t *__restrict__ missd, const int32_t *__restrict__ freel, int64_t count, int64_t parts,
+    const uint4 *__restrict__ host_rows, uint4 *__restrict__ rows, int64_t cap_rows)
+{
     const int lane = threadIdx.x & 63;
     // rows per wave: a power of two with rpw * parts <= 64 (1 for long rows)
     int rpw = 1;
     while (rpw * 2 * parts <= 64) rpw *= 2;
     const int lpr = 64 / rpw;  // lanes per row
     const int r = lane / lpr, j0 = lane % lpr;
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x / 64);
-    for (int64_t e0 = ((int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * rpw;
-         e0 < count; e0 += nw * rpw) {
-        const int64_t e = e0 + r;
-        if (e >= count) continue;
-        const int32_t id = missd[e];
-        const int32_t slot = freel[e];
-        if (slot < 0 || slot >= cap_rows) continue;
-        const uint4 *src = host_rows + (int64_t)id * parts;
-        uint4 *dst = rows + (int64_t)slot * parts;
-        for (int64_t j = j0; j < parts; j += lpr) dst[j] = src[j];
-        if (j0 == 0) {
-            owner[slot] = id;
-            dir[id] = slot;
+    const int64_t step = (int64_t)gridDim.x * (blockDim.x / 64) * rpw;
+    for (int64_t e0 = ((int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6)) * rpw + r; e0 < count;
+         e0 += step * kFillAhead) {
+        int64_t src[kFillAhead], dst[kFillAhead];
+#pragma unroll
+        for (int i = 0; i < kFillAhead; ++i) {
+            const int64_t e = e0 + i * step;
+            const int32_t slot = e < count ? freel[e] : -1;
+            const bool ok = slot >= 0 && slot < cap_rows;
+            src[i] = ok ? (int64_t)missd[e] * parts : 0;
+            dst[i] = ok ? (int64_t)slot * parts : -1;
+        }
+        for (int64_t j = j0; j < parts; j += lpr) {
+            uint4 v[kFillAhead];
+#pragma unroll
+            for (int i = 0; i < kFillAhead; ++i)
+                if (dst[i] >= 0) v[i] = host_rows[src[i] + j];
+#pragma unroll
+            for (int i = 0; i < kFillAhead; ++i)
+                if (dst[i] >= 0) rows[dst[i] + j] = v[i];
         }
     }
 }
@@ -537,9 +648,20 @@ qw_status sort_cands(qw_index *ix, int64_t count, int bits, bool *alt, hipStream
                             st.sort_hist, s, alt);
 }
 
-// One batch [q0, q0 + nq): the index phase, then the data phase.
-qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *io,
-                    BatchResult *res)
+// A batch whose rows are read and whose queries are verified on the side stream
+// while the next one is planned.  It reads its half of missd, freel and bstart2
+// (batches take them in turn) and one arena; its end is event fork[1 + half].
+struct OocFlight {
+    bool any = false;
+    int arena = 0;
+};
+
+// One batch [q0, q0 + nq): the index phase, then the data phase up to the reads
+// of its *miss missing rows, planned on s while the batch of the other half is in
+// flight.  What a flight reads -- its half, its arena, the slot directory, the
+// rows -- changes after it only.
+qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *io, const OocFlight (&fl)[2],
+                    int buf, int64_t *miss, BatchResult *res)
 {
     OocState &st = *ix->ooc;
     const int32_t L = ix->L;
@@ -553,6 +675,13 @@ qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *
     auto *moff = st.moff.as<long long>();
     std::vector<unsigned long long> h;
     const uint32_t tag = ++st.tag;
+    int32_t *missd = st.missd.as<int32_t>() + (buf ? n : 0);
+    int32_t *freel = st.freel.as<int32_t>() + (buf ? st.cap_rows : 0);
+    auto after_flight = [&](int half) -> qw_status {
+        if (fl[half].any) QW_HIP(hipStreamWaitEvent(s, ix->fork[1 + half], 0));
+        return QW_OK;
+    };
+    QW_TRY(after_flight(buf));  // this half's last
     *res = B_OK;
 
     // ---- index phase
@@ -612,6 +741,7 @@ qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *
     if (imiss > 0) {
         int32_t *old_arena = st.arena[st.cur].as<int32_t>();
         int32_t *new_arena = st.arena[st.cur ^ 1].as<int32_t>();
+        if (fl[buf ^ 1].any && fl[buf ^ 1].arena == (st.cur ^ 1)) QW_TRY(after_flight(buf ^ 1));
         place_index_kernel<<<kScanGrid, kOocBlock, 0, s>>>(
             mkey, st.mcap, n, st.o.strategy, tag, st.cap_pool, st.msize.as<uint32_t>(), moff,
             st.mneed.as<uint32_t>(), st.mnoff.as<long long>(), st.copyl.as<int32_t>(), ctr);
@@ -628,7 +758,7 @@ qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *
     }
     io->index_files += imiss;
     io->index_bytes += 4 * (int64_t)miss_ids;
-    uint32_t *bs2 = st.bstart2.as<uint32_t>();
+    uint32_t *bs2 = st.bstart2.as<uint32_t>() + (buf ? st.bstart2.bytes / (2 * sizeof(uint32_t)) : 0);
     uint32_t *bz2 = bs2 + nql;  // resolved sizes
     const int64_t uq0 = st.qbase + q0;  // recency of this batch's first query
     commit_index_kernel<<<grid_exact(nql), kOocBlock, 0, s>>>(
@@ -642,7 +772,7 @@ qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *
         bs2, bz2, nql, arena, tag, st.rneed.as<uint32_t>());
     QW_HIP(hipGetLastError());
     miss_rows_kernel<<<kScanGrid, kOocBlock, 0, s>>>(
-        st.rneed.as<uint32_t>(), st.dir.as<int32_t>(), n, tag, st.missd.as<int32_t>(), ctr);
+        st.rneed.as<uint32_t>(), st.dir.as<int32_t>(), n, tag, missd, ctr);
     QW_HIP(hipGetLastError());
     QW_TRY(read_ctr(st, h, s));
     const int64_t rmiss = (int64_t)h[O_RMISS];
@@ -650,35 +780,41 @@ qw_status run_batch(qw_index *ix, int64_t q0, int64_t nq, hipStream_t s, OocIo *
     if (deficit > 0) {
         const int idbits = bit_width((unsigned long long)(n - 1));
         const int kbits = idbits + bit_width((unsigned long long)qnow);
+        // the candidates: resident rows that this batch does not need
+        if (st.rows_used - (int64_t)h[O_RHIT] < deficit) {
+            *res = B_DATA_FULL;  // the index phase stays done
+            return QW_OK;
+        }
         row_cands_kernel<<<kScanGrid, kOocBlock, 0, s>>>(
             st.owner.as<int32_t>(), st.cap_rows, st.rneed.as<uint32_t>(),
             st.rstamp.as<uint32_t>(), tag, st.o.policy, idbits, kbits,
             st.ckeys.as<unsigned long long>(), st.cvals.as<int32_t>(), ctr);
         QW_HIP(hipGetLastError());
-        QW_TRY(read_ctr(st, h, s));
-        const int64_t count = (int64_t)h[O_RCAND];
-        if (count < deficit) {
-            *res = B_DATA_FULL;  // the index phase stays done
-            return QW_OK;
+        auto *state = st.digits.as<DigitState>();
+        uint32_t *hist = reinterpret_cast<uint32_t *>(state + kDigitPasses);
+        const int passes = (kbits + kDigitBits - 1) / kDigitBits;
+        if (passes > kDigitPasses) return QW_EINTERNAL;
+        QW_TRY(launch_fill_u32(hist, 0u, (int64_t)passes * kDigits, s));
+        const unsigned grid = (unsigned)std::min<int64_t>(grid_exact(st.cap_rows), 2 * ix->cus);
+        for (int p = 0; p < passes; ++p) {
+            digit_kernel<<<grid, kOocBlock, 0, s>>>(st.ckeys.as<unsigned long long>(), ctr, p, kbits,
+                                                    (unsigned long long)deficit, hist, state);
+            QW_HIP(hipGetLastError());
         }
-        bool alt = false;
-        QW_TRY(sort_cands(ix, count, kbits, &alt, s));
-        const int32_t *vals = alt ? st.cvals2.as<int32_t>() : st.cvals.as<int32_t>();
-        evict_rows_kernel<<<grid_exact(deficit), kOocBlock, 0, s>>>(vals, deficit,
-                                                                    st.owner.as<int32_t>(),
-                                                                    st.dir.as<int32_t>());
+        QW_TRY(after_flight(buf ^ 1));
+        evict_rows_kernel<<<grid, kOocBlock, 0, s>>>(
+            st.ckeys.as<unsigned long long>(), st.cvals.as<int32_t>(), ctr, passes, kbits,
+            (unsigned long long)deficit, hist, state, st.owner.as<int32_t>(), st.dir.as<int32_t>());
         QW_HIP(hipGetLastError());
     }
-    if (rmiss > 0) {
-        free_rows_kernel<<<kScanGrid, kOocBlock, 0, s>>>(
-            st.owner.as<int32_t>(), st.cap_rows, st.freel.as<int32_t>(), ctr);
+    if (rmiss > 0) {  // (free slots and absent rows are nobody's in flight)
+        free_rows_kernel<<<kScanGrid, kOocBlock, 0, s>>>(st.owner.as<int32_t>(), st.cap_rows, freel, ctr);
         QW_HIP(hipGetLastError());
-        fill_rows_kernel<<<kOocGrid, kOocBlock, 0, s>>>(
-            st.missd.as<int32_t>(), st.freel.as<int32_t>(), ctr, st.row_bytes / 16,
-            static_cast<const uint4 *>(st.dev_rows), st.rows.as<uint4>(), st.owner.as<int32_t>(),
-            st.dir.as<int32_t>(), st.cap_rows);
+        assign_rows_kernel<<<grid_for(rmiss, kOocBlock), kOocBlock, 0, s>>>(
+            missd, freel, ctr, st.owner.as<int32_t>(), st.dir.as<int32_t>());
         QW_HIP(hipGetLastError());
     }
+    *miss = rmiss;
     st.rows_used += rmiss - std::max<int64_t>(deficit, 0);
     io->data_objects += rmiss;
     io->data_bytes += rmiss * st.row_bytes;
@@ -755,12 +891,12 @@ qw_status ooc_enable(qw_index *ix, const qw_ooc_opts &o, hipStream_t s)
         QW_TRY(st->mneed.ensure(4 * mcap));
         QW_TRY(st->rows.ensure((size_t)row_bytes * std::max<int64_t>(cap_rows, 1)));
         QW_TRY(st->owner.ensure(4 * std::max<int64_t>(cap_rows, 1)));
-        QW_TRY(st->freel.ensure(4 * std::max<int64_t>(cap_rows, 1)));
+        QW_TRY(st->freel.ensure(2 * 4 * std::max<int64_t>(cap_rows, 1)));
         QW_TRY(st->dir.ensure(4 * n));
         QW_TRY(st->rstamp.ensure(4 * n));
         QW_TRY(st->rneed.ensure(4 * n));
-        QW_TRY(st->missd.ensure(4 * n));
-                QW_TRY(st->copyl.ensure(4 * mcap));
+        QW_TRY(st->missd.ensure(2 * 4 * n));
+        QW_TRY(st->copyl.ensure(4 * mcap));
         QW_TRY(st->ckeys.ensure(8 * cc));
         QW_TRY(st->ckeys2.ensure(8 * cc));
         QW_TRY(st->cvals.ensure(4 * cc));
@@ -770,6 +906,7 @@ qw_status ooc_enable(qw_index *ix, const qw_ooc_opts &o, hipStream_t s)
         QW_TRY(st->sort_hist.ensure(radix_sort_scratch_bytes(cc)));
         QW_TRY(st->scan_tmp.ensure(scan_scratch_bytes(cc)));
         QW_TRY(st->ctr.ensure(sizeof(unsigned long long) * O_WORDS));
+        QW_TRY(st->digits.ensure(kDigitPasses * (sizeof(DigitState) + sizeof(uint32_t) * kDigits)));
         if (ix->ooc) {  // already out of core: keep the host copies
             std::swap(st->host_ids, ix->ooc->host_ids);
             std::swap(st->host_rows, ix->ooc->host_rows);
@@ -826,7 +963,7 @@ qw_status ooc_disable(qw_index *ix, hipStream_t s)
                       &st.moff, &st.mnoff, &st.mneed, &st.owner, &st.freel, &st.dir, &st.rstamp,
                       &st.rneed, &st.missd, &st.copyl, &st.ckeys, &st.ckeys2,
                       &st.cvals, &st.cvals2, &st.csz, &st.cscan, &st.sort_hist, &st.scan_tmp,
-                      &st.bstart2})
+                      &st.bstart2, &st.digits})
         b->release();
     QW_TRY(ix->ids.ensure(ib));
     QW_TRY(ix->data.ensure(row_data_bytes(ix)));
@@ -843,45 +980,76 @@ qw_status ooc_answer(qw_index *ix, int64_t Q, const VerifyArgs &tmpl, const void
     OocState &st = *ix->ooc;
     const int32_t L = ix->L;
     const int64_t B = std::min<int64_t>(std::max<int32_t>(st.o.batch, 1), Q);
-    QW_TRY(st.bstart2.ensure(2 * sizeof(uint32_t) * (size_t)B * L));  // starts, then sizes
+    // starts, then sizes; two batches' (a multiple of 512 bytes: whole halves)
+    QW_TRY(st.bstart2.ensure((4 * sizeof(uint32_t) * (size_t)B * L + 511) & ~size_t(511)));
     if (!st.o.keep) QW_TRY(ooc_reset(ix, s));
     const int elem = ix->dtype == QW_U8 ? 1 : 4;
     const int64_t qrow_bytes = (int64_t)ix->dp * elem;
+    OocFlight fl[2];
+    int buf = 0;
+    auto batch = [&](int64_t lo, int64_t nq, BatchResult *res) -> qw_status {
+        int64_t rmiss = 0;
+        QW_TRY(run_batch(ix, lo, nq, s, io, fl, buf, &rmiss, res));
+        if (*res != B_OK) return QW_OK;
+        QW_HIP(hipEventRecord(ix->fork[0], s));
+        QW_HIP(hipStreamWaitEvent(ix->side, ix->fork[0], 0));
+        if (rmiss > 0) {
+            fill_rows_kernel<<<kFillGrid, kFillBlock, 0, ix->side>>>(
+                st.missd.as<int32_t>() + (buf ? ix->n : 0), st.freel.as<int32_t>() + (buf ? st.cap_rows : 0),
+                rmiss, st.row_bytes / 16, static_cast<const uint4 *>(st.dev_rows), st.rows.as<uint4>(),
+                st.cap_rows);
+            QW_HIP(hipGetLastError());
+        }
+        VerifyArgs a = tmpl;
+        a.bstart = st.bstart2.as<uint32_t>() + (buf ? st.bstart2.bytes / (2 * sizeof(uint32_t)) : 0);
+        a.bsize = a.bstart + nq * L;
+        a.ids = st.arena[st.cur].as<int32_t>();
+        a.n = 0;  // list offsets are arena offsets (no layer stride)
+        a.data = st.rows.p;
+        a.row_slot = st.dir.as<int32_t>();
+        a.queries = static_cast<const unsigned char *>(qrows) + lo * qrow_bytes;
+        a.out_ids = out_ids + lo * tmpl.K;
+        a.out_dist = static_cast<char *>(out_dist) + lo * tmpl.K * 4;
+        a.nitems = nq;
+        a.counter = nullptr;
+        a.ucount_out = tmpl.ucount_out ? tmpl.ucount_out + lo : nullptr;
+        QW_TRY(launch_verify(a, (int)nq, ix->side));
+        QW_HIP(hipEventRecord(ix->fork[1 + buf], ix->side));
+        fl[buf].any = true;
+        fl[buf].arena = st.cur;
+        buf ^= 1;
+        ++io->batches;
+        return QW_OK;
+    };
     std::vector<std::pair<int64_t, int64_t>> stack;
-    for (int64_t b0 = 0; b0 < Q; b0 += B) {
-        stack.clear();
-        stack.emplace_back(b0, std::min(Q, b0 + B));
-        while (!stack.empty()) {
-            const auto r = stack.back();
-            stack.pop_back();
-            const int64_t lo = r.first, nq = r.second - r.first;
-            BatchResult res;
-            QW_TRY(run_batch(ix, lo, nq, s, io, &res));
-            if (res != B_OK) {
+    auto batches = [&]() -> qw_status {
+        for (int64_t b0 = 0; b0 < Q; b0 += B) {
+            stack.clear();
+            stack.emplace_back(b0, std::min(Q, b0 + B));
+            while (!stack.empty()) {
+                const auto r = stack.back();
+                stack.pop_back();
+                const int64_t lo = r.first, nq = r.second - r.first;
+                BatchResult res;
+                QW_TRY(batch(lo, nq, &res));
+                if (res == B_OK) continue;
                 if (nq == 1) return QW_EUNSUPPORTED;
                 ++io->splits;
                 const int64_t mid = lo + (nq + 1) / 2;
                 stack.emplace_back(mid, r.second);
                 stack.emplace_back(lo, mid);
-                continue;
             }
-            VerifyArgs a = tmpl;
-            a.bstart = st.bstart2.as<uint32_t>();
-            a.bsize = st.bstart2.as<uint32_t>() + nq * L;
-            a.ids = st.arena[st.cur].as<int32_t>();
-            a.n = 0;  // list offsets are arena offsets (no layer stride)
-            a.data = st.rows.p;
-            a.row_slot = st.dir.as<int32_t>();
-            a.queries = static_cast<const unsigned char *>(qrows) + lo * qrow_bytes;
-            a.out_ids = out_ids + lo * tmpl.K;
-            a.out_dist = static_cast<char *>(out_dist) + lo * tmpl.K * 4;
-            a.nitems = nq;
-            a.counter = nullptr;
-            a.ucount_out = tmpl.ucount_out ? tmpl.ucount_out + lo : nullptr;
-            QW_TRY(launch_verify(a, (int)nq, s));
-            ++io->batches;
         }
+        return QW_OK;
+    };
+    const qw_status rc = batches();
+    // whatever happened, the caller's stream continues after the side stream
+    if (rc != QW_OK) (void)hipStreamSynchronize(ix->side);
+    if (fl[buf ^ 1].any && hipStreamWaitEvent(s, ix->fork[1 + (buf ^ 1)], 0) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipStreamSynchronize(ix->side);
     }
+    QW_TRY(rc);
     st.qbase += Q;  // with persistent caches, the next call's queries come later
     return QW_OK;
 }

@@ -331,3 +331,27 @@ def test_autotune_picks_the_fastest_share(u8case):
         check_topk(ids, dist, c.ids, c.dist, True)
     finally:
         ix.close()
+
+
+@pytest.mark.parametrize("batch,cache_mb", [(64, 256), (64, 24), (200, 16), (200, 12)])
+def test_reads_in_flight(batch, cache_mb):
+    """Batches of several MB of rows, whose reads outlast the next batches'
+    planning: without evictions, with some, and with splits."""
+    rng = np.random.default_rng(batch + cache_mb)
+    n, d, Q = 60000, 512, 1000
+    centres = rng.integers(40, 216, (60, d))
+    data = np.clip(centres[rng.integers(0, 60, n)] + rng.normal(0, 20, (n, d)), 0, 255).astype(np.uint8)
+    q = np.clip(centres[rng.integers(0, 60, Q)] + rng.normal(0, 20, (Q, d)), 0, 255).astype(np.uint8)
+    p = synth.hash_params(3, 8, 6, d, 2500.0)
+    ids_o, dist_o, _ = oracle.lsh_query(data, q, p.a, p.b(), 2500.0, 10)
+    ix = lib.Index(dev(data), dev(p.a), dev(p.b()), 2500.0)
+    ix.set_out_of_core(cache_mb << 20, index_percent=30, strategy=2, batch=batch)
+    if cache_mb == 12:  # one query's 16,000 rows do not fit
+        with pytest.raises(lib.QwError):
+            ix.query(dev(q), 10)
+        ix.set_out_of_core(24 << 20, index_percent=30, strategy=2, batch=batch)
+    for _ in range(2):
+        ids, dist, st = ix.query(dev(q), 10, stats=True)
+        check_topk(ids, dist, ids_o, dist_o, True)
+    assert st["ooc_data_bytes"] > 20 << 20
+    ix.close()
