@@ -36,6 +36,11 @@ constexpr int kHistBins = kMaxL + 2;
 // where their sets leave room (measured on 10K queries of 4,784 listed ids
 // each, two workgroups per CU: 256 threads 1.05 ms, 512 0.72 ms, 1024 0.61 ms).
 constexpr int kCountBlockSmall = 512, kCountBlockLarge = 1024;
+// Bound by vector instructions (issued 80 % of the time, half of them in the
+// counting).  The small workgroups over 9,300 of 10,000 queries of 4,784 listed ids:
+// 403 us when every id searched for its list, swapped before it read and every
+// thread verified a row of its own, 345 us now (chunks of 16 or 32 ids: 354, 356).
+constexpr uint32_t kChunk = 8;  // ids of a list that adjacent lanes take
 
 // The set (tab) is read until the kept ids are compacted into cid; the keys
 // of the kept ids (ckey) and the survivors of the final selection (surv) are
@@ -135,6 +140,15 @@ __device__ inline uint32_t block_select(uint32_t nitems, uint32_t need, Val val,
     return scal[SC_PREFIX];
 }
 
+// The dot product of 16 bytes (wrapping uint32 arithmetic)
+__device__ inline uint32_t dot_parts(uint4 a, uint4 b)
+{
+    uint32_t s = __builtin_amdgcn_udot4(a.x, b.x, 0u, false);
+    s = __builtin_amdgcn_udot4(a.y, b.y, s, false);
+    s = __builtin_amdgcn_udot4(a.z, b.z, s, false);
+    return __builtin_amdgcn_udot4(a.w, b.w, s, false);
+}
+
 template <int DT, int B>
 __global__ __launch_bounds__(B) void count_kernel(const CountArgs A)
 {
@@ -148,81 +162,112 @@ __global__ __launch_bounds__(B) void count_kernel(const CountArgs A)
     uint32_t *radix = reinterpret_cast<uint32_t *>(smem + lay.radix);
     uint32_t *scal = reinterpret_cast<uint32_t *>(smem + lay.scal);
 
-    __shared__ uint32_t lpref[kMaxL + 1], lstart[kMaxL];
+    // per list: its chunks' prefix, its ids, its first id's place in ids
+    __shared__ uint32_t cpref[kMaxL + 1], lsize[kMaxL], lfirst[kMaxL], s_total;
     const int tid = threadIdx.x;
     const int64_t q = A.qlist ? (int64_t)A.qlist[blockIdx.x] : (int64_t)blockIdx.x;
 
-    // list offsets: an exclusive prefix of the L list sizes over the first wave
-    if (tid < 64) {
-        uint32_t sz = 0, st = 0;
-        if (tid < A.L) {
-            sz = A.bsize[q * A.L + tid];
-            st = A.bstart[q * A.L + tid];
+    if (tid < 64) {  // the L lists over the first wave
+        const uint32_t sz = tid < A.L ? A.bsize[q * A.L + tid] : 0u;
+        const uint32_t ch = (sz + kChunk - 1u) / kChunk;
+        const uint32_t inc = wave_inclusive_sum(ch), all = wave_inclusive_sum(sz);
+        cpref[tid] = inc - ch;
+        lsize[tid] = sz;
+        lfirst[tid] = tid < A.L ? (uint32_t)tid * (uint32_t)A.n + A.bstart[q * A.L + tid] : 0u;
+        if (tid == 63) {
+            cpref[kMaxL] = inc;
+            s_total = all;
         }
-        const uint32_t inc = wave_inclusive_sum(sz);
-        lpref[tid] = inc - sz;
-        lstart[tid] = st;
-        if (tid == 63) lpref[kMaxL] = inc;
     }
     __syncthreads();
-    const uint32_t total = lpref[kMaxL];
+    const uint32_t total = s_total;
     // this query's set: at least 4/3 of its listed ids (<= the launch's size)
     int c = 4;
     while ((3u << c) < 4u * total && c < (int)A.cap_log2) ++c;
     const uint32_t cap = 1u << c, mask = cap - 1u;
 
-    for (uint32_t s = tid; s < cap; s += B) tab[s] = 0u;
+    for (uint32_t s = 4 * tid; s < cap; s += 4 * B) *reinterpret_cast<uint4 *>(tab + s) = uint4{0u, 0u, 0u, 0u};
     for (int s = tid; s < kHistBins; s += B) hist[s] = 0u;
     if (tid == 0) scal[SC_NCAND] = 0u;
     __syncthreads();
 
-    // 1. count: one insert per listed id (a point lies in one bucket per
-    // layer); kCountLoads positions of the concatenated lists per thread are
-    // located (binary search over the prefix) and loaded together
-    constexpr int kCountLoads = 4;
-    for (uint32_t base = 0; base < total; base += kCountLoads * B) {
-        uint32_t id[kCountLoads];
+    // 1. count: one insert per listed id (a point lies in one bucket per layer).
+    // kChunk lanes take an even share of the lists' chunks, walk from list to
+    // list and load kCountLoads chunks together.  Most ids are in the set
+    // already, so a slot is read before anything is written.
+    {
+        constexpr int kCountLoads = 4, parts = B / kChunk;
+        const uint32_t h = (uint32_t)tid / kChunk, hl = (uint32_t)tid % kChunk, nch = cpref[kMaxL];
+        uint32_t at = nch * h / parts;
+        const uint32_t end = nch * (h + 1) / parts;
+        int l = 0;  // the list of chunk `at`: the last one whose chunks start at or before it
 #pragma unroll
-        for (int r = 0; r < kCountLoads; ++r) {
-            const uint32_t pos = base + (uint32_t)(r * B + tid);
-            id[r] = kEmpty;
-            if (pos < total) {
-                int lo = 0;  // largest layer with lpref <= pos (its list holds pos)
+        for (int step = kMaxL / 2; step > 0; step >>= 1)
+            if (cpref[l + step] <= at) l += step;
+        uint32_t off = at < end ? (at - cpref[l]) * kChunk : 0u, size = lsize[l], first = lfirst[l];
+        const uint32_t inc = 1u << kCountShift;
+        while (__ballot(at < end)) {
+            uint32_t id[kCountLoads], slot[kCountLoads], pend = 0;
 #pragma unroll
-                for (int step = kMaxL / 2; step > 0; step >>= 1) {
-                    const int m = lo + step;
-                    if (m < A.L && lpref[m] <= pos) lo = m;
+            for (int r = 0; r < kCountLoads; ++r) {
+                id[r] = 0;
+                if (at < end) {
+                    if (off >= size) {  // on to the next list that has any
+                        do ++l;
+                        while (lsize[l] == 0u);
+                        size = lsize[l];
+                        first = lfirst[l];
+                        off = 0u;
+                    }
+                    if (off + hl < size) {
+                        id[r] = (uint32_t)A.ids[first + off + hl];
+                        pend |= 1u << r;
+                    }
+                    off += kChunk;
+                    ++at;
                 }
-                id[r] = (uint32_t)A.ids[(int64_t)lo * A.n + lstart[lo] + (pos - lpref[lo])];
             }
-        }
 #pragma unroll
-        for (int r = 0; r < kCountLoads; ++r) {
-            if (id[r] == kEmpty) continue;
-            uint32_t h = hash_id(id[r], c);
-            const uint32_t step = hash_step(id[r], c);
+            for (int r = 0; r < kCountLoads; ++r) slot[r] = hash_id(id[r], c);
             // the set holds at most 3/4 of its slots, so some slot of the
             // odd-step sequence is free or holds the id
-            for (uint32_t t = 0; t < cap; ++t) {
-                const uint32_t key = id[r] + 1u;
-                const uint32_t prev = atomicCAS(&tab[h], 0u, key | (1u << kCountShift));
-                if (prev == 0u) break;  // new, counted once
-                if ((prev & kSlotId) == key) {
-                    atomicAdd(&tab[h], 1u << kCountShift);
-                    break;
+            while (pend) {
+                uint32_t w[kCountLoads];
+#pragma unroll
+                for (int r = 0; r < kCountLoads; ++r) w[r] = tab[slot[r]];
+#pragma unroll
+                for (int r = 0; r < kCountLoads; ++r) {
+                    if (!((pend >> r) & 1u)) continue;
+                    const uint32_t key = id[r] + 1u;
+                    uint32_t o = w[r];
+                    if (o == 0u) {
+                        o = atomicCAS(&tab[slot[r]], 0u, key | inc);
+                        if (o == 0u) {  // new, counted once
+                            pend &= ~(1u << r);
+                            continue;
+                        }
+                    }
+                    if ((o & kSlotId) == key) {
+                        atomicAdd(&tab[slot[r]], inc);
+                        pend &= ~(1u << r);
+                    } else {
+                        slot[r] = (slot[r] + hash_step(id[r], c)) & mask;
+                    }
                 }
-                h = (h + step) & mask;
             }
         }
     }
     __syncthreads();
 
     // 2. counts >= theta, the crossing count c* and how many ids it contributes
-    for (uint32_t s = tid; s < cap; s += B)
-        if (tab[s] != 0u) {
-            const uint32_t k = slot_count(tab[s]);
+    for (uint32_t s = 4 * tid; s < cap; s += 4 * B) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(tab + s);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {  // (a free slot counts 0)
+            const uint32_t k = slot_count(i == 0 ? w.x : i == 1 ? w.y : i == 2 ? w.z : w.w);
             if (k >= (uint32_t)A.theta) atomicAdd(&hist[k], 1u);
         }
+    }
     __syncthreads();
     if (tid < 64) {
         // lane i holds the ids counted L - i (descending counts); the lane
@@ -252,43 +297,77 @@ __global__ __launch_bounds__(B) void count_kernel(const CountArgs A)
 
     // kept: counted above c*, or counted c* with an id up to `last`
     // (one LDS atomic per wave and round, not one per kept id on one address)
-    for (uint32_t s0 = 0; s0 < cap; s0 += B) {
-        const uint32_t s = s0 + (uint32_t)tid;
-        const uint32_t w = s < cap ? tab[s] : 0u;
-        const uint32_t id = slot_id(w), k = slot_count(w);
-        const bool keep = w != 0u && (k > cstar || (k == cstar && id <= last));
-        const unsigned long long m = __ballot(keep);
+    for (uint32_t s0 = 0; s0 < cap; s0 += 4 * B) {
+        const uint32_t s = s0 + 4u * (uint32_t)tid;
+        const uint4 w = s < cap ? *reinterpret_cast<const uint4 *>(tab + s) : uint4{0u, 0u, 0u, 0u};
         const int lane = tid & 63;
-        uint32_t at = 0;
-        if (lane == 0 && m) at = atomicAdd(&scal[SC_NCAND], (uint32_t)__popcll(m));
+        uint32_t id[4];
+        bool keep[4];
+        unsigned long long m[4];
+        uint32_t n = 0, at = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = i == 0 ? w.x : i == 1 ? w.y : i == 2 ? w.z : w.w, k = slot_count(x);
+            id[i] = slot_id(x);
+            keep[i] = x != 0u && (k > cstar || (k == cstar && id[i] <= last));
+            m[i] = __ballot(keep[i]);
+            n += (uint32_t)__popcll(m[i]);
+        }
+        if (lane == 0 && n) at = atomicAdd(&scal[SC_NCAND], n);
         at = (uint32_t)__shfl((int)at, 0);
-        if (keep) cid[at + (uint32_t)__popcll(m & (lane ? (~0ull >> (64 - lane)) : 0ull))] = id;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (keep[i]) cid[at + (uint32_t)__popcll(m[i] & (lane ? (~0ull >> (64 - lane)) : 0ull))] = id[i];
+            at += (uint32_t)__popcll(m[i]);
+        }
     }
     __syncthreads();
     const int nc = (int)scal[SC_NCAND];
 
     // 3. verify the kept ids
-    for (int i = tid; i < nc; i += B) {
-        const uint32_t id = cid[i];
-        if constexpr (DT == QW_U8) {
-            const uint4 *x = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(A.data) +
-                                                             (int64_t)id * A.dp);
-            const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(A.queries) +
-                                                              q * A.dp);
-            uint32_t acc = 0;
-            float unused = 0.f;
-            const int n16 = A.dp / 16;
-            for (int p0 = 0; p0 < n16; p0 += 8) {  // eight 16-byte parts in flight
-                uint4 xv[8];
+    if constexpr (DT == QW_U8) {
+        // one 16-byte part per lane (a row's lanes read whole lines), kAhead
+        // rows per group of lanes in flight
+        constexpr int kAhead = 4;
+        const int n16 = A.dp / 16;
+        int lpr = 1;
+        while (lpr < n16 && lpr < 64) lpr <<= 1;
+        const int part = tid & (lpr - 1), g = tid / lpr, groups = B / lpr;
+        const uint4 *x = static_cast<const uint4 *>(A.data);
+        const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(A.queries) + q * A.dp);
+        const uint4 y0 = part < n16 ? qv[part] : uint4{0u, 0u, 0u, 0u};
+        const uint32_t yy = dot_parts(y0, y0);
+        for (int i0 = 0; i0 < nc; i0 += groups * kAhead) {  // uniform
+            uint32_t acc[kAhead] = {};
+            int64_t row[kAhead];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) xv[u] = x[p0 + u < n16 ? p0 + u : n16 - 1];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (p0 + u < n16) part_dist<QW_U8>(xv[u], qv[p0 + u], acc, unused);
+            for (int u = 0; u < kAhead; ++u) {
+                const int i = i0 + u * groups + g;
+                row[u] = (int64_t)cid[i < nc ? i : nc - 1] * n16;
             }
-            ckey[i] = ((uint64_t)acc << 32) | id;
-        } else {
-            const float *x = static_cast<const float *>(A.data) + (int64_t)id * A.dp;
+            if (part < n16) {
+                uint4 xv[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) xv[u] = x[row[u] + part];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) acc[u] = dot_parts(xv[u], xv[u]) - 2u * dot_parts(xv[u], y0) + yy;
+            }
+            for (int p = part + 64; p < n16; p += 64) {  // rows of more than 64 parts
+                const uint4 y = qv[p];
+                float unused = 0.f;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) part_dist<QW_U8>(x[row[u] + p], y, acc[u], unused);
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                for (int o = lpr >> 1; o > 0; o >>= 1) acc[u] += (uint32_t)__shfl_xor((int)acc[u], o);
+                const int i = i0 + u * groups + g;
+                if (part == 0 && i < nc) ckey[i] = ((uint64_t)acc[u] << 32) | cid[i];
+            }
+        }
+    } else {
+        for (int i = tid; i < nc; i += B) {
+            const float *x = static_cast<const float *>(A.data) + (int64_t)cid[i] * A.dp;
             const float *qv = static_cast<const float *>(A.queries) + q * A.dp;
             ckey[i] = (uint64_t)__double_as_longlong(exact_dist_row(x, qv, A.dp));
         }
