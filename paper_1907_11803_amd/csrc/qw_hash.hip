@@ -579,6 +579,120 @@ __global__ __launch_bounds__(kBlock) void hash_mfma_f32_kernel(
         atomicAdd(recomputed + (blockIdx.y * gridDim.x + blockIdx.x) % kRecompSlots, nre);
 }
 
+// The same products for few rows: 16 rows x 64 functions per workgroup, its
+// eight waves taking every eighth K chunk and their FP64 sums added at the end.
+// Operands come straight from L2 in the matrix layout (nothing is shared between
+// the waves).  Few rows leave most of the chip idle and the 64-row form's chunks
+// then wait for memory one after the other.  960 columns, 192 functions, the
+// whole hashing stage: 1 row 58 us in 64-row tiles, 40 here; 1,000 rows 106 and
+// 48; 8,000 173 and 124; 16,000 187 and 205.  300 columns, 80 functions: 1,000
+// rows 40 and 26, 8,000 51 and 44, 16,000 64 and 67.
+constexpr int64_t kSplitRows = 8192;  // up to which this form is the faster one
+constexpr int kSplitBlock = 512, kSplitWaves = kSplitBlock / 64;
+__global__ __launch_bounds__(kSplitBlock) void hash_split_f32_kernel(
+    const float *__restrict__ x, int64_t m, int32_t dp, int32_t d, const float *__restrict__ a32,
+    const float *__restrict__ b, int32_t f0, int32_t nfun, double w,
+    const double *__restrict__ gbc, int32_t *__restrict__ out, int32_t out_ld,
+    unsigned long long *recomputed)
+{
+    constexpr int KC = kKcF32, NS = KC / 16, half = kSplitWaves / 2;
+    __shared__ double part[half][16 * 64];
+    __shared__ float s_xmax[kSplitWaves][16];
+    __shared__ uint16_t pool[16 * 64];
+    __shared__ uint32_t npool;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nft = (nfun + 63) / 64;
+    const int64_t rowb = (int64_t)(blockIdx.x / nft) * 16;
+    const int fbase = f0 + (int)(blockIdx.x % nft) * 64;
+    const int r = lane & 15, kq = (lane >> 4) * 4;
+    const float *xp = x + (rowb + r < m ? rowb + r : m - 1) * dp + kq;
+    const float *ap = a32 + (int64_t)(fbase + r) * dp + kq;
+    if (tid == 0) npool = 0;
+    double dacc[4][4];
+#pragma unroll
+    for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) dacc[fb][j] = 0.0;
+    float xmax = 0.f;
+    for (int kc = wv * KC; kc < dp; kc += kSplitWaves * KC) {
+        const int ns = min(NS, (dp - kc) / 16);
+        float4 xv[NS], av[NS][4];
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const int k = kc + (st < ns ? st : ns - 1) * 16;  // a step past dp re-reads the last one
+            xv[st] = *reinterpret_cast<const float4 *>(xp + k);
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb)
+                av[st][fb] = *reinterpret_cast<const float4 *>(ap + (int64_t)fb * 16 * dp + k);
+        }
+        floatx4_t acc[4];
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb) acc[fb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            if (st >= ns) break;  // uniform
+            const float4 v = xv[st];
+            xmax = fmaxf(xmax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb) acc[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.x, av[st][fb].x, acc[fb], 0, 0, 0);
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb) acc[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.y, av[st][fb].y, acc[fb], 0, 0, 0);
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb) acc[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.z, av[st][fb].z, acc[fb], 0, 0, 0);
+#pragma unroll
+            for (int fb = 0; fb < 4; ++fb) acc[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(v.w, av[st][fb].w, acc[fb], 0, 0, 0);
+        }
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dacc[fb][j] += (double)acc[fb][j];
+    }
+    xmax = fmaxf(xmax, __shfl_xor(xmax, 16));
+    xmax = fmaxf(xmax, __shfl_xor(xmax, 32));
+    if (lane < 16) s_xmax[wv][lane] = xmax;
+    // output (row kq + j, function fb * 16 + r) of the block at row * 64 + function
+    auto at = [&](int fb, int j) { return (kq + j) * 64 + fb * 16 + r; };
+    if (wv >= half)
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[wv - half][at(fb, j)] = dacc[fb][j];
+    __syncthreads();
+    if (wv < half)  // the same lane wrote the place in the other half
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[wv][at(fb, j)] += dacc[fb][j];
+    __syncthreads();
+    const float iw = (float)(1.0 / w);
+    for (int o = tid; o < 16 * 64; o += kSplitBlock) {
+        const int64_t row = rowb + (o >> 6);
+        const int f = fbase + (o & 63);
+        if (row >= m || f >= f0 + nfun) continue;
+        double sum = 0.0;
+        float xm = 0.f;
+#pragma unroll
+        for (int i = 0; i < half; ++i) sum += part[i][o];
+#pragma unroll
+        for (int i = 0; i < kSplitWaves; ++i) xm = fmaxf(xm, s_xmax[i][o >> 6]);
+        int32_t h;
+        if (accept_fp32((float)sum, b[f], iw, band_coef(gbc[f], w) * xm, h))
+            out[row * out_ld + (f - f0)] = h;
+        else
+            pool[atomicAdd(&npool, 1u)] = (uint16_t)o;
+    }
+    __syncthreads();
+    unsigned long long nre = 0;
+    for (uint32_t i = tid; i < npool; i += kSplitBlock) {
+        const int o = pool[i], f = fbase + (o & 63);
+        const int64_t row = rowb + (o >> 6);
+        out[row * out_ld + (f - f0)] = hash_exact<float>(x + row * dp, a32 + (int64_t)f * dp, d, b[f], w);
+        ++nre;
+    }
+    if (recomputed && nre) atomicAdd(recomputed + blockIdx.x % kRecompSlots, nre);
+}
+
 qw_status launch_hash(const qw_index *ix, const void *xpad, int64_t m, int32_t f0, int32_t nfun,
                       int32_t form, int32_t *out, int32_t out_ld,
                       unsigned long long *recomputed, hipStream_t s)
@@ -607,6 +721,11 @@ qw_status launch_hash(const qw_index *ix, const void *xpad, int64_t m, int32_t f
             (const uint8_t *)xpad, m, ix->dp, ix->d, ix->a_hi.as<_Float16>(),
             ix->a_lo.as<_Float16>(), ix->a32.as<float>(), ix->b32.as<float>(), f0, nfun, bpw, w,
             ix->gb_fast.as<double>(), out, out_ld, recomputed);
+    } else if (ix->dtype == QW_F32 && m <= kSplitRows) {
+        const unsigned g1 = (unsigned)(ceil_div(m, 16) * ceil_div(nfun, 64));
+        hash_split_f32_kernel<<<g1, kSplitBlock, 0, s>>>(
+            (const float *)xpad, m, ix->dp, ix->d, ix->a32.as<float>(), ix->b32.as<float>(), f0,
+            nfun, w, ix->gb_fast.as<double>(), out, out_ld, recomputed);
     } else if (ix->dtype == QW_F32) {
         hash_mfma_f32_kernel<<<grid, kBlock, 0, s>>>(
             (const float *)xpad, m, ix->dp, ix->d, ix->a32.as<float>(), ix->b32.as<float>(), f0,

@@ -616,6 +616,21 @@ def grouped_workload(seed, n, d, Q, ncl, spread, far=0):
     return np.clip(data, 0, 1).astype(np.float32), q.astype(np.float32)
 
 
+@pytest.mark.parametrize("m", [1, 15, 17, 8192, 8193])  # rows split over waves up to 8,192
+@pytest.mark.parametrize("d,L,k", [(16, 1, 1), (60, 7, 9), (64, 4, 16), (530, 5, 13), (960, 16, 12)])
+def test_float_query_hashing(m, d, L, k):
+    if m > 1000 and d > 64:
+        m = 1000 + m % 100  # the oracle's time
+    rng = np.random.default_rng(m + d)
+    data = rng.random((2000, d), dtype=np.float32)
+    q = rng.random((m, d), dtype=np.float32)
+    p = synth.hash_params(6, L, k, d, 1.0)
+    ix = build(data, p.a, p.b(), 1.0)
+    want = oracle.hash_points(q, p.a, p.b(), 1.0).reshape(m, L * k)
+    got = ix.hash(dev(q))[0].cpu().numpy().reshape(m, L * k)
+    assert np.array_equal(got, want)
+
+
 @pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K", [
     (3000, 16, 1, 4, 6, 4, 1.0, 10), (3000, 17, 33, 3, 6, 4, 1.0, 1),       # one query; one past a group
     (4000, 64, 200, 6, 8, 6, 2.0, 10), (4000, 100, 130, 5, 8, 6, 2.5, 100),  # whole chunk; ragged row, long list
