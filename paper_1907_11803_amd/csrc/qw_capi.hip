@@ -52,6 +52,15 @@ constexpr int kGroupedSetLog2 = 14;
 // ids each (150,000 x 50) took 0.58 ms query by query, 0.73 shared; 59,000 that
 // list 1,660 (460,000 x 73) 1.24 and 0.79.
 constexpr uint32_t kMinRun = 8, kShareGain = 8, kShareListed = 1024;
+// Queries up to which each takes one workgroup of 1,024 threads, whole calls (two
+// probes over 1M x 128, by a wave per query before; the plain union, by 256 threads):
+// 64 queries 99 -> 75 us and 128 -> 73, 512 120 -> 116 and 133 -> 110, 1,024 123 ->
+// 157 and 162 -> 158.  Where a wave would take a query it is one launch fewer, and
+// as fast for few listed ids: a single query 64 us by a wave and 65 so, ten that
+// list 450 ids each 61 and 71; so only from nl * mean_hit_bucket = kWideListed on
+// (at 650 both took 95 us, at 1,450 148 and 105).
+constexpr int64_t kWideQueries = 512;
+constexpr double kWideListed = 700.0;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
 constexpr int64_t kCandPerQuery = 4096;  // pair space reserved per query (beyond: fallback)
@@ -662,7 +671,7 @@ qw_status check_index(const qw_index *ix)
 // that verify their candidates and either select the top K themselves or
 // write keys into per-XCD regions for the select kernel, then the fallback.
 qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int64_t Q, int K,
-                       const qw_opts &o, bool share, hipStream_t s, int32_t *out_ids, void *out_dist,
+                       const qw_opts &o, bool share, bool wide, hipStream_t s, int32_t *out_ids, void *out_dist,
                        hipEvent_t *ev)
 {
     Workspace &w = ix->ws;
@@ -794,7 +803,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.cls_hi = hi;
             a.queue_only = queue_only;
             a.cap_base = kCmin;
-            a.xchunk = o.group ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
+            a.xchunk = o.group && !wide ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
             a.xwork = slot < 0 ? c32(ix) + W_GWORK + 2 * kXcd : c32(ix) + W_XWORK + kXcd * slot;
             a.in_list = in_list;
             a.in_count = in_count;
@@ -840,11 +849,12 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             } else {
                 a.cap_log2 = (uint32_t)(kCmin + hi);  // LDS size; also the queue's class
                 a.limit = 0xFFFFFFFFu;                 // each set's own 3/4 bound
+                a.wide = wide ? 1 : 0;
             }
-            return launch_dedup(a, plan.dgrid[hi], st);
+            return launch_dedup(a, a.wide ? (int)std::min<int64_t>(ceil_div(Q, kXcd) * kXcd, ix->cus) : plan.dgrid[hi], st);
         };
         const bool wave = plan.wgrid > 0 && o.dedup == 2;  // o: settings resolved by the caller
-        const bool wave_all = wave && topk && !count_only;  // serves every class by itself
+        const bool wave_all = wave && topk && !count_only && !wide;  // serves every class by itself
         const bool grouped = use_grouped && !count_only;
         // all queries of the classes up to gmax are in groups
         const bool only_groups = grouped && minrun <= 1u;
@@ -943,6 +953,12 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         // of their scratch sets), so the latter follows the merged launch on
         // its own stream instead of waiting for the side stream first
         const int gsplit = plan.grid_g >= 2 ? 1 : 0;
+        if (wide) {  // every LDS class in one launch; then the global class and what overflowed
+            QW_TRY(launch_range(0, glob - 1, nullptr, nullptr, queues + (int64_t)kQueueMerged * Q,
+                                c32(ix) + W_QMERGED, 0, 0, s));
+            return launch_range(glob, glob, queues + (int64_t)kQueueMerged * Q, c32(ix) + W_QMERGED,
+                                queues + (int64_t)(glob + 1) * Q, c32(ix) + W_DUMMY, kMaxClasses, 0, s);
+        }
         if (grouped && !only_groups) QW_TRY(groups());  // may add to any class
         QW_HIP(hipEventRecord(ix->fork[0], s));
         QW_HIP(hipStreamWaitEvent(ix->side, ix->fork[0], 0));
@@ -1395,10 +1411,15 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
                 eff.stage_split = -1;
         }
         const bool share = group_shares(ix, K, eff);
+        // few queries: nothing else fills the chip (left to the caller's or the
+        // tuned choice of kernel where there is one)
+        const bool wide = Q <= kWideQueries && opt.dedup == 0 && !tuned && !share &&
+                          eff.stage_split <= 0 && ix->nl <= 64 &&
+                          (eff.dedup == 1 || (Q > 1 && ix->nl * ix->mean_hit_bucket >= kWideListed));
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,
                          share ? Q : 0, K));
         if (opt.timing || !opt.graph) {
-            QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, share, s, out_ids, out_dist,
+            QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, share, wide, s, out_ids, out_dist,
                                 opt.timing ? ix->ev : nullptr));
         } else {
             GraphKey key;
@@ -1409,7 +1430,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             key.dedup = eff.dedup;
             key.xchunk = eff.xchunk;
             key.split = eff.stage_split;
-            key.share = share && group_held(ix, Q);
+            key.share = (share && group_held(ix, Q) ? 1 : 0) | (wide ? 2 : 0);
             auto it = ix->graphs.find(key);
             if (it == ix->graphs.end()) {
                 hipStream_t cs;
@@ -1420,7 +1441,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
                     (void)hipStreamDestroy(cs);
                     return QW_EDEVICE;
                 }
-                rc = enqueue_fast(ix, plan, queries, Q, K, eff, share, cs, out_ids, out_dist, nullptr);
+                rc = enqueue_fast(ix, plan, queries, Q, K, eff, share, wide, cs, out_ids, out_dist, nullptr);
                 hipError_t ec = hipStreamEndCapture(cs, &g);
                 (void)hipStreamDestroy(cs);
                 if (rc != QW_OK) {

@@ -176,7 +176,7 @@ __device__ inline uint32_t block_list_prefix(uint32_t *lpref, uint32_t *lstart, 
     return total;
 }
 
-// Loads positions base + r * kBlock + threadIdx.x (r < R) of the concatenated
+// Loads positions base + r * B + threadIdx.x (r < R; B threads) of the concatenated
 // bucket lists (list i holds positions [lpref[i], lpref[i+1]); lstart holds
 // the list offsets of a prefix above) into id[r]; returns the mask of
 // positions below T.  The list of a position is found by a binary search
@@ -185,7 +185,7 @@ __device__ inline uint32_t block_list_prefix(uint32_t *lpref, uint32_t *lstart, 
 // together; each group of four positions starts only if some position of the
 // workgroup's group lies below T (uniform), so the work follows the query's
 // list total rather than R.
-template <int R, int TOP = 32>
+template <int R, int TOP = 32, int B = kBlock>
 __device__ inline uint32_t load_ids(const int32_t *__restrict__ ids, int32_t nl,
                                     const uint32_t *lpref, const uint32_t *lstart, uint32_t T,
                                     uint32_t base, uint32_t (&id)[R])
@@ -194,12 +194,12 @@ __device__ inline uint32_t load_ids(const int32_t *__restrict__ ids, int32_t nl,
     uint32_t valid = 0;
 #pragma unroll
     for (int g = 0; g < R / 4; ++g) {
-        if (base + (uint32_t)(4 * g * kBlock) < T) {  // uniform
+        if (base + (uint32_t)(4 * g * B) < T) {  // uniform
             uint32_t pos[4];
             int lo[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                pos[r] = base + (uint32_t)((4 * g + r) * kBlock) + threadIdx.x;
+                pos[r] = base + (uint32_t)((4 * g + r) * B) + threadIdx.x;
                 lo[r] = 0;
             }
 #pragma unroll
@@ -228,7 +228,7 @@ __device__ inline uint32_t load_ids(const int32_t *__restrict__ ids, int32_t nl,
     return valid;
 }
 
-// Whole workgroup (kBlock threads).  Inserts the T ids of the concatenated
+// Whole workgroup (B threads, B at most the set's slots).  Inserts the T ids of the concatenated
 // bucket lists (as load_ids reads them) into the cleared set `tab` of
 // 2^cap_log2 slots.  The
 // unique count goes to *ucount; *ovf is set when it exceeds `limit` or the
@@ -236,7 +236,7 @@ __device__ inline uint32_t load_ids(const int32_t *__restrict__ ids, int32_t nl,
 // place: tab[0..U) holds the unique ids (unspecified order).  *ucount, *ovf
 // and *cpos must be 0 and visible to all threads on entry; returns after a
 // barrier.
-template <int TOP = 32>
+template <int TOP = 32, int B = kBlock>
 __device__ __attribute__((always_inline)) inline void set_union(const int32_t *__restrict__ ids, int32_t nl,
                                  const uint32_t *lpref, const uint32_t *lstart, uint32_t T,
                                  uint32_t *tab, int cap_log2, uint32_t limit, bool glob,
@@ -248,8 +248,8 @@ __device__ __attribute__((always_inline)) inline void set_union(const int32_t *_
     const unsigned long long lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
     // the next round's ids load while this round's are inserted
     uint32_t idn[R];
-    uint32_t pn = load_ids<R, TOP>(ids, nl, lpref, lstart, T, 0u, idn);
-    for (uint32_t base = 0; base < T; base += R * kBlock) {
+    uint32_t pn = load_ids<R, TOP, B>(ids, nl, lpref, lstart, T, 0u, idn);
+    for (uint32_t base = 0; base < T; base += R * B) {
         // every thread reads the flag before any thread of this pass can set
         // it, so the early exit is uniform
         const bool stop = *ovf != 0;
@@ -259,7 +259,7 @@ __device__ __attribute__((always_inline)) inline void set_union(const int32_t *_
 #pragma unroll
         for (int r = 0; r < R; ++r) idr[r] = idn[r];
         const uint32_t pend = pn;
-        if (base + R * kBlock < T) pn = load_ids<R, TOP>(ids, nl, lpref, lstart, T, base + R * kBlock, idn);
+        if (base + R * B < T) pn = load_ids<R, TOP, B>(ids, nl, lpref, lstart, T, base + R * B, idn);
         bool full = false;
         uint32_t nnew = (uint32_t)__popc(insert_streams<R, 4>(tab, cap_log2, idr, pend, max_probe, full));
         // one LDS atomic per wave for the unique count
@@ -276,7 +276,7 @@ __device__ __attribute__((always_inline)) inline void set_union(const int32_t *_
     // compact in place: contents move only to lower positions that were read
     // in this or an earlier round
     const uint32_t cap = 1u << cap_log2;
-    for (uint32_t base = 0; base < cap; base += kBlock) {
+    for (uint32_t base = 0; base < cap; base += B) {
         const uint32_t v = tab[base + tid];
         const bool occ = v != kEmpty;
         if (glob) __threadfence();

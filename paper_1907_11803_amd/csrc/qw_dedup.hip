@@ -16,10 +16,15 @@ namespace qw {
 
 enum {
     D_UCOUNT = 0, D_OVF, D_CPOS, D_T, D_CAP, D_OFF = 6 /* u64 */,
-    D_WT = 8 /* per-wave counts, kBlock / 64 */, D_NEXT = 12, D_LCNT = 13, D_BAD = 14,
-    D_BOUND = 16 /* u64 */, D_KTH = 18 /* u64 */, D_NSCAL = 20
+    D_NEXT = 12, D_LCNT = 13, D_BAD = 14,
+    D_BOUND = 16 /* u64 */, D_KTH = 18 /* u64 */, D_WT = 20 /* per-wave counts, kWideBlock / 64 */, D_NSCAL = 36
 };
 constexpr int kRegIds = 12;  // ids per thread of the register-resident path
+// Threads of a workgroup when few queries leave CUs to spare: a query's lists,
+// set and rows are then one workgroup's latency.  This kernel over 64 queries of
+// 1,470 listed ids: a wave each 57 us, 256 threads 36, 1,024 26; of 3,190: 256
+// threads 70 us, 1,024 34.
+constexpr int kWideBlock = 1024;
 
 __host__ __device__ inline size_t a16(size_t v) { return (v + 15) & ~size_t(15); }
 
@@ -32,10 +37,11 @@ size_t dedup_lds_bytes(int cap_log2, int global_tab, int nl, int row_bytes)
 
 // Exclusive prefix of the per-wave counts in scal[D_WT..]: the wave's base and
 // the workgroup total.  Call after the barrier that publishes the counts.
+template <int B>
 __device__ inline uint32_t wave_base(const uint32_t *scal, int wave, uint32_t *total)
 {
     uint32_t b = 0, t = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
+    for (int w = 0; w < B / 64; ++w) {
         const uint32_t c = scal[D_WT + w];
         b += w < wave ? c : 0u;
         t += c;
@@ -79,7 +85,7 @@ __device__ inline void lane_top_insert(LaneTop &t, unsigned long long key, bool 
 // written).
 enum { kVerifyKeys = 0, kVerifyTop = 1, kVerifyCollect = 2 };
 
-template <int DT, int MODE>
+template <int DT, int MODE, int B>
 __device__ inline void verify_small(const DedupArgs &A, const uint32_t *list, uint32_t U,
                                     const uint4 *qrow, int parts, unsigned long long *keys,
                                     uint32_t qq, LaneTop &top, unsigned long long bound = 0,
@@ -90,7 +96,7 @@ __device__ inline void verify_small(const DedupArgs &A, const uint32_t *list, ui
     const int pl = (parts + 1) / 2;  // lanes' worth of part pairs
     int G = 1;
     while (G < pl) G <<= 1;
-    const int NG = kBlock / G;
+    const int NG = B / G;
     const uint32_t PI = (uint32_t)(NG * UN2);
     const int grp = tid / G, j = tid % G;
     const int lg_ng = __builtin_ctz((unsigned)NG);
@@ -214,7 +220,7 @@ __device__ inline void verify_small(const DedupArgs &A, const uint32_t *list, ui
 // squares of differences.  Rows of one part per lane: the
 // next step's rows are loaded before the current step is reduced, so two
 // steps are in flight.  No barriers.
-template <int DT, int MODE>
+template <int DT, int MODE, int B>
 __device__ inline void verify_list(const DedupArgs &A, const uint32_t *list, uint32_t U,
                                    const uint4 *qrow, int parts, unsigned long long *keys,
                                    LaneTop &top, unsigned long long bound = 0,
@@ -225,7 +231,7 @@ __device__ inline void verify_list(const DedupArgs &A, const uint32_t *list, uin
     int G = 1;
     while (G < parts && G < 64) G <<= 1;
     const int P = (parts + G - 1) / G;
-    const int NG = kBlock / G;
+    const int NG = B / G;
     const uint32_t PI = (uint32_t)(NG * UN);
     const int grp = tid / G, j = tid % G;
     const uint4 *drows = reinterpret_cast<const uint4 *>(A.data);
@@ -262,7 +268,7 @@ __device__ inline void verify_list(const DedupArgs &A, const uint32_t *list, uin
             }
     };
     if (P == 1 || MODE != kVerifyKeys) {  // the fused top K runs only on rows of at most 64 parts
-        verify_small<DT, MODE>(A, list, U, qrow, parts, keys, qq, top, bound, lcnt, cap);
+        verify_small<DT, MODE, B>(A, list, U, qrow, parts, keys, qq, top, bound, lcnt, cap);
         return;
     }
     for (uint32_t base = 0; base < U; base += PI) {
@@ -345,7 +351,7 @@ __device__ inline uint32_t wave_kth_u32(uint32_t v, int K)
 //     sends the query to the fallback.
 // A.topk_keep < kTopR keeps fewer keys per lane (a diagnostic: more queries
 // take the second pass; the result does not change).
-template <bool GLOB, int DT>
+template <bool GLOB, int DT, int BS>
 __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, const uint32_t *tab,
                                   uint32_t U, uint32_t cap_words, const uint4 *qrow, int parts,
                                   uint32_t *scal)
@@ -387,7 +393,7 @@ __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, cons
             }
             return;
         }
-        for (uint32_t i = tid; i < c; i += kBlock) {
+        for (uint32_t i = tid; i < c; i += BS) {
             const unsigned long long k = lst[i];
             int r = 0;
             for (uint32_t e = 0; e < c; ++e) r += lst[e] < k;
@@ -398,7 +404,7 @@ __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, cons
             }
             if (r == K - 1) *s_kth = k;  // keys are unique: one writer
         }
-        for (int r = (int)c + tid; r < K; r += kBlock) {
+        for (int r = (int)c + tid; r < K; r += BS) {
             const int64_t o = q * K + r;
             A.out_ids[o] = -1;
             reinterpret_cast<int32_t *>(A.out_dist)[o] = INT32_MAX;
@@ -439,7 +445,7 @@ __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, cons
     }
     sync();
     LaneTop unused;
-    verify_list<DT, kVerifyCollect>(A, tab, U, qrow, parts, lst, unused, T, &scal[D_LCNT], lcap);
+    verify_list<DT, kVerifyCollect, BS>(A, tab, U, qrow, parts, lst, unused, T, &scal[D_LCNT], lcap);
     sync();
     const uint32_t c2 = scal[D_LCNT];
     if (c2 > lcap) {
@@ -456,7 +462,7 @@ __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, cons
 // workgroup's atomic on one address), so neighbouring queries of the order --
 // grouped by candidate overlap -- share one XCD's L2.  Each workgroup fetches
 // its next item while the current one runs.  Queries with
-// at most kRegIds * kBlock (12 x 256)
+// at most kRegIds * B (12 x 256, or 12 x 1,024)
 // bucket entries in an LDS set keep their ids in registers from the load to
 // the write; larger ones (and the global-memory class, GLOB) go through the
 // set and read the unique ids back from it.
@@ -465,8 +471,8 @@ __device__ inline void fused_topk(const DedupArgs &A, int64_t q, LaneTop t, cons
 // MP: neighbour probing (more than 64 lists per query): the list ranges load
 // at the start of each query instead of during the previous one, the list
 // prefix takes the whole workgroup and the list search ten steps.
-template <bool GLOB, int DT, bool MP>
-__global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
+template <bool GLOB, int DT, bool MP, int B = kBlock>
+__global__ __launch_bounds__(B, 4) void dedup_kernel(DedupArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -546,7 +552,7 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
         if (tid == 0) next = atomicAdd(A.xwork + xcd, 1u);  // published at the end of the iteration
         const int64_t q = query_of(item);
         if (MP) {
-            for (int i = tid; i < A.nl; i += kBlock) {
+            for (int i = tid; i < A.nl; i += B) {
                 lstart[i] = A.bstart[q * A.nl + i];
                 lpref[i + 1] = A.bsize[q * A.nl + i];
             }
@@ -554,7 +560,7 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
             lstart[tid] = pf_start;
             lpref[tid + 1] = pf_size;
         }
-        for (int i = tid; i < parts; i += kBlock)  // the query row, for the verification
+        for (int i = tid; i < parts; i += B)  // the query row, for the verification
             qrow[i] = reinterpret_cast<const uint4 *>(A.queries)[q * parts + i];
         if (tid == 0) {
             scal[D_UCOUNT] = 0;
@@ -584,12 +590,12 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
         const uint32_t set_limit = (cap >> 2) * 3;
         const uint32_t limit = glob ? set_limit : (A.limit < set_limit ? A.limit : set_limit);
         const uint32_t max_probe = glob ? 0xFFFFFFFFu : kShortProbe;
-        const bool in_regs = !glob && T <= (uint32_t)(kRegIds * kBlock);
+        const bool in_regs = !glob && T <= (uint32_t)(kRegIds * B);
         uint32_t idr[kRegIds];
         uint32_t pend = 0;
         if (in_regs)  // the id loads fly while the set is cleared
-            pend = load_ids<kRegIds, kTop>(A.ids, A.nl, lpref, lstart, T, 0u, idr);
-        for (uint32_t i = 4 * tid; i < cap; i += 4 * kBlock)  // cap >= 1024: whole 16-byte stores
+            pend = load_ids<kRegIds, kTop, B>(A.ids, A.nl, lpref, lstart, T, 0u, idr);
+        for (uint32_t i = 4 * tid; i < cap; i += 4 * B)  // cap >= 1024: whole 16-byte stores
             *reinterpret_cast<uint4 *>(tab + i) = uint4{kEmpty, kEmpty, kEmpty, kEmpty};
         if (glob) __threadfence();
         bar();
@@ -610,11 +616,11 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
             if (__ballot(full) != 0ull && lane == 0) scal[D_OVF] = 1;
             bar();
             uint32_t tot = 0;
-            wbase += wave_base(scal, wave, &tot);
+            wbase += wave_base<B>(scal, wave, &tot);
             U = tot;
             ovf = scal[D_OVF] != 0 || U > limit;
         } else {
-            set_union<kTop>(A.ids, A.nl, lpref, lstart, T, tab, cap_log2, limit, glob, max_probe,
+            set_union<kTop, B>(A.ids, A.nl, lpref, lstart, T, tab, cap_log2, limit, glob, max_probe,
                       true, &scal[D_UCOUNT], &scal[D_OVF], &scal[D_CPOS]);
             U = scal[D_UCOUNT];
             ovf = scal[D_OVF] != 0 || U > limit;
@@ -664,7 +670,7 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
                 uint32_t e = wbase;
 #pragma unroll
                 for (int g = 0; g < kRegIds / 4; ++g)
-                    if ((uint32_t)(4 * g * kBlock) < T)  // uniform: groups that held ids
+                    if ((uint32_t)(4 * g * B) < T)  // uniform: groups that held ids
 #pragma unroll
                         for (int r = 4 * g; r < 4 * g + 4; ++r)
                             if ((newm >> r) & 1u) tab[e++] = idr[r];
@@ -675,11 +681,11 @@ __global__ __launch_bounds__(kBlock, 4) void dedup_kernel(DedupArgs A)
             for (int r = 0; r < kTopR; ++r) top.k[r] = ~0ull;
             top.dmin = ~0ull;
             if (DT == QW_U8 && A.topk) {
-                verify_list<DT, kVerifyTop>(A, tab, U, qrow, parts, nullptr, top);
+                verify_list<DT, kVerifyTop, B>(A, tab, U, qrow, parts, nullptr, top);
                 // the selection list goes into the set's memory after the ids
-                fused_topk<GLOB, DT>(A, q, top, tab, U, 1u << A.cap_log2, qrow, parts, scal);
+                fused_topk<GLOB, DT, B>(A, q, top, tab, U, 1u << A.cap_log2, qrow, parts, scal);
             } else {
-                verify_list<DT, kVerifyKeys>(A, tab, U, qrow, parts, A.keys + off, top);
+                verify_list<DT, kVerifyKeys, B>(A, tab, U, qrow, parts, A.keys + off, top);
             }
         }
         bar();  // scal and the set are rewritten by the next item
@@ -697,6 +703,13 @@ qw_status launch_dedup(const DedupArgs &a, int grid, hipStream_t s)
     if (a.nl < 1 || a.nl > kMaxLists || (a.nl > 64 && !a.pmagic)) return QW_EINVAL;
     const size_t lds = dedup_lds_bytes((int)a.cap_log2, a.global_tab, a.nl,
                                        a.dp * (a.dtype == QW_U8 ? 1 : 4));
+    if (a.wide) {
+        if (a.nl > 64 || a.global_tab || (1 << a.cap_base) < kWideBlock) return QW_EINTERNAL;
+        if (a.dtype == QW_U8) dedup_kernel<false, QW_U8, false, kWideBlock><<<grid, kWideBlock, lds, s>>>(a);
+        else dedup_kernel<false, QW_F32, false, kWideBlock><<<grid, kWideBlock, lds, s>>>(a);
+        QW_HIP(hipGetLastError());
+        return QW_OK;
+    }
     const bool mp = a.nl > 64;  // the wide-list instantiation only where 64 lists do not suffice
     if (a.dtype == QW_U8) {
         if (mp) {

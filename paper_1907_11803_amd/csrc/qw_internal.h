@@ -514,6 +514,7 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
 
 // ---------------------------------------------------------------- flat pipeline
 struct DedupArgs {
+    int32_t wide;                    // one large workgroup per query (few queries)
     const int32_t *order;            // scheduled query order
     const unsigned long long *seg;   // {begin, end} of every class in the order (gaps allowed)
     int32_t cls_lo, cls_hi;          // this launch serves classes cls_lo..cls_hi

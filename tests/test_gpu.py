@@ -616,6 +616,26 @@ def grouped_workload(seed, n, d, Q, ncl, spread, far=0):
     return np.clip(data, 0, 1).astype(np.float32), q.astype(np.float32)
 
 
+@pytest.mark.parametrize("Q", [1, 2, 512, 513])  # a large workgroup per query up to 512
+@pytest.mark.parametrize("n,d,ncl,w,K,dtype", [
+    (6000, 64, 6, 700.0, 10, "u8"), (6000, 48, 6, 500.0, 40, "u8"),        # in-kernel top K; key lists
+    (9000, 32, 1, 9000.0, 10, "u8"), (40000, 16, 1, 9000.0, 3, "u8"),      # the largest sets; beyond them
+    (6000, 40, 6, 2.0, 10, "f32"), (40000, 16, 1, 50.0, 5, "f32"),
+])
+def test_few_queries(Q, n, d, ncl, w, K, dtype):
+    data, q = grouped_workload(n + d, n, d, Q, ncl, 0.08)
+    if dtype == "u8":
+        data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+    p = synth.hash_params(5, 5, 3, d, w)
+    ix = build(data, p.a, p.b(), w)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    for sched in (lib.QW_SCHED_SUM, lib.QW_SCHED_ACTUAL):
+        for graph in (0, 1, 1):
+            ids, dist, st = ix.query(dev(q), K, lib.make_opts(sched=sched, graph=graph), stats=True)
+            check_topk(ids, dist, ids_o, dist_o, dtype == "u8")
+            assert st["cand_unique"] == int(cnt_o.sum())
+
+
 @pytest.mark.parametrize("m", [1, 15, 17, 8192, 8193])  # rows split over waves up to 8,192
 @pytest.mark.parametrize("d,L,k", [(16, 1, 1), (60, 7, 9), (64, 4, 16), (530, 5, 13), (960, 16, 12)])
 def test_float_query_hashing(m, d, L, k):
