@@ -1411,9 +1411,16 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
                 eff.stage_split = -1;
         }
         const bool share = group_shares(ix, K, eff);
-        // few queries: nothing else fills the chip (left to the caller's or the
-        // tuned choice of kernel where there is one)
-        const bool wide = Q <= kWideQueries && opt.dedup == 0 && !tuned && !share &&
+        // few queries: nothing else fills the chip (left to the caller's choice of
+        // kernel, or a tuned one other than the built-in, where there is one)
+        bool chosen = opt.dedup != 0;
+        if (tuned && !chosen) {
+            qw_opts built = opt;
+            built.tune_cache = nullptr;
+            resolve_fast_auto(ix, Q, K, &built, nullptr);
+            chosen = eff.dedup != built.dedup || eff.group != built.group || eff.xchunk != built.xchunk;
+        }
+        const bool wide = Q <= kWideQueries && !chosen && !share &&
                           eff.stage_split <= 0 && ix->nl <= 64 &&
                           (eff.dedup == 1 || (Q > 1 && ix->nl * ix->mean_hit_bucket >= kWideListed));
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,

@@ -225,7 +225,7 @@ extern "C" qw_status qw_autotune(qw_index *ix, const void *queries, int64_t Q, i
                 cands.push_back(c);
             }
         qw_opts o = b;
-        o.dedup = cands[i].dedup;
+        o.dedup = i ? cands[i].dedup : 0;  // the automatic choice has kernels of its own for few queries
         o.group = cands[i].group;
         o.xchunk = cands[i].xchunk;
         o.stage_split = cands[i].split;
