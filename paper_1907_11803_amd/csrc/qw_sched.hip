@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kBlock) void group_bin_kernel(GroupOrderArgs A, uin
             const int cls = class_of(s_sum[tid], A.n, A.exact, q, A.pred_log != nullptr, A.pred_log ? A.pred_log[q] : 0.f,
                                      A.margin, A.force_max, A.cmin, A.cfloor, A.cmax, A.ncls);
             atomicAdd(&hist[cls], 1u);
-            if (cls <= A.gmax) bin = (mix32(lb) & (bins - 1u)) * kSub + mix32(t) % kSub;
+            bin = ((mix32(lb) & (bins - 1u)) + (cls > A.gmax ? bins : 0u)) * kSub + mix32(t) % kSub;
             A.cls[q] = cls;
         }
         s_bin[tid] = bin;
@@ -184,7 +184,10 @@ __global__ __launch_bounds__(kBlock) void group_bin_kernel(GroupOrderArgs A, uin
 }
 
 // A label with minrun queries at least gives groups of kGroupMax at most, of
-// even sizes, at the front of gorder; the other labels' queries go to its back.
+// even sizes, at the front of gorder; the other labels' queries go to its back,
+// and so do those of classes no group takes (the second half of the bins: they
+// run query by query, but neighbours still share rows in L2 -- 100,000 skewed
+// queries over 1M x 960 in one class took 160 ms in label order, 199 in none).
 // count[] becomes the finer bins' places there (kBack: counted from the back).
 // The class segments start empty.
 constexpr uint32_t kBack = 0x80000000u;
@@ -198,11 +201,11 @@ __global__ __launch_bounds__(kBlock) void group_place_kernel(GroupOrderArgs A, u
     uint4 *cw = reinterpret_cast<uint4 *>(count + (size_t)b * kSub);
     uint32_t c[kSub], sum = 0;
     static_assert(kSub == 4, "one load");
-    const uint4 v = b < bins ? cw[0] : uint4{~0u, ~0u, ~0u, ~0u};
+    const uint4 v = b < 2u * bins ? cw[0] : uint4{~0u, ~0u, ~0u, ~0u};
     c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
 #pragma unroll
     for (uint32_t i = 0; i < kSub; ++i) sum += bin_count(c[i]);
-    const bool take = sum > 0u && sum >= A.minrun;
+    const bool take = b < bins && sum > 0u && sum >= A.minrun;
     const uint32_t ng = take ? (sum + kGroupMax - 1u) / kGroupMax : 0u;
     const uint32_t mine[3] = {ng, take ? sum : 0u, take ? 0u : sum};  // as gcount's words
     uint32_t x[3] = {mine[0], mine[1], mine[2]};
@@ -222,7 +225,7 @@ __global__ __launch_bounds__(kBlock) void group_place_kernel(GroupOrderArgs A, u
         s_base[tid] = t ? atomicAdd(A.gcount + tid, t) : 0u;
     }
     __syncthreads();
-    if (b >= bins) return;
+    if (b >= 2u * bins) return;
     uint32_t at[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -262,20 +265,14 @@ __device__ inline void append_classes(const GroupOrderArgs &A, int64_t q)
     if (q >= 0) A.order[base[cls] + p] = (int32_t)q;
 }
 
-// Every query with a bin to its place in gorder, the others to their classes.
+// Every query to its place in gorder.
 __global__ __launch_bounds__(kBlock) void group_scatter_kernel(GroupOrderArgs A, const uint32_t *__restrict__ place)
 {
     const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    bool rest = false;
-    if (q < A.Q) {
-        const uint2 b = A.bin[q];
-        rest = b.x == 0xFFFFFFFFu;
-        if (!rest) {
-            const uint32_t at = place[b.x] + b.y;
-            A.gorder[at & kBack ? A.Q - 1 - (int64_t)(at & ~kBack) : (int64_t)at] = (int32_t)q;
-        }
-    }
-    append_classes(A, rest ? q : -1);
+    if (q >= A.Q) return;
+    const uint2 b = A.bin[q];
+    const uint32_t at = place[b.x] + b.y;
+    A.gorder[at & kBack ? A.Q - 1 - (int64_t)(at & ~kBack) : (int64_t)at] = (int32_t)q;
 }
 
 // The queries at the back of gorder to their classes: queries of one label stay
@@ -297,11 +294,11 @@ uint32_t group_bins(int64_t Q)
 }
 size_t group_table_bytes(int64_t Q)
 {
-    return sizeof(uint32_t) * (2 * (size_t)kLabelSlots + (size_t)group_bins(Q) * kSub);
+    return sizeof(uint32_t) * (2 * (size_t)kLabelSlots + 2 * (size_t)group_bins(Q) * kSub);
 }
 
 // Order of a workload whose queries share workgroups.  tab: the slots' owners and
-// labels (64 slots a query, kLabelSlots at most), then the bins.  100,000 queries:
+// labels (64 slots a query, kLabelSlots at most), then the bins, twice.  100,000 queries:
 // 0.12 ms (sorting them by class, label and t took 0.3).
 qw_status launch_group_order(const GroupOrderArgs &a, uint32_t *tab, hipStream_t s)
 {
@@ -311,21 +308,19 @@ qw_status launch_group_order(const GroupOrderArgs &a, uint32_t *tab, hipStream_t
     while (slots < kLabelSlots && (int64_t)slots < 64 * a.Q) slots <<= 1;
     const uint32_t bins = group_bins(a.Q);
     uint32_t *count = tab + 2 * (size_t)slots;
-    QW_TRY(launch_fill_u32(tab, 0xFFFFFFFFu, 2 * (int64_t)slots + (int64_t)bins * kSub, s));
+    QW_TRY(launch_fill_u32(tab, 0xFFFFFFFFu, 2 * (int64_t)slots + 2 * (int64_t)bins * kSub, s));
     constexpr int wpb = kBlock / 64;
     const int32_t step = (int32_t)std::max<int64_t>(1, a.Q / kLabelSample);
     label_kernel<<<(unsigned)ceil_div(ceil_div(a.Q, step), wpb), kBlock, 0, s>>>(a.Q, a.L, step, a.bmh, slots, tab, tab + slots);
     QW_HIP(hipGetLastError());
     group_bin_kernel<<<(unsigned)ceil_div(a.Q, kBinBlock), kBlock, 0, s>>>(a, slots, bins, tab, count);
     QW_HIP(hipGetLastError());
-    group_place_kernel<<<(unsigned)ceil_div(bins, kBlock), kBlock, 0, s>>>(a, bins, count);
+    group_place_kernel<<<(unsigned)ceil_div(2 * (int64_t)bins, kBlock), kBlock, 0, s>>>(a, bins, count);
     QW_HIP(hipGetLastError());
     group_scatter_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a, count);
     QW_HIP(hipGetLastError());
-    if (a.minrun > 1) {
-        group_rest_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a);
-        QW_HIP(hipGetLastError());
-    }
+    group_rest_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a);
+    QW_HIP(hipGetLastError());
     return QW_OK;
 }
 

@@ -735,6 +735,29 @@ def test_grouped_uint8_queries(n, d, Q, ncl, L, k, w, K, probes):
                     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("dtype", ["u8", "f32"])
+@pytest.mark.parametrize("Q,big", [(257, 9000), (1025, 9000), (1025, 0)])
+def test_grouped_order_classes_beyond_groups(dtype, Q, big):
+    """Queries whose class no group takes, beside ones that share (big: the points
+    of one large cluster, listed by half of the queries), and no binning at all."""
+    data, q = grouped_workload(Q + big, 4000, 48, Q, 10, 0.02)
+    if big:
+        more, qm = grouped_workload(7, big, 48, Q // 2, 1, 0.02)
+        data, q = np.concatenate([data, more]), np.concatenate([q[Q // 2:], qm])
+    w = 4.0
+    if dtype == "u8":
+        data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+        w *= 255
+    p = synth.hash_params(5, 6, 4, 48, w)
+    ix = build(data, p.a, p.b(), w)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, 10)
+    for sched in (lib.QW_SCHED_SUM, lib.QW_SCHED_NONE):
+        for graph in (0, 1):
+            ids, dist, st = ix.query(dev(q), 10, lib.make_opts(group=1, sched=sched, graph=graph), stats=True)
+            check_topk(ids, dist, ids_o, dist_o, dtype == "u8")
+            assert st["cand_unique"] == int(cnt_o.sum())
+
+
 def test_huge_w_equals_bruteforce():
     """Every point in one bucket per layer: LSH top-K equals exact kNN."""
     rng = np.random.default_rng(61)
