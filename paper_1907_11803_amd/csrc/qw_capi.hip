@@ -58,8 +58,11 @@ constexpr uint32_t kMinRun = 8, kShareGain = 8, kShareListed = 1024;
 // 157 and 162 -> 158.  Where a wave would take a query it is one launch fewer, and
 // as fast for few listed ids: a single query 64 us by a wave and 65 so, ten that
 // list 450 ids each 61 and 71; so only from nl * mean_hit_bucket = kWideListed on
-// (at 650 both took 95 us, at 1,450 148 and 105).
-constexpr int64_t kWideQueries = 512;
+// (at 650 both took 95 us, at 1,450 148 and 105).  Waves fill the chip from 513
+// queries on (576 probed ones 120 us by them, 133 so), workgroups of 256 threads
+// only from 769, the fourth round of large ones: 576 of the plain union 133 and
+// 127, 768 of 300,007 x 100 with K = 100 136 and 130 but 832 139 and 143.
+constexpr int64_t kWideQueries = 512, kWideBlockQueries = 768;
 constexpr double kWideListed = 700.0;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
@@ -1420,7 +1423,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             resolve_fast_auto(ix, Q, K, &built, nullptr);
             chosen = eff.dedup != built.dedup || eff.group != built.group || eff.xchunk != built.xchunk;
         }
-        const bool wide = Q <= kWideQueries && !chosen && !share &&
+        const bool wide = Q <= (eff.dedup == 1 ? kWideBlockQueries : kWideQueries) && !chosen && !share &&
                           eff.stage_split <= 0 && ix->nl <= 64 &&
                           (eff.dedup == 1 || (Q > 1 && ix->nl * ix->mean_hit_bucket >= kWideListed));
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,

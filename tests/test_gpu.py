@@ -616,7 +616,7 @@ def grouped_workload(seed, n, d, Q, ncl, spread, far=0):
     return np.clip(data, 0, 1).astype(np.float32), q.astype(np.float32)
 
 
-@pytest.mark.parametrize("Q", [1, 2, 512, 513])  # a large workgroup per query up to 512
+@pytest.mark.parametrize("Q", [1, 2, 512, 513, 768, 769])  # a large workgroup per query up to 512 or 768
 @pytest.mark.parametrize("n,d,ncl,w,K,dtype", [
     (6000, 64, 6, 700.0, 10, "u8"), (6000, 48, 6, 500.0, 40, "u8"),        # in-kernel top K; key lists
     (9000, 32, 1, 9000.0, 10, "u8"), (40000, 16, 1, 9000.0, 3, "u8"),      # the largest sets; beyond them
