@@ -31,7 +31,8 @@ struct RankF {
 //    float: the K-th key of the list fixes the band, every entry in the band is
 //    re-ranked by its FP64 index-order distance (the c-k-ANN output, Section 3).
 // A list or band beyond capacity sends the query to the fallback.
-template <int DT>
+// SHARED: queries that shared a workgroup (kroom) are among them.
+template <int DT, bool SHARED>
 __device__ inline void select_query(const SelectArgs &A, const int64_t q, unsigned char *smem)
 {
     unsigned long long *lst = reinterpret_cast<unsigned long long *>(smem);
@@ -44,7 +45,7 @@ __device__ inline void select_query(const SelectArgs &A, const int64_t q, unsign
     // the flag, the count and the range offset load together (uniform)
     const uint32_t bad = A.flag[q];
     // keys written: the candidates, or fewer (queries that shared a workgroup)
-    const uint32_t room = A.kroom ? A.kroom[q] : 0u;
+    const uint32_t room = SHARED ? A.kroom[q] : 0u;
     const uint32_t U = room ? A.kcount[q] : A.ucount[q];
     const unsigned long long coff = A.coff[q];
     const float err = DT == QW_F32 && A.abs_err ? A.abs_err[q] : 0.f;
@@ -214,13 +215,13 @@ __device__ inline void select_query(const SelectArgs &A, const int64_t q, unsign
     }
 }
 
-template <int DT>
+template <int DT, bool SHARED>
 __global__ __launch_bounds__(kBlock) void select_kernel(SelectArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     // (one query per workgroup: looping over several cost a quarter more)
     if (A.qlist && blockIdx.x >= *A.qcount) return;  // uniform
-    select_query<DT>(A, A.qlist ? A.qlist[blockIdx.x] : (int64_t)blockIdx.x, smem);
+    select_query<DT, SHARED>(A, A.qlist ? A.qlist[blockIdx.x] : (int64_t)blockIdx.x, smem);
 }
 
 // The key list holds LC >= 4K entries (also room for the ceil(K / kBlock) *
@@ -237,10 +238,10 @@ qw_status launch_select(const SelectArgs &a, int64_t Q, hipStream_t s)
 {
     if (Q <= 0) return QW_OK;
     const size_t lds = select_lds_bytes(a.LC, a.dtype, a.dp);
-    if (a.dtype == QW_U8)
-        select_kernel<QW_U8><<<(unsigned)Q, kBlock, lds, s>>>(a);
-    else
-        select_kernel<QW_F32><<<(unsigned)Q, kBlock, lds, s>>>(a);
+    const bool u8 = a.dtype == QW_U8, shared = a.kroom != nullptr;
+    auto *kernel = u8 ? (shared ? select_kernel<QW_U8, true> : select_kernel<QW_U8, false>)
+                      : (shared ? select_kernel<QW_F32, true> : select_kernel<QW_F32, false>);
+    kernel<<<(unsigned)Q, kBlock, lds, s>>>(a);
     QW_HIP(hipGetLastError());
     return QW_OK;
 }
