@@ -888,7 +888,9 @@ __global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_ke
         }
         __syncthreads();
         const int cols = (keep >> 16) ? 32 : 16;
-        stage_queries<DT>(A, s_q, keep, rec.j0, pc == 0u, qp, q0s, s_qn, s_err);
+        // (the piece of the first rows: pieces before it are empty where there are
+        // fewer tiles than pieces)
+        stage_queries<DT>(A, s_q, keep, rec.j0, r0 == 0u, qp, q0s, s_qn, s_err);
         for (int j = tid; j < cols; j += kVB<DT>) {
             const int32_t q = s_q[j];
             if ((keep >> j) & 1u) {
@@ -955,7 +957,7 @@ __global__ __launch_bounds__(kVB<QW_F32>, 3) void dense_verify_kernel(GroupedArg
             s_base[tid] = (unsigned long long)q * D.cap;
         }
         __syncthreads();
-        stage_queries<QW_F32>(A, s_q, keep, 0, !D.bound && pc == 0u, qp, q0s, s_qn, s_err);
+        stage_queries<QW_F32>(A, s_q, keep, 0, !D.bound && r0 == 0, qp, q0s, s_qn, s_err);
         __syncthreads();
         VerifyGroup G = {nullptr, (uint32_t)(r1 - r0), keep, qp, q0s, s_qn, nullptr, s_thr, s_err,
                          s_base, s_room, nullptr, s_q, true, r0 * D.stride, D.stride};

@@ -704,6 +704,32 @@ def test_group_key_bound(K, n, Q, same):
     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("Q,n", [(2, 33), (5, 96), (32, 320), (32, 480), (40, 200), (32, 544)])
+@pytest.mark.parametrize("K", [1, 5])
+def test_group_error_band_of_few_rows(Q, n, K):
+    """One group of few rows (fewer tiles of 32 than pieces of a record up to 480),
+    every query with near duplicates whose distances differ by less than the
+    error of its keys, which its distance to the group's first query sets; then
+    queries beyond FP32's range in a column that no hash function reads."""
+    rng = np.random.default_rng(Q + n)
+    d, w = 256, 1000.0
+    q = rng.random((Q, d), dtype=np.float32)
+    near = q + rng.normal(0, 0.006, (Q, d)).astype(np.float32)
+    data = near[np.arange(n) % Q] + rng.normal(0, 1e-6, (n, d)).astype(np.float32)
+    p = synth.hash_params(5, 3, 2, d, w)
+    p.a[:, :, -1] = 0
+    ix = build(data, p.a, p.b(), w)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1), stats=True)
+    check_topk(ids, dist, ids_o, dist_o, False)
+    assert st["cand_unique"] == int(cnt_o.sum())
+    q[-1, -1], q[Q // 2, -1] = 1e25, np.inf
+    want = ix.query(dev(q), K, lib.make_opts(form=lib.QW_FORM_PLAIN_FP32))
+    got = ix.query(dev(q), K, lib.make_opts(group=1))
+    for g, v in zip(got, want):
+        assert np.array_equal(g.cpu().numpy(), v.cpu().numpy(), equal_nan=True)
+
+
 @pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K,probes", [
     (6000, 32, 1024, 12, 6, 4, 600.0, 10, 0),   # the smallest workload that shares
     (6000, 100, 1500, 12, 8, 6, 2000.0, 16, 0),  # ragged rows, largest in-kernel K
