@@ -501,18 +501,10 @@ qw_status ooc_query(qw_index *ix, int64_t Q, int K, hipStream_t s, int32_t *out_
     return ooc_answer(ix, Q, a, ix->ws.qrows, out_ids, out_dist, s, io);
 }
 
-// Room for one round of queries; false when the device has none, or when the
-// stream is being captured and the room is not there yet (the per-query
-// kernel, which needs no lists, answers then).
-bool ensure_round(qw_index *ix, size_t bmin, size_t bkeys, size_t bstate, hipStream_t s)
+// Room for one round of queries; false when the device has none.
+bool ensure_round(qw_index *ix, size_t bmin, size_t bkeys, size_t bstate)
 {
     Workspace &w = ix->ws;
-    if (w.bf_min.bytes >= bmin && w.bf_keys.bytes >= bkeys && w.bf_state.bytes >= bstate) return true;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;
-    }
     if (w.bf_min.ensure(bmin) == QW_OK && w.bf_keys.ensure(bkeys) == QW_OK &&
         w.bf_state.ensure(bstate) == QW_OK)
         return true;
@@ -522,22 +514,34 @@ bool ensure_round(qw_index *ix, size_t bmin, size_t bkeys, size_t bstate, hipStr
     return false;
 }
 
-bool ensure_brute(qw_index *ix, const BrutePlan &p, hipStream_t s)
+// A call that is being captured (or whose state is not known) takes the
+// per-query kernel, which needs no lists: the library does not see the graph's
+// replays, so it could neither keep the lists in place for them nor order them
+// against other calls.
+bool captured(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+bool ensure_brute(qw_index *ix, const BrutePlan &p)
 {
     const size_t q = (size_t)p.chunk;
     // state per query: bound, count, flag, fallback entry, list offset; then
     // the fallback queue's length and work counter
     return ensure_round(ix, sizeof(int32_t) * q * (size_t)p.streams, sizeof(unsigned long long) * q * (size_t)p.cap,
-                        q * (4 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256, s);
+                        q * (4 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256);
 }
 
-bool ensure_dense(qw_index *ix, const DensePlan &p, hipStream_t s)
+bool ensure_dense(qw_index *ix, const DensePlan &p)
 {
     const size_t q = (size_t)p.chunk;
     // state per query: list offset; flag, keys, error, room, bound, fallback
     // entry; then the fallback queue's length and work counter
     return ensure_round(ix, 0, sizeof(unsigned long long) * q * (size_t)p.cap,
-                        q * (6 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256, s);
+                        q * (6 * sizeof(uint32_t) + sizeof(unsigned long long)) + 256);
 }
 
 // What both brute-force forms leave behind: the select kernel's setup for a
@@ -1606,11 +1610,18 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     a.nl = 0;  // no bucket lists: every point
     a.pmagic = 0;
     BrutePlan bp;
-    if (brute_plan(ix->n, ix->dtype, ix->dp, Q, K, &bp) && ensure_brute(ix, bp, s))
-        return brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist));
     DensePlan dp;
-    if (dense_plan(ix->n, ix->dtype, ix->dp, Q, K, ix->lds_max, &dp) && ensure_dense(ix, dp, s))
-        return brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));
+    const bool mfma = brute_plan(ix->n, ix->dtype, ix->dp, Q, K, &bp);
+    const bool dense = !mfma && dense_plan(ix->n, ix->dtype, ix->dp, Q, K, ix->lds_max, &dp);
+    if ((mfma || dense) && !captured(s) && (mfma ? ensure_brute(ix, bp) : ensure_dense(ix, dp))) {
+        // the key lists are the index's: after the call that used them last,
+        // whose stream may be another
+        QW_HIP(hipStreamWaitEvent(s, ix->brute, 0));
+        const qw_status rc = mfma ? brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist))
+                                  : brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));
+        QW_HIP(hipEventRecord(ix->brute, s));
+        return rc;
+    }
     a.nitems = Q;
     a.cap_log2 = 1;
     a.limit = 1;

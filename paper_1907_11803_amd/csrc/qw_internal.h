@@ -278,6 +278,9 @@ struct qw_index {
     // classes run beside the merged launch
     hipStream_t side = nullptr;
     hipEvent_t fork[3] = {};
+    // end of the last brute force that used the key lists (Workspace::bf_*): the
+    // next one, on whatever stream, waits for it
+    hipEvent_t brute = nullptr;
     // tuning cache: the file last named by a call, read once, and the
     // device's architecture name
     std::string tune_path, tune_arch;
@@ -292,6 +295,7 @@ struct qw_index {
     {
         for (auto &e : fork)
             if (e) (void)hipEventDestroy(e);
+        if (brute) (void)hipEventDestroy(brute);
         if (side) (void)hipStreamDestroy(side);
     }
 };

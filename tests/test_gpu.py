@@ -606,6 +606,39 @@ def test_bruteforce_matrix_cores_key_lists(kind):
     check_topk(ids, dist, ids_o, dist_o, True)
 
 
+@pytest.mark.parametrize("dtype", ["u8", "f32"])
+def test_bruteforce_streams_and_capture(dtype):
+    """Calls on one index from two streams, one enqueued after the other without a
+    wait between them, and a captured call that is replayed after larger calls."""
+    data, q = grouped_workload(21, 30000, 64, 300, 20, 0.05)
+    if dtype == "u8":
+        data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+    p = synth.hash_params(3, 1, 1, 64, 1000.0)
+    ix = build(data, p.a, p.b(), 1000.0)
+    part = [q[:300], q[100:117]]
+    want = [oracle.bruteforce(data, v, 10) for v in part]
+    qd = [dev(v) for v in part]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    ix.bruteforce(qd[0], 10)
+    torch.cuda.synchronize()
+    got = []
+    for i in range(40):
+        with torch.cuda.stream(streams[i % 2]):
+            got.append(ix.bruteforce(qd[i % 2], 10))
+    torch.cuda.synchronize()
+    for i, (ids, dist) in enumerate(got):
+        check_topk(ids, dist, *want[i % 2], dtype == "u8")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ids, dist = ix.bruteforce(qd[1], 10)
+    for K in (10, 100, 1000):
+        ix.bruteforce(qd[0], K)  # longer lists: the workspace moves
+        ids.zero_(), dist.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        check_topk(ids, dist, *want[1], dtype == "u8")
+
+
 def grouped_workload(seed, n, d, Q, ncl, spread, far=0):
     """Float clusters and queries near few of them, so that candidate sets overlap."""
     rng = np.random.default_rng(seed)
