@@ -173,8 +173,10 @@ bool group_shares(const qw_index *ix, int32_t K, const qw_opts &eff)
            (double)ix->L * ix->mean_hit_bucket >= (double)kShareListed;
 }
 
-qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false, int64_t group_q = 0,
-                    int group_k = 0)
+// keys: key lists for the select kernel, the order dealt to the XCDs xchunk
+// queries at a time; group_q: the queries that may share workgroups.
+qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false, int64_t xchunk = 1,
+                    int64_t group_q = 0, int group_k = 0)
 {
     Workspace &w = ix->ws;
     auto ptrs = [&w]() {
@@ -239,11 +241,17 @@ qw_status ensure_ws(qw_index *ix, int64_t Q, const Plan *plan, bool keys = false
         if (plan) {
             const size_t g = (size_t)plan->grid_g * (size_t(1) << plan->cap_g) * 4;
             QW_TRY(grow(w.gscratch, g));
-            // one equal region per XCD, each with room for its share of the
-            // queries plus one chunk of items per dedup launch (at most ncls + 1),
-            // but no more than all of them (few queries: 600 MB of slack otherwise)
-            const int64_t share = std::min<int64_t>(q, ceil_div(q, kXcd) + (int64_t)kXcdChunk * (plan->ncls + 1));
-            const int64_t cand_cap = std::max<int64_t>(kXcd * share * kCandPerQuery, 1 << 20);
+            // one equal region per XCD: its share of the queries and one chunk of
+            // them per dedup launch (at most ncls + 1) at all the candidates they
+            // can have, or kCandPerQuery for each and for kXcdChunk per launch,
+            // whichever is less (64 queries of 100,000 x 64 float rows, all of them
+            // candidates: 12.5 ms; with kCandPerQuery for each of the 64 alone 48
+            // overflowed their regions into the fallback, 26.7)
+            const int64_t share = ceil_div(q, kXcd), launches = plan->ncls + 1;
+            const int64_t most = std::min<int64_t>(ix->n, (int64_t)ix->nl * ix->max_bucket);
+            const int64_t region = std::min((share + (int64_t)kXcdChunk * launches) * kCandPerQuery,
+                                            std::min(q, share + xchunk * launches) * most);
+            const int64_t cand_cap = std::max<int64_t>(kXcd * region, 1 << 20);
             QW_TRY(grow(w.coff, sizeof(unsigned long long) * q));
             QW_TRY(grow(w.flag, 4 * sizeof(uint32_t) * q));
             if (keys) QW_TRY(grow(w.pkeys, sizeof(unsigned long long) * cand_cap));
@@ -1431,7 +1439,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
                           eff.stage_split <= 0 && ix->nl <= 64 &&
                           (eff.dedup == 1 || (Q > 1 && ix->nl * ix->mean_hit_bucket >= kWideListed));
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,
-                         share ? Q : 0, K));
+                         (eff.group && !wide) || eff.stage_split > 0 ? kXcdChunk : 1, share ? Q : 0, K));
         if (opt.timing || !opt.graph) {
             QW_TRY(enqueue_fast(ix, plan, queries, Q, K, eff, share, wide, s, out_ids, out_dist,
                                 opt.timing ? ix->ev : nullptr));

@@ -669,6 +669,27 @@ def test_few_queries(Q, n, d, ncl, w, K, dtype):
             assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("Q,n,K,dtype,group", [
+    (1, 140000, 10, "f32", 0), (64, 40000, 10, "f32", 0), (20, 120000, 3, "f32", 0),  # dealt one by one
+    (64, 9000, 10, "f32", 1), (300, 9000, 10, "f32", 1),                              # in chunks of 256
+    (64, 40000, 17, "u8", 0), (64, 40000, 17, "u8", 1),
+])
+def test_key_space_of_few_queries(Q, n, K, dtype, group):
+    """Every point a candidate of every query: their keys fit the XCDs' regions."""
+    data, q = grouped_workload(n + Q, n, 16, Q, 1, 0.08)
+    w = 50.0
+    if dtype == "u8":
+        data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+        w = 9000.0
+    p = synth.hash_params(5, 3, 2, 16, w)
+    ix = build(data, p.a, p.b(), w)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    assert (cnt_o == n).all()
+    ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=group), stats=True)
+    check_topk(ids, dist, ids_o, dist_o, dtype == "u8")
+    assert st["fallback"] == 0
+
+
 @pytest.mark.parametrize("m", [1, 15, 17, 8192, 8193])  # rows split over waves up to 8,192
 @pytest.mark.parametrize("d,L,k", [(16, 1, 1), (60, 7, 9), (64, 4, 16), (530, 5, 13), (960, 16, 12)])
 def test_float_query_hashing(m, d, L, k):
