@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kBlock, 2) void brute_kernel(BruteArgs A)
 
 // One workgroup per query: the K-th smallest of its `streams` minima (at most
 // 32 per thread), by a radix search from the top bit, and the query's list
-// state cleared.
+// state cleared, with the round's fallback queue.
 constexpr int kMinPerThread = 32;
 __global__ __launch_bounds__(kBlock) void brute_bound_kernel(BruteArgs A)
 {
@@ -300,6 +300,7 @@ __global__ __launch_bounds__(kBlock) void brute_bound_kernel(BruteArgs A)
         A.count[q] = 0u;
         A.flag[q] = 0u;
         A.coff[q] = (unsigned long long)q * A.cap;
+        if (q == 0) A.fb_count[0] = A.fb_count[1] = 0u;
     }
 }
 

@@ -654,7 +654,7 @@ qw_status brute_mfma(qw_index *ix, const BrutePlan &p, VerifyArgs fb, int64_t Q,
         a.flag = flag;
         a.coff = coff;
         a.keys = w.bf_keys.as<unsigned long long>();
-        QW_TRY(launch_fill_u32(fb_count, 0u, 2, s));
+        a.fb_count = fb_count;
         QW_TRY(launch_brute(p, a, s));
         SelectArgs m;
         std::memset(&m, 0, sizeof(m));
@@ -1623,7 +1623,7 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     const bool dense = !mfma && dense_plan(ix->n, ix->dtype, ix->dp, Q, K, ix->lds_max, &dp);
     if ((mfma || dense) && !captured(s) && (mfma ? ensure_brute(ix, bp) : ensure_dense(ix, dp))) {
         // the key lists are the index's: after the call that used them last,
-        // whose stream may be another
+        // whose stream may be another (the event costs 5 us of such calls)
         QW_HIP(hipStreamWaitEvent(s, ix->brute, 0));
         const qw_status rc = mfma ? brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist))
                                   : brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));

@@ -667,6 +667,7 @@ struct BruteArgs {
     int32_t *minima;             // [Q][streams]
     int32_t *bound;              // [Q]: at least the K-th distance
     uint32_t *count, *flag;      // [Q]: keys found; 1: left to the per-query kernel
+    uint32_t *fb_count;          // its queue's length and work counter (cleared here)
     unsigned long long *coff, *keys;  // [Q]: the query's first key; [Q][cap] (distance << 32) | id
 };
 // false: not applicable (the per-query kernel answers).
