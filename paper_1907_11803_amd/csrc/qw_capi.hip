@@ -153,10 +153,12 @@ bool group_held(const qw_index *ix, int64_t Q)
 }
 
 // Keys held per query of a group: about 16 K pass the bound of a group's first
-// rows; a query with more goes to the fallback.  Beyond the bound's K, all.
+// rows; a query with more goes to the fallback.  Up to 16 pieces of a record bound
+// their keys separately, and one of fewer than K / 8 tiles (8 minima each) writes
+// them all: 16 pieces of K / 8 tiles of 32 rows are 64 K.  Beyond the bound's K, all.
 uint32_t grouped_keys(int dtype, int K)
 {
-    return K <= group_filter_topk(dtype) ? (uint32_t)std::min(2048, std::max(512, 64 * K)) : 0xFFFFFFFFu;
+    return K <= group_filter_topk(dtype) ? (uint32_t)std::max(512, 64 * K) : 0xFFFFFFFFu;
 }
 
 // Do a workload's queries share workgroups?  In the grouped order, of float rows

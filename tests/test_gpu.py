@@ -690,6 +690,21 @@ def test_key_space_of_few_queries(Q, n, K, dtype, group):
     assert st["fallback"] == 0
 
 
+@pytest.mark.parametrize("K", [33, 41, 44, 48, 49])  # bounded up to 48
+@pytest.mark.parametrize("n", [2050, 2600, 2900, 3200])
+def test_group_pieces_of_few_tiles(K, n):
+    """Few groups, whose pieces have fewer minima than K or just as many: the keys
+    they write fit a query's room."""
+    data, q = grouped_workload(K + n, n, 64, 40, 1, 0.05)
+    p = synth.hash_params(5, 3, 2, 64, 50.0)
+    ix = build(data, p.a, p.b(), 50.0)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), 50.0, K)
+    assert (cnt_o == n).all()
+    ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1), stats=True)
+    check_topk(ids, dist, ids_o, dist_o, False)
+    assert st["fallback"] == 0
+
+
 @pytest.mark.parametrize("m", [1, 15, 17, 8192, 8193])  # rows split over waves up to 8,192
 @pytest.mark.parametrize("d,L,k", [(16, 1, 1), (60, 7, 9), (64, 4, 16), (530, 5, 13), (960, 16, 12)])
 def test_float_query_hashing(m, d, L, k):
