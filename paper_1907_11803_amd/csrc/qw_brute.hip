@@ -37,7 +37,14 @@ namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-constexpr int kHitBuf = 1024;            // LDS hit buffer of a workgroup
+// LDS hit buffer of a workgroup.  A tile of 128 points and 512 queries has about
+// 65,536 K r / n hits of its own (K r keys per query of n rows; half a buffer may
+// be left from tiles before it): what the buffer does not hold goes to the lists
+// directly, up to kHitMax (beyond it many rows are equal, and such queries
+// overflow their lists anyway: they take no more).  500 queries, K = 1000, over 200,000 x 128: 2.75
+// ms with a workgroup per query, 3.43 when a hit beyond the buffer sent its query
+// there after this kernel, 0.75 now.
+constexpr int kHitBuf = 1024, kHitMax = 2 * kHitBuf;
 constexpr int32_t kNoPoint = 0x7FFFFFFE;  // |x'|^2 of a row past the end: never within a bound
 
 // 16 bytes of a row as signed bytes; zeros past the row's parts (both
@@ -155,6 +162,11 @@ __global__ __launch_bounds__(kBlock, 2) void brute_kernel(BruteArgs A)
             xr[i] = data[row * parts + (p < parts ? p : parts - 1)];
         }
     };
+    auto append = [&](int32_t q, unsigned long long key) {
+        const uint32_t pos = atomicAdd(&A.count[q], 1u);
+        if (pos < A.cap) A.keys[(int64_t)q * A.cap + pos] = key;
+        else A.flag[q] = 1u;
+    };
     if (t0 < t1) load_tile(t0);
     for (int32_t t = t0; t < t1; ++t) {
         __syncthreads();  // the previous tile has been read
@@ -224,8 +236,11 @@ __global__ __launch_bounds__(kBlock, 2) void brute_kernel(BruteArgs A)
                             if (e < (uint32_t)kHitBuf) {
                                 hkey[e] = ((unsigned long long)(uint32_t)dist << 32) | (uint32_t)row;
                                 hq[e] = q;
-                            } else {
-                                A.flag[q] = 1u;  // more hits in a tile than the buffer holds
+                            } else if (e < (uint32_t)kHitMax) {  // to the query's list at once
+                                append(q, ((unsigned long long)(uint32_t)dist << 32) | (uint32_t)row);
+                            } else {  // equal rows: no more of this query here
+                                A.flag[q] = 1u;
+                                best[c] = INT32_MAX;
                             }
                         }
                     }
@@ -235,13 +250,10 @@ __global__ __launch_bounds__(kBlock, 2) void brute_kernel(BruteArgs A)
         if (COLLECT) {
             __syncthreads();
             const uint32_t nh = hcnt < (uint32_t)kHitBuf ? hcnt : (uint32_t)kHitBuf;
+            const bool over = hcnt > (uint32_t)kHitMax;  // some queries are flagged
             if (nh > (uint32_t)kHitBuf / 2 || (t + 1 == t1 && nh)) {  // uniform
-                for (uint32_t e = tid; e < nh; e += kBlock) {
-                    const int32_t q = hq[e];
-                    const uint32_t pos = atomicAdd(&A.count[q], 1u);
-                    if (pos < A.cap) A.keys[(int64_t)q * A.cap + pos] = hkey[e];
-                    else A.flag[q] = 1u;
-                }
+                for (uint32_t e = tid; e < nh; e += kBlock)
+                    if (!over || A.flag[hq[e]] == 0u) append(hq[e], hkey[e]);
                 __syncthreads();
                 if (tid == 0) hcnt = 0;
             }

@@ -533,6 +533,20 @@ def test_bruteforce_matrix_cores(n, d, Q, K):
         check_topk(ids, dist, ids_o, dist_o, True)
 
 
+@pytest.mark.parametrize("n,d,Q,K", [(16000, 128, 512, 200), (16000, 100, 530, 250), (33000, 80, 512, 500)])
+def test_bruteforce_hits_beyond_a_buffer(n, d, Q, K):
+    """Long result lists over few rows: a tile's hits exceed a workgroup's buffer."""
+    rng = np.random.default_rng(n + K)
+    data = rng.integers(0, 256, (n, d), dtype=np.uint8)
+    queries = rng.integers(0, 256, (Q, d), dtype=np.uint8)
+    queries[7] = data[5]
+    p = synth.hash_params(3, 1, 1, d, 1000.0)
+    ix = build(data, p.a, p.b(), 1000.0)
+    ids_o, dist_o = oracle.bruteforce(data, queries, K)
+    ids, dist = ix.bruteforce(dev(queries), K)
+    check_topk(ids, dist, ids_o, dist_o, True)
+
+
 @pytest.mark.parametrize("n,d,Q,K", [
     (2048, 16, 1, 1), (4096, 20, 33, 10), (2047, 30, 5, 10),             # every key; not applicable
     (4097, 17, 16, 10), (5001, 64, 17, 1), (9000, 100, 64, 64),          # sampled
