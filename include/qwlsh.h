@@ -88,9 +88,10 @@ typedef struct {
                           bucket's smallest mixed id) and deal the order to the XCDs in
                           chunks, so queries with overlapping candidates share an L2,
                           0 = no bucket ordering, -1 = automatic (default): ordering for
-                          rows of 1024 bytes or more or workloads of 32768 queries or
-                          more, where neighbouring queries share the rows they verify
-                          in cache */
+                          rows of 1024 bytes or more (float rows: where a query lists
+                          about 1000 ids, or there are many) or workloads of 32768
+                          queries or more, where neighbouring queries share the rows
+                          they verify */
     int32_t graph;     /* fast form: 1 = capture/replay the query pipeline as a HIP graph */
     int32_t timing;    /* 1 = record per-stage HIP events and report them in qw_stats (syncs) */
     int32_t topk_keep; /* fast form, uint8 rows of at most 1024 bytes, K <= 16: the dedup kernel

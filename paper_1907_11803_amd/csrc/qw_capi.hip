@@ -52,6 +52,16 @@ constexpr int kGroupedSetLog2 = 14;
 // ids each (150,000 x 50) took 0.58 ms query by query, 0.73 shared; 59,000 that
 // list 1,660 (460,000 x 73) 1.24 and 0.79.
 constexpr uint32_t kMinRun = 8, kShareGain = 8, kShareListed = 1024;
+// Float rows: finding the groups and their two kernels cost about 60 us, and the
+// fewer rows a query has the less of them a group shares: queries share from
+// kShareListed ids each on, or where their number times the square of the ids and
+// the bytes of a row is kShareWork.  In the order of before and shared: 200,000 x 256, 1,000 queries of
+// 265 ids 206 and 277 us, 8,000 430 and 492, 16,000 633 and 619; of 990, one query 112
+// and 132, 1,000 252 and 254, 4,000 411 and 341; 200,000 x 512, 1,000 of 500 293 and
+// 332, 4,500 581 and 487; 200,000 x 960, 16,000 of 167 1,205 and 1,381, 64,000 3,735
+// and 3,449; 200,000 x 64, 9,000 of 690 377 and 414; 200,000 x 256, one query of
+// 2,430 146 and 130.
+constexpr double kShareWork = double(int64_t(1) << 41);
 // Queries up to which each takes one workgroup of 1,024 threads, whole calls (two
 // probes over 1M x 128, by a wave per query before; the plain union, by 256 threads):
 // 64 queries 99 -> 75 us and 128 -> 73, 512 120 -> 116 and 133 -> 110, 1,024 123 ->
@@ -161,18 +171,26 @@ uint32_t grouped_keys(int dtype, int K)
     return K <= group_filter_topk(dtype) ? (uint32_t)std::max(512, 64 * K) : 0xFFFFFFFFu;
 }
 
+// Ids that a query lists: a data point of the collection L * mean_hit_bucket.
+double listed_ids(const qw_index *ix) { return (double)ix->L * ix->mean_hit_bucket; }
+
+// Float queries list enough for sharing a workgroup to pay.
+bool float_shares(const qw_index *ix, int64_t Q)
+{
+    const double ids = listed_ids(ix);
+    return ids >= (double)kShareListed || (double)Q * ids * ids * 4.0 * ix->dp >= kShareWork;
+}
+
 // Do a workload's queries share workgroups?  In the grouped order, of float rows
-// always (what a row's reuse saves is large), of uint8 rows those groups whose
-// queries list the same buckets often enough (kShareGain) -- and only where a
-// query lists enough ids for it to pay (a data point of the collection lists
-// L * mean_hit_bucket; finding the groups costs 30 us more than the plain order).
-bool group_shares(const qw_index *ix, int32_t K, const qw_opts &eff)
+// where it pays (float_shares), of uint8 rows those groups whose queries list the
+// same buckets often enough (kShareGain) -- and only where a query lists enough
+// ids for it to pay (finding the groups costs 30 us more than the plain order).
+bool group_shares(const qw_index *ix, int64_t Q, int32_t K, const qw_opts &eff)
 {
     if (eff.stage_split > 0 || !group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max)) return false;
     if (!eff.group) return false;
-    if (ix->dtype == QW_F32) return true;
-    return eff.topk_keep >= 0 && K <= group_filter_topk(ix->dtype) &&
-           (double)ix->L * ix->mean_hit_bucket >= (double)kShareListed;
+    if (ix->dtype == QW_F32) return float_shares(ix, Q);
+    return eff.topk_keep >= 0 && K <= group_filter_topk(ix->dtype) && listed_ids(ix) >= (double)kShareListed;
 }
 
 // keys: key lists for the select kernel, the order dealt to the XCDs xchunk
@@ -707,11 +725,12 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     const int gmax = std::min(kGroupedSetLog2 - kCmin, plan.ncls - 2);
     const bool use_grouped = share && gmax >= 2 && group_held(ix, Q);
     const uint32_t minrun = ix->dtype == QW_F32 ? 1u : kMinRun;
+    // (large workgroups take a query each, in any order)
+    const bool ordered = o.group && !wide;
     // the binning kernel runs the count model itself; the grouped schedule
     // takes the predictions from the inference kernel
-    QW_TRY(front(ix, queries, Q, QW_FORM_FAST, s, ev,
-                 learned && (o.group || use_grouped) ? w.feats.as<float>() : nullptr,
-                 o.group || use_grouped ? w.bmh.as<uint32_t>() : nullptr, clear_in_moves));
+    QW_TRY(front(ix, queries, Q, QW_FORM_FAST, s, ev, learned && ordered ? w.feats.as<float>() : nullptr,
+                 ordered ? w.bmh.as<uint32_t>() : nullptr, clear_in_moves));
     if (ev) QW_HIP(hipEventRecord(ev[2], s));
     unsigned long long *seg = w.binoff.as<unsigned long long>();
     unsigned long long *ccount = c64(ix) + C_CLASS;
@@ -720,7 +739,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
     auto schedule = [&](const int32_t *ex, const float *pl, int force_max, bool counting,
                         const int32_t **order) -> qw_status {
         const bool grouped = use_grouped && !counting;
-        if (!o.group && !grouped) {  // classes only: one binning kernel (with the count model)
+        if (!ordered) {  // classes only: one binning kernel (with the count model)
             QW_TRY(launch_classify_bin(Q, ix->L, ix->n, layer_sizes(ix), ex,
                                        learned && !ex ? ix->mlp_lane.as<uint32_t>() : nullptr,
                                        ix->mlp_margin, force_max, kCmin, plan.cfloor, plan.cmax,
@@ -820,7 +839,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.cls_hi = hi;
             a.queue_only = queue_only;
             a.cap_base = kCmin;
-            a.xchunk = o.group && !wide ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
+            a.xchunk = ordered ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
             a.xwork = slot < 0 ? c32(ix) + W_GWORK + 2 * kXcd : c32(ix) + W_XWORK + kXcd * slot;
             a.in_list = in_list;
             a.in_count = in_count;
@@ -1014,7 +1033,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         QW_TRY(launch_fill_u32(c32(ix) + W_XWORK, 0u, kXcd * (kMaxClasses + 1), s));
         QW_TRY(launch_fill_u32(c32(ix) + W_QMERGED, 0u, 1, s));
         exact = reinterpret_cast<const int32_t *>(w.ucount.p);
-    } else if (learned && (o.group || use_grouped)) {
+    } else if (learned && ordered) {
         QW_TRY(launch_mlp_predict_bf16(ix->mlp_dev.as<float>(), ix->L, w.feats.as<float>(), Q,
                                        w.mlpout.as<float>(), s));
         pred_log = w.mlpout.as<float>();
@@ -1210,7 +1229,8 @@ bool qw::resolve_fast_auto(qw_index *ix, int64_t Q, int32_t K, qw_opts *o, bool 
     if (o->stage_split == 0) o->stage_split = -1;  // off unless tuned or asked for
     if (o->dedup == 0) o->dedup = plan.wgrid > 0 && plan.wave_default ? 2 : 1;
     if (o->group < 0)
-        o->group = ix->dp * (ix->dtype == QW_U8 ? 1 : 4) >= kGroupRowBytes || Q >= kGroupQueries;
+        o->group = Q >= kGroupQueries ||
+                   (ix->dtype == QW_F32 ? ix->dp * 4 >= kGroupRowBytes && float_shares(ix, Q) : ix->dp >= kGroupRowBytes);
     if (o->xchunk == 0 && o->group) o->xchunk = (int32_t)kXcdChunk;
     if (!o->group) o->xchunk = 0;  // unused without grouping
     return tuned;
@@ -1427,7 +1447,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
             if (ix->nl > 64 || rb > kStageMaxRow || stage_lds_bytes(rb, eff.stage_split, &icn, &dcn) > ix->lds_max)
                 eff.stage_split = -1;
         }
-        const bool share = group_shares(ix, K, eff);
+        const bool share = group_shares(ix, Q, K, eff);
         // few queries: nothing else fills the chip (left to the caller's choice of
         // kernel, or a tuned one other than the built-in, where there is one)
         bool chosen = opt.dedup != 0;

@@ -787,6 +787,31 @@ def test_group_key_bound(K, n, Q, same):
     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K,pays", [
+    (1500, 1152, 70, 3, 8, 5, 10.0, 10, True),      # longest rows of a group
+    (6000, 24, 600, 300, 40, 3, 0.8, 5, True),      # small sets, many groups
+    (30, 48, 40, 1, 40, 2, 50.0, 37, True),         # fewer candidates than K
+    (4000, 256, 1, 200, 6, 4, 3.0, 10, False), (4000, 256, 768, 200, 6, 4, 3.0, 10, False),  # a large workgroup each
+    (4000, 256, 769, 200, 6, 4, 3.0, 10, False), (4000, 300, 1500, 200, 6, 4, 3.0, 100, False),  # a workgroup each
+])
+def test_float_sharing_rule(n, d, Q, ncl, L, k, w, K, pays):
+    """Queries share workgroups where they list enough ids; the automatic order is
+    the grouped one only then."""
+    data, q = grouped_workload(n + d, n, d, Q, ncl, 0.05)
+    p = synth.hash_params(5, L, k, d, w)
+    ix = build(data, p.a, p.b(), w)
+    listed = L * ix.info()["mean_hit_bucket"]
+    assert pays == (listed >= 1024 or Q * listed ** 2 * 4 * (-(-d // 16) * 16) >= 2 ** 41)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
+    for sched in (lib.QW_SCHED_SUM, lib.QW_SCHED_ACTUAL):
+        for group in (-1, 0, 1):
+            for graph in (0, 1):
+                ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=group, sched=sched, graph=graph), stats=True)
+                check_topk(ids, dist, ids_o, dist_o, False)
+                assert st["cand_unique"] == int(cnt_o.sum())
+                assert st["group_used"] == (group if group >= 0 else int(pays and d >= 241))
+
+
 @pytest.mark.parametrize("Q,n", [(2, 33), (5, 96), (32, 320), (32, 480), (40, 200), (32, 544)])
 @pytest.mark.parametrize("K", [1, 5])
 def test_group_error_band_of_few_rows(Q, n, K):
@@ -799,7 +824,7 @@ def test_group_error_band_of_few_rows(Q, n, K):
     q = rng.random((Q, d), dtype=np.float32)
     near = q + rng.normal(0, 0.006, (Q, d)).astype(np.float32)
     data = near[np.arange(n) % Q] + rng.normal(0, 1e-6, (n, d)).astype(np.float32)
-    p = synth.hash_params(5, 3, 2, d, w)
+    p = synth.hash_params(5, 32, 2, d, w)  # 32 n ids listed: enough to share
     p.a[:, :, -1] = 0
     ix = build(data, p.a, p.b(), w)
     ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), w, K)
