@@ -831,6 +831,11 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
         auto launch_range = [&](int lo, int hi, const int32_t *in_list, const uint32_t *in_count,
                                 int32_t *ovf_list, uint32_t *ovf_count, int slot, int queue_only,
                                 hipStream_t st, int gpart = 0) -> qw_status {
+            // of few queries those that groups give back (slot < 0) take large
+            // workgroups too, any XCD's: 64 of 3,100 candidates over 200,000 x
+            // 256 float rows, some of them given back, took 0.53 ms when these had 256
+            // threads each on one XCD, 0.35 so (0.41 all query by query in 256)
+            const bool large = wide || (slot < 0 && Q <= kWideBlockQueries);
             DedupArgs a;
             std::memset(&a, 0, sizeof(a));
             a.order = order;
@@ -839,7 +844,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             a.cls_hi = hi;
             a.queue_only = queue_only;
             a.cap_base = kCmin;
-            a.xchunk = ordered ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
+            a.xchunk = ordered && !large ? (o.xchunk > 0 ? (uint32_t)o.xchunk : kXcdChunk) : 1u;
             a.xwork = slot < 0 ? c32(ix) + W_GWORK + 2 * kXcd : c32(ix) + W_XWORK + kXcd * slot;
             a.in_list = in_list;
             a.in_count = in_count;
@@ -885,7 +890,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             } else {
                 a.cap_log2 = (uint32_t)(kCmin + hi);  // LDS size; also the queue's class
                 a.limit = 0xFFFFFFFFu;                 // each set's own 3/4 bound
-                a.wide = wide ? 1 : 0;
+                a.wide = large ? 1 : 0;
             }
             return launch_dedup(a, a.wide ? (int)std::min<int64_t>(ceil_div(Q, kXcd) * kXcd, ix->cus) : plan.dgrid[hi], st);
         };

@@ -787,6 +787,21 @@ def test_group_key_bound(K, n, Q, same):
     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("Q", [1, 33, 768, 769])  # large workgroups up to 768
+@pytest.mark.parametrize("n,K", [(9000, 10), (16000, 49)])  # beyond a group's set; and any LDS set
+def test_queries_given_back_by_groups(Q, n, K):
+    data, q = grouped_workload(n + Q, n, 16, Q, 1, 0.08)
+    data[: n // 3] += 40  # a second region: half of the queries' groups fit
+    q[::2] += 40
+    p = synth.hash_params(5, 4, 2, 16, 50.0)
+    ix = build(data, p.a, p.b(), 50.0)
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), 50.0, K)
+    for graph in (0, 1):
+        ids, dist, st = ix.query(dev(q), K, lib.make_opts(group=1, graph=graph), stats=True)
+        check_topk(ids, dist, ids_o, dist_o, False)
+        assert st["cand_unique"] == int(cnt_o.sum())
+
+
 @pytest.mark.parametrize("n,d,Q,ncl,L,k,w,K,pays", [
     (1500, 1152, 70, 3, 8, 5, 10.0, 10, True),      # longest rows of a group
     (6000, 24, 600, 300, 40, 3, 0.8, 5, True),      # small sets, many groups
