@@ -51,7 +51,16 @@ constexpr int kGroupedSetLog2 = 14;
 // of few candidates cost little by themselves: 51,000 skewed ones that list 790
 // ids each (150,000 x 50) took 0.58 ms query by query, 0.73 shared; 59,000 that
 // list 1,660 (460,000 x 73) 1.24 and 0.79.
+// Few queries leave the chip room for all of them: large workgroups answer up to
+// kWideQueries (below), and within two rounds of the per-query kernel the queries
+// left over take about as long as all would, so a workload shares only where 15 of
+// 16 of its queries do, a larger one where a quarter does.  In the order of before
+// and shared, skewed queries: 200,000 x 256 by waves, 64 219 and 223 us, 2,000 265 and
+// 366, 4,500 429 and 450, 9,000 591 and 514; 50,000 x 1,100 by workgroups, 2,000 632
+// and 692, 4,000 1,060 and 548.  All around 3 points: 200,000 x 256, 520 235 and 163,
+// 4,500 422 and 306; 50,000 x 1,100, 1,000 576 and 265.
 constexpr uint32_t kMinRun = 8, kShareGain = 8, kShareListed = 1024;
+constexpr uint32_t kSharePart = 4, kSharePartFew = 15;  // sixteenths
 // Float rows: finding the groups and their two kernels cost about 60 us, and the
 // fewer rows a query has the less of them a group shares: queries share from
 // kShareListed ids each on, or where their number times the square of the ids and
@@ -190,7 +199,8 @@ bool group_shares(const qw_index *ix, int64_t Q, int32_t K, const qw_opts &eff)
     if (eff.stage_split > 0 || !group_applies(ix->dtype, ix->dp, ix->nl, ix->lds_max)) return false;
     if (!eff.group) return false;
     if (ix->dtype == QW_F32) return float_shares(ix, Q);
-    return eff.topk_keep >= 0 && K <= group_filter_topk(ix->dtype) && listed_ids(ix) >= (double)kShareListed;
+    return eff.topk_keep >= 0 && K <= group_filter_topk(ix->dtype) && Q > kWideQueries &&
+           listed_ids(ix) >= (double)kShareListed;
 }
 
 // keys: key lists for the select kernel, the order dealt to the XCDs xchunk
@@ -937,6 +947,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
                 a.cls = w.vals.as<int32_t>();
                 a.seg = seg;
                 a.gain = kShareGain;
+                a.gain_part = Q <= 2 * (int64_t)(wave ? plan.wgrid : plan.dgrid[0]) ? kSharePartFew : kSharePart;
                 a.gain_listed = kShareListed;
                 a.groups2 = w.keys2.as<uint2>();
                 a.qlist2 = w.pred.as<int32_t>();

@@ -179,7 +179,6 @@ __device__ inline void group_give_back(const GroupedArgs &A, int32_t q)
 // counts its queries.
 constexpr int kGainLists = 8, kGainBlock = 1024, kGainGroups = kGainBlock / 64;
 constexpr uint32_t kGainMark = 0x80000000u;
-constexpr uint32_t kGainQueries = 4;  // a quarter of the queries at least
 __global__ __launch_bounds__(kGainBlock) void group_gain_kernel(GroupedArgs A)
 {
     __shared__ uint32_t s_queries;
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(kGainBlock) void group_split_kernel(GroupedArgs A)
     if (tid == 0) s_groups = s_queries = 0u;
     __syncthreads();
     uint2 gr = g < ng ? A.groups[g] : uint2{0u, 0u};
-    const bool share = (gr.y & kGainMark) && (uint64_t)A.gcount[kGroupCounts + 2] * kGainQueries >= (uint64_t)A.Q;
+    const bool share = (gr.y & kGainMark) && (uint64_t)A.gcount[kGroupCounts + 2] * 16u >= (uint64_t)A.Q * A.gain_part;
     gr.y &= ~kGainMark;
     const int32_t q = (uint32_t)j < gr.y ? A.order[gr.x + j] : -1;
     const int c = q >= 0 ? A.cls[q] : 0;

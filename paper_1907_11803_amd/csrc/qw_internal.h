@@ -609,6 +609,7 @@ struct GroupedArgs {
     // gain > 0: only groups whose queries list at least gain times the ids of
     // their distinct buckets share a workgroup: groups2, their queries qlist2
     uint32_t gain, gain_listed;  // and gain_listed ids per query
+    uint32_t gain_part;          // sixteenths of the Q queries that such groups hold at least, else none
     uint2 *groups2;
     int32_t *qlist2;
     void *recs;                  // group_rec_bytes

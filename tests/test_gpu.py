@@ -884,6 +884,28 @@ def test_grouped_uint8_queries(n, d, Q, ncl, L, k, w, K, probes):
                     assert st["cand_unique"] == int(cnt_o.sum())
 
 
+@pytest.mark.parametrize("Q", [512, 513, 1100, 9000])  # none share; few: nearly all or none; a quarter at least
+@pytest.mark.parametrize("alone", [0.0, 0.04, 0.3, 0.9])  # part of the queries that are near no others
+def test_uint8_sharing_rule(Q, alone):
+    data, q = grouped_workload(77, 6000, 48, 1200, 6, 0.08)
+    rng = np.random.default_rng(Q)
+    more = rng.random((3000, 48), dtype=np.float32)  # a point each for the queries near no others
+    q = q[rng.integers(0, 1200, Q)]
+    far = rng.random(Q) < alone
+    q[far] = more[rng.integers(0, 3000, far.sum())]
+    data = np.concatenate([data, more])
+    data, q = (np.clip(np.rint(v * 255), 0, 255).astype(np.uint8) for v in (data, q))
+    p = synth.hash_params(5, 8, 6, 48, 1200.0)
+    ix = build(data, p.a, p.b(), 1200.0)
+    assert ix.info()["mean_hit_bucket"] * 8 >= 1024
+    ids_o, dist_o, cnt_o = oracle.lsh_query(data, q, p.a, p.b(), 1200.0, 10)
+    for dedup in (0, 1, 2):
+        for graph in (0, 1):
+            ids, dist, st = ix.query(dev(q), 10, lib.make_opts(group=1, dedup=dedup, graph=graph), stats=True)
+            check_topk(ids, dist, ids_o, dist_o, True)
+            assert st["cand_unique"] == int(cnt_o.sum())
+
+
 @pytest.mark.parametrize("dtype", ["u8", "f32"])
 @pytest.mark.parametrize("Q,big", [(257, 9000), (1025, 9000), (1025, 0)])
 def test_grouped_order_classes_beyond_groups(dtype, Q, big):
