@@ -542,6 +542,7 @@ struct VerifyGroup {
     const int32_t *q;
     bool pieces;
     int64_t row0, stride;      // brute force: the rows' ids instead of `rows`
+    int64_t at0;               // brute force without a bound: row r's key goes to place at0 + r (else -1)
 };
 // Bytes of a row per step (a 16-byte part per quarter of the lanes), and steps
 // whose loads are in flight together.
@@ -697,12 +698,24 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
             }
         }
     };
-    // each query's keys of the tile within its bound: lanes of one row16 share
+    // each query's keys of tile t within its bound: lanes of one row16 share
     // a query, one of them takes the room for all
-    auto emit = [&]() {
+    auto emit = [&](int t) {
 #pragma unroll
         for (int b = 0; b < CB; ++b) {
             const int j = b * 16 + row16;
+            if (DENSE && G.at0 >= 0) {  // uniform: every key, by its row
+                unsigned long long *out = A.keys + G.base[j] + G.at0;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t id = (uint32_t)__shfl((int)(h ? e1.x : e0.x), 4 * kg + i);
+                        if (key[h][b][i] != kNoKey)
+                            out[t * 32 + h * 16 + 4 * kg + i] = ((unsigned long long)key[h][b][i] << 32) | id;
+                    }
+                continue;
+            }
             const uint32_t thr = G.thr[j];
             uint32_t c = 0;
 #pragma unroll
@@ -758,7 +771,7 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
                             min(min(key[h][b][0], key[h][b][1]), min(key[h][b][2], key[h][b][3]));
                 bounds();
             }
-            emit();
+            emit(t);
 #pragma unroll
             for (int b = 0; b < CB; ++b) acc0[b] = acc1[b] = acc_t{0, 0, 0, 0};
             xn0 = xn1 = 0;
@@ -784,7 +797,8 @@ __device__ inline void verify_rows(const GroupedArgs &A, const VerifyGroup &G)
 
 // q' of the group's queries (zeros in the columns of others) and |q'|^2; float
 // rows: q0 and the keys' error, once (`first`) for the select kernel too.
-template <int DT>
+// DENSE: the flag has no other writer.
+template <int DT, bool DENSE>
 __device__ inline void stage_queries(const GroupedArgs &A, const int32_t *s_q, uint32_t keep, int j0, bool first,
                                      unsigned char *qp, float *q0s, uint32_t *s_qn, float *s_err)
 {
@@ -817,7 +831,8 @@ __device__ inline void stage_queries(const GroupedArgs &A, const int32_t *s_q, u
                 s_err[j] = err;
                 if (in && first) {
                     A.abs_err[q] = err;
-                    if (!(acc < 1e30f)) A.flag[q] = 1u;
+                    if (DENSE) A.flag[q] = acc < 1e30f ? 0u : 1u;
+                    else if (!(acc < 1e30f)) A.flag[q] = 1u;
                 }
             }
         } else {
@@ -889,7 +904,7 @@ __global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_ke
         const int cols = (keep >> 16) ? 32 : 16;
         // (the piece of the first rows: pieces before it are empty where there are
         // fewer tiles than pieces)
-        stage_queries<DT>(A, s_q, keep, rec.j0, r0 == 0u, qp, q0s, s_qn, s_err);
+        stage_queries<DT, false>(A, s_q, keep, rec.j0, r0 == 0u, qp, q0s, s_qn, s_err);
         for (int j = tid; j < cols; j += kVB<DT>) {
             const int32_t q = s_q[j];
             if ((keep >> j) & 1u) {
@@ -899,7 +914,7 @@ __global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_ke
         }
         __syncthreads();
         VerifyGroup G = {A.glist + rec.rows + r0, r1 - r0, keep, qp, q0s, s_qn, minima, s_thr, s_err,
-                         s_base, s_room, s_pos, s_q, np > 1u, 0, 0};
+                         s_base, s_room, s_pos, s_q, np > 1u, 0, 0, -1};
         if (cols == 32) verify_rows<DT, 2, false>(A, G);
         else verify_rows<DT, 1, false>(A, G);
         __syncthreads();  // every key is counted; q' is read before the next group's
@@ -908,20 +923,11 @@ __global__ __launch_bounds__(kVB<DT>, DT == QW_F32 ? 3 : 4) void group_verify_ke
     }
 }
 
-// Empty lists of cap keys; ovf_count: the fallback queue's two words.
-__global__ __launch_bounds__(kBlock) void dense_init_kernel(GroupedArgs A, DenseArgs D)
-{
-    const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q < 2) A.ovf_count[q] = 0u;
-    if (q >= A.Q) return;
-    A.flag[q] = A.kpos[q] = 0u;
-    A.kroom[q] = D.cap;
-    A.coff[q] = (unsigned long long)q * D.cap;
-}
-
 // Brute force over float rows: 32 consecutive queries and a piece of the rows per
 // item, items of the same piece on one XCD (its L2 holds the rows while the
-// queries pass).  Bound by the matrix cores' FP32 rate from 32 queries on, by the
+// queries pass).  Without a bound (the sample, or few rows) every row's key has its
+// place in a query's list, and the item of the first rows sets up the lists and the
+// fallback queue (ovf_count: its two words).  Bound by the matrix cores' FP32 rate from 32 queries on, by the
 // rows' bytes below; rows beyond about 1,100 columns (LDS) stay with the
 // per-query kernel, one workgroup per query.
 // Measured (whole calls): 25 queries over 186,000 x 512: 44 ms with a workgroup
@@ -954,12 +960,20 @@ __global__ __launch_bounds__(kVB<QW_F32>, 3) void dense_verify_kernel(GroupedArg
             s_thr[tid] = tid < m && D.bound ? D.bound[q] : kNoKey;
             s_room[tid] = D.cap;
             s_base[tid] = (unsigned long long)q * D.cap;
+            if (!D.bound && r0 == 0) {
+                if (q < 2) A.ovf_count[q] = 0u;
+                if (tid < m) {
+                    A.kpos[q] = (uint32_t)D.rows;
+                    A.kroom[q] = D.cap;
+                    A.coff[q] = (unsigned long long)q * D.cap;
+                }
+            }
         }
         __syncthreads();
-        stage_queries<QW_F32>(A, s_q, keep, 0, !D.bound && r0 == 0, qp, q0s, s_qn, s_err);
+        stage_queries<QW_F32, true>(A, s_q, keep, 0, !D.bound && r0 == 0, qp, q0s, s_qn, s_err);
         __syncthreads();
         VerifyGroup G = {nullptr, (uint32_t)(r1 - r0), keep, qp, q0s, s_qn, nullptr, s_thr, s_err,
-                         s_base, s_room, nullptr, s_q, true, r0 * D.stride, D.stride};
+                         s_base, s_room, nullptr, s_q, true, r0 * D.stride, D.stride, D.bound ? -1 : r0};
         if (m > 16) verify_rows<QW_F32, 2, true>(A, G);
         else verify_rows<QW_F32, 1, true>(A, G);
         __syncthreads();  // q' is read before the next item's
@@ -976,7 +990,7 @@ __global__ __launch_bounds__(kBlock) void dense_bound_kernel(GroupedArgs A, Dens
     __shared__ uint32_t hist[256], s_pick, s_left;
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t q = blockIdx.x;
-    const uint32_t n = min(A.kpos[q], (uint32_t)D.rows);
+    const uint32_t n = (uint32_t)D.rows;
     const unsigned long long *keys = A.keys + q * D.cap;
     for (uint32_t i = tid; i < n; i += kBlock) v[i] = (uint32_t)(keys[i] >> 32);
     uint32_t t = 0, left = (uint32_t)A.K;  // the K-th smallest's bits so far; its rank among their equals
@@ -1120,8 +1134,6 @@ qw_status launch_dense(const DensePlan &p, GroupedArgs a, int64_t n, uint32_t *b
         return QW_OK;
     };
     const DenseArgs d = {p.sample, 0, bound, p.cap, 0};
-    dense_init_kernel<<<(unsigned)ceil_div(a.Q, kBlock), kBlock, 0, s>>>(a, d);
-    QW_HIP(hipGetLastError());
     if (p.sample == n) return pass(n, 1, nullptr);
     QW_TRY(pass(p.sample, n / p.sample, nullptr));
     dense_bound_kernel<<<(unsigned)a.Q, kBlock, sizeof(uint32_t) * (size_t)p.sample, s>>>(a, d);
