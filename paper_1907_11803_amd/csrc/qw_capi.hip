@@ -76,15 +76,13 @@ constexpr double kShareWork = double(int64_t(1) << 41);
 // 64 queries 99 -> 75 us and 128 -> 73, 512 120 -> 116 and 133 -> 110, 1,024 123 ->
 // 157 and 162 -> 158.  Where a wave would take a query it is one launch fewer, and
 // as fast for few listed ids: a single query 64 us by a wave and 65 so, ten that
-// list 450 ids each 61 and 71; so only from nl * mean_hit_bucket = kWideListed on,
-// beyond a large workgroup per CU from kWideListedMore (500,000 x 96, 256 and 300
-// queries: listing 860 ids 86 and 87 us by waves, 75 and 92 so; 1,110 105 and 94, 77
-// and 96; 1,430 109 and 109, 77 and 96).  Waves fill the chip from 513
+// list 450 ids each 61 and 71; so only from nl * mean_hit_bucket = kWideListed on
+// (at 650 both took 95 us, at 1,450 148 and 105).  Waves fill the chip from 513
 // queries on (576 probed ones 120 us by them, 133 so), workgroups of 256 threads
 // only from 769, the fourth round of large ones: 576 of the plain union 133 and
 // 127, 768 of 300,007 x 100 with K = 100 136 and 130 but 832 139 and 143.
 constexpr int64_t kWideQueries = 512, kWideBlockQueries = 768;
-constexpr double kWideListed = 700.0, kWideListedMore = 1050.0;
+constexpr double kWideListed = 700.0;
 constexpr uint32_t kStageChunk = 16;   // staged kernel: consecutive items per workgroup run
 constexpr int kStageBlocksPerCu = 2;   // its LDS (80 KiB) allows two workgroups per CU
 constexpr int64_t kCandPerQuery = 4096;  // pair space reserved per query (beyond: fallback)
@@ -1477,8 +1475,7 @@ qw_status qw_query_workload(qw_index *ix, const void *queries, int64_t Q, int32_
         }
         const bool wide = Q <= (eff.dedup == 1 ? kWideBlockQueries : kWideQueries) && !chosen && !share &&
                           eff.stage_split <= 0 && ix->nl <= 64 &&
-                          (eff.dedup == 1 ||
-                           (Q > 1 && ix->nl * ix->mean_hit_bucket >= (Q <= ix->cus ? kWideListed : kWideListedMore)));
+                          (eff.dedup == 1 || (Q > 1 && ix->nl * ix->mean_hit_bucket >= kWideListed));
         QW_TRY(ensure_ws(ix, Q, &plan, !(eff.topk_keep >= 0 && plan.topk) || eff.stage_split > 0,
                          (eff.group && !wide) || eff.stage_split > 0 ? kXcdChunk : 1, share ? Q : 0, K));
         if (opt.timing || !opt.graph) {
