@@ -291,8 +291,16 @@ qw_status qw_autotune(qw_index *ix, const void *queries, int64_t Q, int32_t K,
                       const qw_opts *base, const char *cache_path, void *stream,
                       qw_tune_result *out);
 
-/* Release the index and all device memory it holds (NULL is a no-op). */
+/* Release the index and all device memory it holds (NULL is a no-op).  The library
+ * keeps up to 1 GiB of released blocks per device for the indexes built next (a
+ * program that builds index after index would wait for the driver to clear them
+ * each time) while at least an eighth of the device's memory is free; they go back
+ * when an allocation of the library does not fit beside them, or with qw_trim. */
 void qw_free_index(qw_index *ix);
+
+/* Return the blocks that the library keeps on the current device to the driver.
+ * QW_EDEVICE when there is no device.  May be called from any thread. */
+qw_status qw_trim(void);
 
 /* Static string naming a status code. */
 const char *qw_status_string(qw_status s);

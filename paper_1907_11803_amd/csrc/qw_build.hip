@@ -908,8 +908,9 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
     }
     ix->tab_pb = pb;
     QW_HIP(hipStreamSynchronize(s));  // the temporaries and the host arrays go
-    arena.retire(ix->device);
-    pbuf.retire(ix->device);
+    const int pool = pool_device(ix->device);
+    arena.retire(pool);
+    pbuf.retire(pool);
     double sb = 0.0;
     for (int32_t l = 0; l < L; ++l) sb += (double)hst[l].sumsq / (double)n;
     ix->mean_hit_bucket = sb / L;

@@ -1313,6 +1313,7 @@ void qw_free_index(qw_index *ix)
     int dev = -1;
     if (hipGetDevice(&dev) == hipSuccess && dev == ix->device) {
         Workspace &w = ix->ws;
+        dev = pool_device(dev);
         for (DevBuf *b : {&ix->data, &ix->ids, &w.qpad, &w.h, &w.bstart, &w.bsize, &w.ovf, &w.gscratch,
                           &w.order, &w.pkeys, &w.glist, &w.grecs, &w.bf_min, &w.bf_keys})
             b->retire(dev);
@@ -1320,6 +1321,14 @@ void qw_free_index(qw_index *ix)
     }
     (void)hipGetLastError();
     delete ix;  // the destructor releases the rest, the side stream and its events
+}
+
+qw_status qw_trim(void)
+{
+    int dev = -1;
+    QW_HIP(hipGetDevice(&dev));
+    (void)pool_give_back(dev);
+    return QW_OK;
 }
 
 qw_status qw_get_index_info(const qw_index *ix, qw_index_info *info)

@@ -101,7 +101,7 @@ struct DevBuf {
     qw_status ensure(size_t want);  // grows (contents discarded); never shrinks
     void release();
     // release() for memory of device `dev` that no enqueued work uses any
-    // more: the block may stay in the device's pool (see pool_put)
+    // more: the block may stay in the device's pool (see pool_put; -1: never)
     void retire(int dev);
     void view(void *mem, size_t n)
     {
@@ -115,6 +115,8 @@ struct DevBuf {
 
 // Returns the device's pooled blocks to the driver; true when it held any.
 bool pool_give_back(int dev);
+// What to pass to retire(): the current device `dev`, -1 while its memory is scarce.
+int pool_device(int dev);
 
 // ---------------------------------------------------------------- index
 // Probe-table entry: a bucket of one layer, keyed by its packed k-tuple.

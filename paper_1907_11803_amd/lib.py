@@ -103,6 +103,7 @@ SIGNATURES = {
     "qw_query_workload_noalloc": (ctypes.c_int, [_P, _P, _I64, _I32, _P, _P, _P]),
     "qw_autotune": (ctypes.c_int, [_P, _P, _I64, _I32, _P, ctypes.c_char_p, _P, _P]),
     "qw_free_index": (None, [_P]),
+    "qw_trim": (ctypes.c_int, []),
     "qw_get_index_info": (ctypes.c_int, [_P, _P]),
     "qw_hash": (ctypes.c_int, [_P, _P, _I64, _I32, _P, _P, _P]),
     "qw_bucket_sizes": (ctypes.c_int, [_P, _P, _I64, _P, _P]),
@@ -255,6 +256,11 @@ def qw_autotune(ix, queries: torch.Tensor, K: int, cache_path: str, opts: Option
 def qw_free_index(ix):
     if ix:
         load().qw_free_index(ix)
+
+
+def qw_trim():
+    """Return the device memory that the library keeps for the next indexes."""
+    _check(load().qw_trim(), "qw_trim")
 
 
 def qw_get_index_info(ix) -> dict:

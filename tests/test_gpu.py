@@ -513,6 +513,35 @@ def test_bruteforce_matches_oracle(dtype):
     check_topk(ids, dist, ids_o, dist_o, dtype == "u8")
 
 
+def test_trim_returns_released_memory():
+    rng = np.random.default_rng(3)
+    data = rng.integers(0, 256, (400000, 64), dtype=np.uint8)
+    p = synth.hash_params(7, 10, 8, 64, 900.0)
+    x, a, b = dev(data), dev(p.a), dev(p.b())
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    def once():
+        ix = lib.Index(x, a, b, 900.0)
+        ix.bruteforce(x[:100], 10)
+        ix.query(x[:100], 10)
+        ix.close()
+
+    once()  # what the runtime itself allocates at first use stays
+    lib.qw_trim()
+    before = free()
+    once()
+    assert free() < before - (100 << 20)  # kept for the next index
+    lib.qw_trim()
+    assert free() >= before
+    lib.qw_trim()  # nothing left to return
+    once()
+    lib.qw_trim()
+    assert free() >= before
+
+
 @pytest.mark.parametrize("n,d,Q,K", [
     (4096, 16, 1, 1), (4097, 17, 3, 10), (5000, 64, 16, 64), (9001, 65, 17, 65),   # one, two steps
     (20011, 128, 65, 10), (4224, 200, 129, 37), (6001, 256, 257, 100),             # four steps
