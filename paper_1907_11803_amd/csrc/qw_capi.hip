@@ -788,7 +788,7 @@ qw_status enqueue_fast(qw_index *ix, const Plan &plan, const void *queries, int6
             return launch_group_order(a, reinterpret_cast<uint32_t *>(w.grecs.as<char>() + group_rec_bytes(Q)), s);
         }
         QW_TRY(launch_classify(Q, ix->L, ix->n, layer_mh(ix), layer_sizes(ix), ex, pl, ix->mlp_margin,
-                               force_max, kCmin, plan.cfloor, plan.cmax, plan.ncls, o.group,
+                               force_max, kCmin, plan.cfloor, plan.cmax, plan.ncls,
                                w.keys.as<unsigned long long>(), w.vals.as<int32_t>(), ccount, s));
         bool alt = false;
         QW_TRY(radix_sort_pairs(w.keys.as<unsigned long long>(), w.vals.as<int32_t>(), Q, 0, 24,

@@ -144,7 +144,9 @@ struct Workspace {
     DevBuf qpad, h, bstart, bsize, bmh, lsum, lmh, moves, pred, feats, keys, keys2, vals,
         vals2, hist, order, binoff, counters, ovf, gscratch, mlpout, scan;
     // flat pipeline
-    DevBuf ucount, coff, flag, pkeys, fb;  // flag: [3 Q], then the keys' absolute errors, then key counts
+    // flag: four arrays of Q words: flags, the keys' absolute errors, keys written
+    // and room for them (the last three of queries in groups)
+    DevBuf ucount, coff, flag, pkeys, fb;
     DevBuf glist, grecs;  // groups of queries: their candidate rows, their records
     // brute force: stream minima, per-query state, key lists
     DevBuf bf_min, bf_state, bf_keys;
@@ -492,9 +494,8 @@ qw_status launch_group_order(const GroupOrderArgs &a, uint32_t *tab, hipStream_t
 qw_status launch_classify(int64_t Q, int32_t L, int64_t n,
                           const uint32_t *bmh, const uint32_t *bsize, const int32_t *exact,
                           const float *pred_log, float margin, int32_t force_max, int32_t cmin,
-                          int32_t cfloor, int32_t cmax, int32_t ncls, int32_t group,
-                          unsigned long long *keys,
-                          int32_t *vals, unsigned long long *class_count, hipStream_t s);
+                          int32_t cfloor, int32_t cmax, int32_t ncls, unsigned long long *keys, int32_t *vals,
+                          unsigned long long *class_count, hipStream_t s);
 qw_status launch_segments(const unsigned long long *class_count, int32_t ncls,
                           unsigned long long *seg, hipStream_t s);
 // Classes without bucket grouping in one kernel: class c's queries to
@@ -574,7 +575,7 @@ struct DedupArgs {
 };
 
 
-// Several queries per workgroup over float rows (qw_group.hip).
+// Several queries per workgroup (qw_group.hip).
 struct GroupedArgs {
     int32_t dtype;
     const int32_t *order;

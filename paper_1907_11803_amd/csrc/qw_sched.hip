@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(
     int64_t Q, int32_t L, int64_t n,
     const uint32_t *__restrict__ bmh, const uint32_t *__restrict__ bsize,
     const int32_t *__restrict__ exact, const float *__restrict__ pred_log, float margin,
-    int32_t force_max, int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls, int32_t group,
+    int32_t force_max, int32_t cmin, int32_t cfloor, int32_t cmax, int32_t ncls,
     unsigned long long *__restrict__ keys, int32_t *__restrict__ vals,
     unsigned long long *class_count)
 {
@@ -343,13 +343,9 @@ __global__ __launch_bounds__(kBlock) void classify_kernel(
         const int cls = class_of(tsum, n, exact, q, pred_log != nullptr,
                                  pred_log ? pred_log[q] : 0.f, margin, force_max, cmin, cfloor,
                                  cmax, ncls);
-        uint32_t g = 0;
-        if (group) {  // min-hash of C(q): misses carry 0xFFFFFFFF
-            uint32_t m = 0xFFFFFFFFu;
-            for (int32_t l = 0; l < L; ++l) m = min(m, bmh[q * L + l]);
-            g = mix32(m) & 0xFFFFu;
-        }
-        keys[q] = ((unsigned long long)cls << 16) | g;
+        uint32_t m = 0xFFFFFFFFu;  // min-hash of C(q): misses carry 0xFFFFFFFF
+        for (int32_t l = 0; l < L; ++l) m = min(m, bmh[q * L + l]);
+        keys[q] = ((unsigned long long)cls << 16) | (mix32(m) & 0xFFFFu);
         vals[q] = (int32_t)q;
         atomicAdd(&hist[cls], 1u);
     }
@@ -467,14 +463,13 @@ qw_status launch_classify_bin(int64_t Q, int32_t L, int64_t n, const uint32_t *b
 qw_status launch_classify(int64_t Q, int32_t L, int64_t n,
                           const uint32_t *bmh, const uint32_t *bsize, const int32_t *exact,
                           const float *pred_log, float margin, int32_t force_max, int32_t cmin,
-                          int32_t cfloor, int32_t cmax, int32_t ncls, int32_t group,
-                          unsigned long long *keys, int32_t *vals,
+                          int32_t cfloor, int32_t cmax, int32_t ncls, unsigned long long *keys, int32_t *vals,
                           unsigned long long *class_count, hipStream_t s)
 {
     if (Q <= 0) return QW_OK;
     int g = (int)std::min<int64_t>(1024, ceil_div(Q, kBlock));
     classify_kernel<<<g, kBlock, 0, s>>>(Q, L, n, bmh, bsize, exact, pred_log, margin,
-                                         force_max, cmin, cfloor, cmax, ncls, group, keys, vals,
+                                         force_max, cmin, cfloor, cmax, ncls, keys, vals,
                                          class_count);
     QW_HIP(hipGetLastError());
     return QW_OK;
