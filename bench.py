@@ -94,7 +94,9 @@ def candidate_roofline(st, kms, Q, d, elem, K, is_u8, config, w, probes, probe_t
     (distance, id) key for the select kernel or, when the kernel selects the
     top K itself (uint8 rows of at most 1024 bytes, K <= 16), the K output
     pairs.  Its time: the dedup stage of one step (HIP events in the library,
-    on the stream the kernel runs on)."""
+    on the stream the kernel runs on).  Float queries of the grouped order share
+    workgroups, which read a row once for all of them: bytes gathered query by
+    query are then no traffic, and no fraction of the peak is reported."""
     from paper_1907_11803_amd.profsum import source_hash
     topk_fused = is_u8 and K <= 16 and (d + 15) // 16 <= 64
     wave = topk_fused and st.get("dedup_used") == 2
@@ -104,10 +106,14 @@ def candidate_roofline(st, kms, Q, d, elem, K, is_u8, config, w, probes, probe_t
     else:
         kname = "dedup_kernel (dedup + verify + top-K)" if topk_fused else "dedup_kernel (dedup + verify)"
         kfile, ksrc = "dedup_verify", BLOCK_SOURCES
+    shared = not is_u8 and bool(st.get("group_used"))
+    if shared:
+        kname = "group_union_kernel + group_verify_kernel, dedup_kernel for the queries they give back"
     per_cand = d * elem + (0 if topk_fused else 8)
     kbytes = (4 * st["cand_total"] + st["cand_unique"] * per_cand + Q * d * elem +
               (8 * K * Q if topk_fused else 0))
-    achieved = kbytes / (kms * 1e-3) / 1e9 if kms > 0 else None
+    gathered = kbytes / (kms * 1e-3) / 1e9 if kms > 0 else None
+    achieved = None if shared else gathered
     traffic = None
     tfile = traffic_path(kfile, config, w, probes, probe_t)
     if os.path.exists(tfile):
@@ -126,6 +132,8 @@ def candidate_roofline(st, kms, Q, d, elem, K, is_u8, config, w, probes, probe_t
             "traffic_file": os.path.relpath(tfile, ROOT),
             "kernel_ms": round(kms, 4),
             "kernel_algorithmic_bytes": int(kbytes),
+            # rows counted once per query that lists them, over the kernels' time
+            "gathered_gbs": round(gathered, 1) if shared and gathered else None,
             # algorithmic bytes over counted bytes: rows that neighbouring queries
             # share served from L2 or the Infinity Cache (above 1, `frac` measures
             # that reuse, and `traffic_frac` is the HBM roofline fraction)

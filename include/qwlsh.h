@@ -341,10 +341,10 @@ qw_status qw_candidate_lists(qw_index *ix, const void *queries, int64_t Q,
  * Exact kNN of Q queries (device, Q x d) over all n indexed points -- the c-k-ANN
  * problem with every point a candidate (Section 3); the recall ground truth.
  * Same output conventions as qw_query_workload; 1 <= K <= 1024.
- * The matrix-core forms keep key lists in the index's workspace (256 MiB for
- * uint8 rows at most; for float rows 256 MiB, or the lists of 32 queries of
- * about 4 K n / 8192 keys where those need more); where the device has no room
- * for them, and in a stream capture, a kernel without lists answers.  Calls that
+ * The matrix-core forms keep key lists in the index's workspace: 128 MiB for
+ * uint8 rows at most, 256 MiB for float rows, or 32 queries' lists of about
+ * 4 K n / 8192 keys where those need more.  Where the device has no room for
+ * them, and in a stream capture, a kernel without lists answers.  Calls that
  * use them run one after the other, whatever their streams.
  */
 qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_t K,

@@ -18,6 +18,10 @@
 // hashing): 19.4 ms of kernels, 20 waits and 40 allocations a layer at a time
 // through a global table; 1.1 ms, 8 waits and 6 allocations in 4 chunks here,
 // the whole build with its first workload 32.7 ms before and 3.2 now.
+// A dominant bucket is the work of one workgroup, whose atomics meet on it.  All
+// points in one bucket of each of 20 layers (1M x 32): 38.8 ms (2,245 through the
+// global table), half of them 17.3 (1,149); 10M points, 4 layers of one bucket 271
+// (4,339).
 #include <algorithm>
 #include <cmath>
 #include <memory>
