@@ -674,7 +674,6 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
         ix->lds_max = (size_t)v;
     QW_HIP(hipStreamCreateWithFlags(&ix->side, hipStreamNonBlocking));
     for (auto &e : ix->fork) QW_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    QW_HIP(hipEventCreateWithFlags(&ix->brute, hipEventDisableTiming));
     ix->n = n;
     ix->d = d;
     ix->dp = (int32_t)((d + 15) / 16 * 16);
@@ -912,9 +911,8 @@ qw_status build_index(const void *data, int64_t n, int32_t d, int32_t dtype, con
     }
     ix->tab_pb = pb;
     QW_HIP(hipStreamSynchronize(s));  // the temporaries and the host arrays go
-    const int pool = pool_device(ix->device);
-    arena.retire(pool);
-    pbuf.retire(pool);
+    arena.retire(ix->device);
+    pbuf.retire(ix->device);
     double sb = 0.0;
     for (int32_t l = 0; l < L; ++l) sb += (double)hst[l].sumsq / (double)n;
     ix->mean_hit_bucket = sb / L;

@@ -1313,7 +1313,10 @@ void qw_free_index(qw_index *ix)
     int dev = -1;
     if (hipGetDevice(&dev) == hipSuccess && dev == ix->device) {
         Workspace &w = ix->ws;
-        dev = pool_device(dev);
+        if (memory_scarce()) {
+            (void)pool_give_back(dev);
+            dev = -1;
+        }
         for (DevBuf *b : {&ix->data, &ix->ids, &w.qpad, &w.h, &w.bstart, &w.bsize, &w.ovf, &w.gscratch,
                           &w.order, &w.pkeys, &w.glist, &w.grecs, &w.bf_min, &w.bf_keys})
             b->retire(dev);
@@ -1671,6 +1674,7 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     if ((mfma || dense) && !captured(s) && (mfma ? ensure_brute(ix, bp) : ensure_dense(ix, dp))) {
         // the key lists are the index's: after the call that used them last,
         // whose stream may be another (the event costs 5 us of such calls)
+        if (!ix->brute) QW_HIP(hipEventCreateWithFlags(&ix->brute, hipEventDisableTiming));
         QW_HIP(hipStreamWaitEvent(s, ix->brute, 0));
         const qw_status rc = mfma ? brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist))
                                   : brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));

@@ -28,10 +28,10 @@ void note_hip_error(hipError_t e, const char *what, const char *file, int line)
 // so a program that builds index after index pays for every byte it frees.
 // (1M x 128 in a loop of builds, a workload and the release: 3.0 ms; with every
 // block given back after it 4.3, and 19 once that memory has run out.)
-// Per device at most kPoolBytes in kPoolBlocks blocks, oldest out first, and only
-// while an eighth of the device is free; a block that kPoolAge later requests did
-// not want goes back to the driver, and all do when an allocation would not fit
-// beside them or the program asks (qw_trim).  Only memory that no enqueued work
+// Per device at most kPoolBytes in kPoolBlocks blocks, oldest out first.  A block
+// that kPoolAge later requests did not want goes back to the driver, and all do
+// when an allocation would not fit beside them, when an index is released while
+// less than an eighth of the device is free, or when the program asks (qw_trim).  Only memory that no enqueued work
 // uses is put here, so any thread or stream may take it.
 namespace {
 
@@ -117,12 +117,12 @@ bool pool_drain(int dev)
 
 bool pool_give_back(int dev) { return pool_drain(dev); }
 
-int pool_device(int dev)
+bool memory_scarce()
 {
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b >= total_b / 8) return dev;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) return free_b < total_b / 8;
     (void)hipGetLastError();
-    return -1;
+    return true;
 }
 
 qw_status DevBuf::ensure(size_t want)

@@ -115,8 +115,8 @@ struct DevBuf {
 
 // Returns the device's pooled blocks to the driver; true when it held any.
 bool pool_give_back(int dev);
-// What to pass to retire(): the current device `dev`, -1 while its memory is scarce.
-int pool_device(int dev);
+// Less than an eighth of the current device's memory is free.
+bool memory_scarce();
 
 // ---------------------------------------------------------------- index
 // Probe-table entry: a bucket of one layer, keyed by its packed k-tuple.
