@@ -1673,8 +1673,11 @@ qw_status qw_bruteforce_knn(qw_index *ix, const void *queries, int64_t Q, int32_
     const bool dense = !mfma && dense_plan(ix->n, ix->dtype, ix->dp, Q, K, ix->lds_max, &dp);
     if ((mfma || dense) && !captured(s) && (mfma ? ensure_brute(ix, bp) : ensure_dense(ix, dp))) {
         // the key lists are the index's: after the call that used them last,
-        // whose stream may be another (the event costs 5 us of such calls)
-        if (!ix->brute) QW_HIP(hipEventCreateWithFlags(&ix->brute, hipEventDisableTiming));
+        // whose stream may be another.  (Only this device reads them: an event
+        // with the system's fence costs 5 us of calls that follow each other, one
+        // without it 3.5.)
+        if (!ix->brute)
+            QW_HIP(hipEventCreateWithFlags(&ix->brute, hipEventDisableTiming | hipEventDisableSystemFence));
         QW_HIP(hipStreamWaitEvent(s, ix->brute, 0));
         const qw_status rc = mfma ? brute_mfma(ix, bp, a, Q, s, out_ids, static_cast<int32_t *>(out_dist))
                                   : brute_dense(ix, dp, a, Q, s, out_ids, static_cast<float *>(out_dist));
